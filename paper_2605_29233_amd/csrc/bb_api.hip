@@ -491,7 +491,7 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
         const bool fused = swiglu_out && (wide || !defer) && p.split_k == 1 && p.nt == 2;
         PROF_STAMPED(klass, 2.0 * N * K, 2.0 * rows * (double)N * K);
         if (wide) launch_gemm_wide(Ww, wscale, A, P, mtt, N, K, p, s, fused ? swiglu_out : nullptr, prof_scope_.stamps(),
-                                   fused ? ssq : nullptr, nblk, m.rms_eps);
+                                   fused ? ssq : nullptr, nblk, m.rms_eps, D.counts);
         else {
             GemmEpilogue epi; epi.swiglu_out = fused ? swiglu_out : nullptr;
             launch_gemm(W, A, P, mtt, N, K, p, s, epi, prof_scope_.stamps());
@@ -1074,7 +1074,7 @@ extern "C" int bb_debug_gemm_plan(int M, int N, int K, int wide, int fusable, in
     const GemmPlan p = wide ? gemm_plan_wide(M, N, K, 0, 0, fusable != 0) : gemm_plan(M, N, K, 0, 0);
     const int mt_total = (M + 31) / 32, n_groups = (N / 32 + 4 * p.nt - 1) / (4 * p.nt), m_groups = (mt_total + p.mt - 1) / p.mt;
     out[0] = p.split_k; out[1] = p.chunks_per_split; out[2] = p.nt; out[3] = p.mt;
-    out[4] = std::min(n_groups * m_groups, 256) * p.split_k;
+    out[4] = wide && mt_total > 8 ? std::min(n_groups * m_groups * p.split_k, 256) : std::min(n_groups * m_groups, 256) * p.split_k;
     return BB_OK;
 }
 

@@ -96,15 +96,16 @@ static inline __host__ __device__ size_t tileW_u4(int n, int k8, int ksteps) {
 // Weights: the tiled layout of the bf16 copy (tileW_u4) with fp16 values.  Activation panel:
 // [chunk = k / 64][m_tile][fragment 0..5][lane][16 bytes]:
 //   fragments 0..3: fp16, k-step ks = (k % 64) / 16, lane = row % 32 + 32 ((k / 8) % 2), element k % 8;
-//   fragments 4..5: e5m2, same lane, fragment 4 + ks / 2, byte 8 (ks % 2) + k % 8: a lane's 32 bytes are the
-//   remainders of exactly the 32 k whose fp16 weights it holds, in the order the kernel converts those.
+//   fragments 4..5: e5m2, same lane, fragment 4 + ks % 2, byte 8 (ks / 2) + k % 8.  A lane's 32 bytes (k-steps 0, 2, 1, 3)
+//   are the remainders of exactly the 32 k whose fp16 weights it holds in the 32-row kernels, and its 16 bytes of
+//   fragment 4 + q those of the k whose weights lane group (q, lane half) holds in the 16-row kernel.
 #define BB_WFRAGS 6
 #define BB_LO_SHIFT 8
 static inline __host__ __device__ size_t wideA_hi_u4(int m, int k8, int mt_total) {
     return ((((size_t)(k8 >> 3) * mt_total + (m >> 5)) * BB_WFRAGS + ((k8 & 7) >> 1)) * 64) + (m & 31) + ((k8 & 1) << 5);
 }
 static inline __host__ __device__ size_t wideA_lo_byte(int m, int k8, int mt_total) {      // byte offset of 8 fp8 values
-    return (((((size_t)(k8 >> 3) * mt_total + (m >> 5)) * BB_WFRAGS + 4 + ((k8 & 7) >> 2)) * 64) + (m & 31) + ((k8 & 1) << 5)) * 16 + (((k8 >> 1) & 1) << 3);
+    return (((((size_t)(k8 >> 3) * mt_total + (m >> 5)) * BB_WFRAGS + 4 + ((k8 >> 1) & 1)) * 64) + (m & 31) + ((k8 & 1) << 5)) * 16 + (((k8 >> 2) & 1) << 3);
 }
 
 // ---- KV cache layout ------------------------------------------------------------------------------
@@ -196,6 +197,19 @@ static __device__ __forceinline__ void zero_panel8(u32x4* Apk, int m, int k8, in
         *reinterpret_cast<uint2*>(reinterpret_cast<char*>(Apk) + wideA_lo_byte(m, k8, mt_total)) = make_uint2(0u, 0u);
     }
 }
+// Four fp16 weights (two dwords, already scaled by 2^S) -> four e4m3 values of w 2^(S - BB_LO_SHIFT): the hardware
+// conversion divides by its scale operand and rounds to nearest even; |w 2^S| < 2^15 keeps the result below e4m3's 448.
+// Each conversion writes one half of its destination and keeps the other, which the second one overwrites: `old` may be
+// anything, best what the destination register holds.
+static __device__ __forceinline__ int fp16x4_to_e4m3x4(unsigned int d0, unsigned int d1, int old) {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
+    const float sc = (float)(1 << BB_LO_SHIFT);
+    i16x2 a = __builtin_bit_cast(i16x2, old);
+    a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(a, __builtin_bit_cast(f16x2, d0), sc, false);
+    a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(a, __builtin_bit_cast(f16x2, d1), sc, true);
+    return __builtin_bit_cast(int, a);
+}
 #endif
 
 // ---- running (max, rescaled sum of exponentials, argmax) of a row of logits ------------------------------
@@ -232,7 +246,11 @@ void launch_pack_rows(const float* A, int M, int K, u32x4* Apk, int mt_total, hi
 // the SwiGLU epilogue applies 1 / sqrt(sum / K + rms_eps) to gate and up.
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out = nullptr, LaunchStamps st = LaunchStamps(),
-                      const float* ssq = nullptr, int nblk = 0, float rms_eps = 0.f);
+                      const float* ssq = nullptr, int nblk = 0, float rms_eps = 0.f, const int* rows_live = nullptr);
+// The same for passes with many rows: eight waves per workgroup, tile 32 plan.mt rows x 256 columns (plan.nt == 2, plan.mt 4 or
+// 6).  rows_live (device, may be null): row count of this pass; row groups past it are skipped.
+void launch_gemm_many(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
+                      hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st = LaunchStamps());
 void launch_tile_weights_wide(const uint16_t* src, int rows, int K, u32x4* dst, float* scale_out, int dst_row0, int interleave,
                               hipStream_t s);
 void launch_pack_rows_wide(const float* A, int M, int K, u32x4* Apk, int mt_total, hipStream_t s);

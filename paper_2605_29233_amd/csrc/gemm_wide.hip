@@ -55,14 +55,12 @@ static __device__ __forceinline__ i32x8 as_i32x8(const u32x4& a, const u32x4& b)
     r[4] = (int)b[0]; r[5] = (int)b[1]; r[6] = (int)b[2]; r[7] = (int)b[3];
     return r;
 }
-// Eight fp16 weights (already scaled by 2^S) -> eight e4m3 values of w 2^(S - BB_LO_SHIFT): the hardware conversion
-// divides by its scale operand and rounds to nearest even; |w 2^S| < 2^15 keeps the result below e4m3's 448.
-static __device__ __forceinline__ void to_e4m3x8(const u32x4& w, int& lo, int& hi) {
-    const float sc = (float)(1 << BB_LO_SHIFT);
+// Eight fp16 weights -> eight e4m3 values (fp16x4_to_e4m3x4 twice, starting from the sources themselves, which saves
+// clearing a register).
+static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo, int& hi) {
     // (the dwords are copied out first: a bit cast applied directly to a vector element picked element 0 every time)
     const unsigned int d0 = w[0], d1 = w[1], d2 = w[2], d3 = w[3];
-    // (each conversion writes one half of its destination and keeps the other: starting from the source itself
-    // saves clearing a register, the second conversion overwrites what is left of it)
+    const float sc = (float)(1 << BB_LO_SHIFT);
     i16x2 a = __builtin_bit_cast(i16x2, d0), b = __builtin_bit_cast(i16x2, d2);
     a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(a, __builtin_bit_cast(f16x2, d0), sc, false);
     a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(a, __builtin_bit_cast(f16x2, d1), sc, true);
@@ -175,13 +173,18 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
                 acc[t][mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w8[t], as_i32x8(b[mt][0], b[mt][1]),
                                                                             acc[t][mt], 0, 1, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
     };
-    // k-step j of a lane's fp16 weights becomes bytes 8 j .. 8 j + 7 of its fp8 operand (the panel's e5m2 fragments
-    // are laid out to match)
+    // k-steps 0, 2, 1, 3 of a lane's fp16 weights become the four 8-byte pieces of its fp8 operand (the order of the
+    // panel's e5m2 fragments)
     auto convert_w = [&](i32x8 (&w8)[NT], const u32x4 (&w)[KC][NT]) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int j = 0; j < KC; ++j) { int lo, hi; to_e4m3x8(w[j][t], lo, hi); w8[t][2 * j] = lo; w8[t][2 * j + 1] = hi; }
+            for (int j = 0; j < KC; ++j) {
+                int lo, hi;
+                fp16x8_to_e4m3x8(w[j][t], lo, hi);
+                const int o = 4 * (j & 1) + 2 * (j >> 1);
+                w8[t][o] = lo; w8[t][o + 1] = hi;
+            }
     };
 
     u32x4 w[DW][KC][NT], a[WA_PER_THREAD], bh[2][MT], bl[MT][2];
@@ -200,6 +203,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
 
     auto chunk = [&](auto U, int c) {
         constexpr int u = decltype(U)::value, st = u, st1 = (u + 1) % DW, slot2 = (u + 2) % DW;
+        __builtin_amdgcn_sched_barrier(0);  // (a conversion moved up from a later chunk would wait for that chunk's loads)
         // fp16 k-step 0
         read_bh(bh[1], st, 1);
 #pragma unroll
@@ -328,56 +332,52 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
 }
 
 // Plan of a wide-format GEMM.  Up to 256 rows the two-term kernel's plan (one or two groups of 128 rows, k split so
-// that one round of workgroups covers the chip).  With more rows the candidates (rows per workgroup 128 or 192, tile
-// width 128 / 256 / 384 columns, k split) are priced from measured launches: the time of one 64-k chunk of a
-// workgroup tile (table below: these launches are bound by what reaches the CUs, so a chunk of the 192 x 256 tile,
-// 68 KiB for 12 accumulator tiles, costs less per accumulator tile than one of the 128 x 256 tile, 56 KiB for 8), a
-// fixed prologue and store per tile, whole rounds of 256 workgroups, and the partial tiles, written here and read by
-// the consumer launch once per k split.  fusable: the caller can take SiLU(gate) * up from the epilogue when nt == 2
-// and k is not split; that candidate has no partial tiles at all.
+// that one round of workgroups covers the chip).  With more rows (gemm_many_kernel) the candidates (128 or 192 rows per
+// workgroup, k split) are priced by a model fitted to 800 measured launches (272..4206 rows, N 3584..37888, K
+// 3584..18944; 4.6 % rms): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
+// workgroups except that a last round which leaves CUs idle runs at a higher clock (the chip is at its power limit), and
+// the partial tiles, written here and read by the consumer launch once per k split.  Splits take whole units of 128 k.
+// Where both tiles price within 5 % the larger one is taken: it fetches a fifth less per product.  fusable: the caller
+// can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
     if (mt_total <= 8 || forced_split > 0) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
-    static const double chunk_us[2][3] = {{0.75, 1.17, 1.58}, {0.98, 1.654, 0.0}};       // [mt == 6][nt - 1]
-    const double partial_us = (double)mt_total * 32 * N * 4 * 0.433e-6;     // one copy: written at ~10 TB/s, read at ~3 TB/s
-    GemmPlan best = gemm_plan(m_rows, N, K, 0, forced_nt);
+    GemmPlan best;
+    best.nt = 2;
     double best_t = 1e30;
-    for (int mt = 4; mt <= 6; mt += 2)
-        for (int nt = 1; nt <= 3; ++nt) {
-            if (forced_nt > 0 && nt != forced_nt) continue;
-            if (nt * mt > 12 || (nt > 1 && n_tiles < 4 * nt)) continue;
-            const long base = (long)((n_tiles + 4 * nt - 1) / (4 * nt)) * ((mt_total + mt - 1) / mt);
-            for (int sp = 1; sp <= BB_MAX_SPLITK && sp <= std::max(1, total_chunks / 4); ++sp) {
-                const int cps = (total_chunks + sp - 1) / sp, sp_eff = (total_chunks + cps - 1) / cps;
-                const long rounds = (base * sp_eff + 255) / 256;
-                const bool fused = fusable && nt == 2 && sp_eff == 1;
-                const double t = rounds * (cps * chunk_us[mt == 6][nt - 1] + 6.0) + (fused ? 0.0 : sp_eff * partial_us + 5.0);
-                if (t < best_t) { best_t = t; best.split_k = sp_eff; best.chunks_per_split = cps; best.nt = nt; best.mt = mt; }
-            }
+    for (int mt = 4; mt <= 6; mt += 2) {
+        const double chunk_us = mt == 6 ? 1.67 : 1.18, tile_us = 3.8;
+        const long tiles = (long)((n_tiles + 7) / 8) * ((mt_total + mt - 1) / mt);
+        for (int sp = 1; sp <= BB_MAX_SPLITK && sp <= std::max(1, total_chunks / 4); ++sp) {
+            const int cps = sp == 1 ? total_chunks : ((total_chunks + sp - 1) / sp + 1) / 2 * 2, sp_eff = (total_chunks + cps - 1) / cps;
+            const long items = tiles * sp_eff;
+            const double last = (items % 256) / 256.0, rounds = items / 256 + (last > 0 ? 0.62 + 0.38 * last : 0.0);
+            double t = 2.0 + rounds * (cps * chunk_us + tile_us);
+            if (!(fusable && sp_eff == 1)) t += (fusable ? 8.0 : 0.0) + sp_eff * (double)mt_total * 32 * N * 4 * (0.066e-6 + 0.1e-6);
+            if (mt == 6) t *= 0.95;
+            if (t < best_t) { best_t = t; best.split_k = sp_eff; best.chunks_per_split = cps; best.mt = mt; }
         }
+    }
     return best;
 }
 
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
-                      GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps) {
+                      GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps,
+                      const int* rows_live) {
+    if (mt_total > 8) { launch_gemm_many(Wt, wscale, Apk, P, mt_total, N, K, plan, s, rows_live, swiglu_out, st); return; }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64, m_groups = (mt_total + plan.mt - 1) / plan.mt;
     const size_t split_stride = (size_t)mt_total * 32 * N;
     const int nt = plan.nt;
     const int tiles_x = (n_tiles + 4 * nt - 1) / (4 * nt);
     dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);
 #define WARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, tiles_x, m_groups, swiglu_out, ssq, nblk, 1.0f / (float)K, rms_eps
-#define WLAUNCH(NT_, EPI_, ST_, MT_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, MT_>), grid, dim3(256), 0, s, st.start, st.stop, 0, WARGS)
-    const bool stream = m_groups == 1;                  // (a single row group never takes the 192-row tile)
-    if (plan.mt == 6) {
-        if (swiglu_out) WLAUNCH(2, WEPI_SWIGLU, false, 6);
-        else if (nt == 2) WLAUNCH(2, WEPI_PARTIAL, false, 6);
-        else WLAUNCH(1, WEPI_PARTIAL, false, 6);
-    }
-    else if (swiglu_out) { if (stream) WLAUNCH(2, WEPI_SWIGLU, true, 4); else WLAUNCH(2, WEPI_SWIGLU, false, 4); }
-    else if (nt == 3) { if (stream) WLAUNCH(3, WEPI_PARTIAL, true, 4); else WLAUNCH(3, WEPI_PARTIAL, false, 4); }
-    else if (nt == 2) { if (stream) WLAUNCH(2, WEPI_PARTIAL, true, 4); else WLAUNCH(2, WEPI_PARTIAL, false, 4); }
-    else { if (stream) WLAUNCH(1, WEPI_PARTIAL, true, 4); else WLAUNCH(1, WEPI_PARTIAL, false, 4); }
+#define WLAUNCH(NT_, EPI_, ST_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, 4>), grid, dim3(256), 0, s, st.start, st.stop, 0, WARGS)
+    const bool stream = m_groups == 1;
+    if (swiglu_out) { if (stream) WLAUNCH(2, WEPI_SWIGLU, true); else WLAUNCH(2, WEPI_SWIGLU, false); }
+    else if (nt == 3) { if (stream) WLAUNCH(3, WEPI_PARTIAL, true); else WLAUNCH(3, WEPI_PARTIAL, false); }
+    else if (nt == 2) { if (stream) WLAUNCH(2, WEPI_PARTIAL, true); else WLAUNCH(2, WEPI_PARTIAL, false); }
+    else { if (stream) WLAUNCH(1, WEPI_PARTIAL, true); else WLAUNCH(1, WEPI_PARTIAL, false); }
 #undef WLAUNCH
 #undef WARGS
 }

@@ -75,6 +75,27 @@ def test_wide_format_gemm_matches_fp64(bb, M, N, K, split):
     assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
 
 
+@pytest.mark.parametrize("M,N,K,split", [
+    (257, 32, 64, 0),            # nine m-tiles, one column tile, a single chunk of 64 k: half a unit of the fp8 step
+    (289, 288, 192, 0),          # an odd number of chunks, column tiles that are no multiple of eight
+    (385, 96, 688, 3),           # splits of four chunks, the last one of three with a padded end
+    (520, 512, 1088, 3),         # splits of an odd number of chunks
+    (1030, 256, 128, 0),         # one unit; row groups past a multiple of both tile heights
+])
+def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split):
+    """The eight-wave kernel (more than 256 rows) where units, k splits, row and column groups end: against fp64, bound as
+    in test_wide_format_gemm_matches_fp64."""
+    rng = np.random.default_rng(M * 13 + K)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    Wb = gen_normal_bf16(2, f"m{N}x{K}", N * K, 0.05).view(torch.int16).numpy().view(np.uint16).reshape(N, K)
+    W = (Wb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    print(f"many-row gemm case M={M} N={N} K={K} split={split}", flush=True)
+    C = bb.debug_gemm(A, Wb, split, wide=True)
+    err = np.abs(C - A.astype(np.float64) @ W.T)
+    mag = np.abs(A).astype(np.float64) @ np.abs(W).T
+    assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
+
+
 @pytest.mark.parametrize("hq,hkv,hd,bias", [(4, 2, 64, True), (2, 1, 128, False), (6, 2, 64, True)])
 def test_qkv_projection_gives_the_same_cache_and_logits_under_every_plan(hq, hkv, hd, bias):
     """The q|k|v projection of the block forward with tiles of 128, 256 or 384 columns and with k whole or split in
