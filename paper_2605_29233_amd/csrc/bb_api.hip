@@ -531,7 +531,7 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
           launch_rmsnorm_pack(D, c->h, c->part, s_down, pstride, c->g_final, c->Apk, mt_lm, 1, mode == 1, 0, s); }
         {   // LM head with the vocabulary reduction in its epilogue: no k split, 256-column tiles (128 for tiny vocabularies)
             GemmPlan p = gemm_plan(lm_cap, m.vocab, d, 1, m.vocab / 32 >= 8 ? 2 : 1);
-            GemmEpilogue epi; epi.vocab_part = D.vr_part; epi.mask_id = m.mask_id; epi.keep_logits = c->keep_logits;
+            GemmEpilogue epi; epi.vocab_part = D.vr_part; epi.mask_id = m.mask_id; epi.keep_logits = c->keep_logits; epi.rows_live = D.counts + 1;
             PROF_STAMPED(lm_cap <= 256 ? BB_K_GEMM_SKINNY : BB_K_GEMM_WIDE, 2.0 * m.vocab * d, 2.0 * lm_cap * (double)m.vocab * d);
             launch_gemm(c->lm, c->Apk, c->logits, mt_lm, m.vocab, d, p, s, epi, prof_scope_.stamps());
         }

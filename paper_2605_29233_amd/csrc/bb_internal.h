@@ -231,8 +231,9 @@ GemmPlan gemm_plan(int m_rows, int N, int K, int forced_split, int forced_nt);
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable = false);     // wide-format kernel: may take mt = 6
 // Epilogue of launch_gemm: partial tiles P[split][m][n] (default); SiLU(gate) * up as the down projection's panel
 // (swiglu_out, needs nt == 2 and no k split); or the vocabulary reduction of the LM head (vocab_part: per row and
-// column tile one (max, sum, argmax); needs no k split and nt <= 2; P is then written only if keep_logits).
-struct GemmEpilogue { u32x4* swiglu_out = nullptr; float4* vocab_part = nullptr; int mask_id = -1; int keep_logits = 1; };
+// column tile one (max, sum, argmax); needs no k split and nt <= 2; P is then written only if keep_logits; rows_live: the
+// row count on the device, rows past it are not computed).
+struct GemmEpilogue { u32x4* swiglu_out = nullptr; float4* vocab_part = nullptr; int mask_id = -1; int keep_logits = 1; const int* rows_live = nullptr; };
 // Optional events that receive the begin and end time stamps of the launch's own dispatch packet (profiling): unlike
 // events recorded around a launch they add no packets to the stream and exclude the gap before the kernel.
 struct LaunchStamps { hipEvent_t start = nullptr; hipEvent_t stop = nullptr; };

@@ -10,6 +10,7 @@
 // is split over several workgroups to occupy every CU; each writes its partial tile and the
 // consumer kernel (residual + norm, SwiGLU, bias + RoPE + cache write) sums them in split order.
 #include "bb_internal.h"
+#include "sched.h"
 #include <hip/hip_ext.h>
 #include <type_traits>
 #include <algorithm>
@@ -18,20 +19,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define KC 4        // k-steps (of 16) per staged chunk
-#define MT 4        // m-tiles (of 32 rows) per workgroup
+#define MT_MAX 4    // m-tiles (of 32 rows) per workgroup
 #define DW 3        // weight chunks per wave in the register ring (two in flight ahead of the MFMAs)
-#define CHUNK_U4 (KC * MT * BB_SPLIT * 64)      // uint4 per staged activation chunk (2048 = 32 KiB)
-#define A_PER_THREAD (CHUNK_U4 / 256)
+#define CHUNK_U4(mt) (KC * (mt) * BB_SPLIT * 64)        // uint4 per staged activation chunk of mt m-tiles (four: 2048 = 32 KiB)
 
 static __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
     return *reinterpret_cast<const bf16x8*>(&v);
 }
-
-// sched_group_barrier masks
-#define SG_MFMA 0x008
-#define SG_VMEM 0x020
-#define SG_DSR 0x100
-#define SG_DSW 0x200
 
 // P[split][m][n] (fp32, leading dimension ldp) = this workgroup's share of the k range.
 //
@@ -58,38 +52,41 @@ static __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
 // exponentials, argmax) over the tile's columns (the mask token and padded columns excluded) and written to
 // Vp[row][column tile]; a second kernel merges the column tiles of a row in a fixed order.  The logits themselves
 // are stored only when keep_logits is set (tests).
-template <int NT, int EPI>
-__global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ Wt, const u32x4* __restrict__ Apk,
-                                                      float* __restrict__ P, size_t split_stride, int ldp, int mt_total,
-                                                      int n_tiles, int ksteps, int chunks_per_split, int tiles_x, int tiles_y,
-                                                      u32x4* __restrict__ Opk, float4* __restrict__ Vp, int mask_id,
-                                                      int keep_logits) {
+//
+// The LM head's row list is filled on the device (masked positions only), so the launch is sized for its upper bound and
+// the kernel reads the count: row groups past it are skipped, and the live m-tiles are dealt evenly to the groups, each
+// computed by the body for its own number of m-tiles (a group of one m-tile issues a quarter of the MFMAs and LDS reads of
+// a full one and is bound by the weight stream alone).  Row groups of a column group are neighbours in the item order
+// and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
+// Measured (vocabulary 126464, d 4096; before = every row of the bound, row groups of 128, running sums in the epilogue):
+// 1152 live of 1920 rows 3573 -> 1916 us, 144 of 240 480 -> 414 us, 19 of 32 rows 180 us = 5.7 TB/s; vocabulary 1024, d 256,
+// 34 of 56 rows: 24 -> 12 us, most of it the serial chain of exponentials that the epilogue no longer has.
+struct GemmArgs {
+    const u32x4* Wt; const u32x4* Apk; float* P;
+    size_t split_stride;
+    int ldp, mt_total, n_tiles, ksteps, chunks_per_split, tiles_x, tiles_y;
+    u32x4* Opk; float4* Vp;
+    int mask_id, keep_logits;
+    const int* rows_live;
+};
+
+// One workgroup tile: MT m-tiles from mt0 (mt_cnt of them valid) x column group bx, k range split_id.
+template <int NT, int EPI, int MT>
+static __device__ __forceinline__ void gemm_tile(const GemmArgs& g, u32x4* lds_raw, int bx, int mt0, int mt_cnt, int split_id) {
     constexpr bool SWIGLU = EPI == EPI_SWIGLU;
-    __shared__ u32x4 lds[3][CHUNK_U4];
+    constexpr int CH_U4 = CHUNK_U4(MT), A_PER_THREAD = CH_U4 / 256;
+    u32x4 (*lds)[CH_U4] = reinterpret_cast<u32x4 (*)[CH_U4]>(lds_raw);
+    const u32x4 *__restrict__ Wt = g.Wt, *__restrict__ Apk = g.Apk;
+    float* __restrict__ P = g.P;
+    u32x4* __restrict__ Opk = g.Opk;
+    float4* __restrict__ Vp = g.Vp;
+    const size_t split_stride = g.split_stride;
+    const int ldp = g.ldp, mt_total = g.mt_total, n_tiles = g.n_tiles, ksteps = g.ksteps, chunks_per_split = g.chunks_per_split;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // a workgroup walks the (column group, row group) tiles with the grid's stride: at most one round of
-    // workgroups is ever launched, the rest of the tiles are taken by the same workgroups
-    //
-    // Workgroups go to the 8 XCDs (each with its own L2) round robin by linear id.  With a k split the
-    // (column group, split) items are dealt out so that an XCD gets a contiguous run of them in split-major
-    // order: its workgroups then share one or two k ranges of the activation panel, which its L2 fetches
-    // once, instead of every XCD fetching the whole panel.
-    int first_tile = blockIdx.x, split_id = blockIdx.z;
-    if (gridDim.z > 1 && tiles_y == 1) {
-        const int n = gridDim.x * gridDim.z, lin = blockIdx.x + gridDim.x * blockIdx.z, e = lin & 7;
-        const int item = e * (n >> 3) + min(e, n & 7) + (lin >> 3);
-        first_tile = item % gridDim.x;
-        split_id = item / gridDim.x;
-    }
-    for (int tile = first_tile; tile < tiles_x * tiles_y; tile += gridDim.x) {
-    const int bx = tile % tiles_x, by = tile / tiles_x;
-    const int mt0 = by * MT;
-    const int mt_cnt = min(MT, mt_total - mt0);
     const int total_chunks = ksteps / KC;
     const int c0 = split_id * chunks_per_split;
     const int c1 = min(c0 + chunks_per_split, total_chunks);
-    if (c0 >= c1) continue;
-
+    if (c0 >= c1) return;
     // weight stream: one pointer per tile, advanced by a chunk (KC fragments of 64 lanes) at a time
     const u32x4* wbase[NT];
 #pragma unroll
@@ -165,43 +162,23 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ 
 #pragma unroll
         for (int i = 0; i < A_PER_THREAD; ++i) lds[st1][i * 256 + threadIdx.x] = a[i];
         mfmas(w[u][0], b[0]);
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, NT, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_DSR, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_DSW, 1, 0);
-        }
+        sched_groups<2 * MT, NT, 2 * MT, A_PER_THREAD, 0>();
         // k-step 1
         read_b(b[0], st, 2);
         load_a(a, c + 2);
         mfmas(w[u][1], b[1]);
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, NT, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_DSR, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_VMEM, 1, 0);
-        }
+        sched_groups<2 * MT, NT, 2 * MT, 0, A_PER_THREAD>();
         __syncthreads();                    // chunk c+1 is staged; stage (c+2) mod 3 is free again
         // k-step 2
         read_b(b[1], st, 3);
         load_w(w[slot2], c + 2, 0, KC / 2);
         mfmas(w[u][2], b[0]);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 2 * NT, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_DSR, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_VMEM, 1, 0);
-        }
+        sched_groups<MT, 2 * NT, 2 * MT, 0, 2 * NT>();
         // k-step 3 (reads the first fragments of the next chunk)
         read_b(b[0], st1, 0);
         load_w(w[slot2], c + 2, KC / 2, KC);
         mfmas(w[u][3], b[1]);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 2 * NT, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_DSR, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(SG_VMEM, 1, 0);
-        }
+        sched_groups<MT, 2 * NT, 2 * MT, 0, 2 * NT>();
     };
     // The steady-state loop has no branch inside a triple of chunks: with one the compiler sinks the
     // weight loads next to their uses in the later block and the prefetch distance is lost.
@@ -218,7 +195,7 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ 
         // Register r of lane (m = l%32, g = l/32) holds feature 8 (r/4) + 4 g + r%4 of the wave's 32.  The panel
         // wants the 8 features of group q in one lane of lane-half q%2: lane halves swap the 4-feature
         // pieces they do not own, then each lane stores the groups q = g and g + 2 (hi and lo terms).
-        const int x0 = (bx * 4 + wave) * NT, g = lane >> 5;
+        const int x0 = (bx * 4 + wave) * NT, gh = lane >> 5;
         __syncthreads();                                    // the next tile's prologue overwrites the staged activations
         if (x0 < n_tiles) {
 #pragma unroll
@@ -235,11 +212,11 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ 
                     float y[8];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float mine = act[4 * (2 * p2 + g) + i];            // group q = 2 p2 + g is mine
-                        const float send = act[4 * (2 * p2 + 1 - g) + i];        // the other lane half owns that group
+                        const float mine = act[4 * (2 * p2 + gh) + i];            // group q = 2 p2 + gh is mine
+                        const float send = act[4 * (2 * p2 + 1 - gh) + i];        // the other lane half owns that group
                         const float recv = __shfl_xor(send, 32, 64);
-                        y[i] = g == 0 ? mine : recv;
-                        y[4 + i] = g == 0 ? recv : mine;
+                        y[i] = gh == 0 ? mine : recv;
+                        y[4 + i] = gh == 0 ? recv : mine;
                     }
                     uint16_t hi[8], lo[8];
 #pragma unroll
@@ -247,35 +224,42 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ 
                         hi[e] = f32_to_bf16_rne(y[e]);
                         lo[e] = f32_to_bf16_rne(y[e] - bf16_to_f32(hi[e]));
                     }
-                    const int m = (mt0 + mt) * 32 + (lane & 31), k8 = (x0 / 2) * 4 + 2 * p2 + g;
+                    const int m = (mt0 + mt) * 32 + (lane & 31), k8 = (x0 / 2) * 4 + 2 * p2 + gh;
                     Opk[packA_u4(m, k8, mt_total, 0)] = *reinterpret_cast<u32x4*>(hi);
                     Opk[packA_u4(m, k8, mt_total, 1)] = *reinterpret_cast<u32x4*>(lo);
                 }
             }
         }
-        continue;
+        return;
     }
     if constexpr (EPI == EPI_VOCAB) {
         static_assert(EPI != EPI_VOCAB || NT <= 2, "vocabulary epilogue is written for one or two tiles per wave");
         // Lane l holds, for activation row l % 32 of every m-tile, 16 columns of each of its weight tiles, in
         // ascending column order (register r <-> column 8 (r/4) + 4 (l/32) + r%4): a strict '>' keeps the lowest id.
-        __shared__ MSI sV[4][MT * 32];
+        __shared__ MSI sV[4][MT_MAX * 32];
+        const int mask_id = g.mask_id;
         const int x0v = (bx * 4 + wave) * NT, gv = lane >> 5;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
+            // maximum and its column first, then the exponentials: 32 independent ones, where a running (max, sum) pair
+            // makes every value wait for the one before it
             MSI a = {-INFINITY, 0.f, 0x7fffffff};
+            float x[NT][16];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                if (x0v + t >= n_tiles) break;
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int v = (x0v + t) * 32 + 8 * (r >> 2) + 4 * gv + (r & 3);
-                    const float x = acc[t][mt][r];
-                    if (v == mask_id) continue;
-                    if (x > a.m) { a.s = a.s * expf(a.m - x) + 1.f; a.m = x; a.i = v; }
-                    else a.s += expf(x - a.m);
+                    x[t][r] = x0v + t < n_tiles && v != mask_id ? acc[t][mt][r] : -INFINITY;
+                    if (x[t][r] > a.m) { a.m = x[t][r]; a.i = v; }
                 }
-            }
+            const float top = a.m == -INFINITY ? 0.f : a.m;
+            float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) part[r & 3] += expf(x[t][r] - top);
+            a.s = (part[0] + part[1]) + (part[2] + part[3]);
             const MSI b = {__shfl_xor(a.m, 32, 64), __shfl_xor(a.s, 32, 64), __shfl_xor(a.i, 32, 64)};
             a = gv == 0 ? msi_merge(a, b) : msi_merge(b, a);       // both halves compute the same merge
             if (gv == 0) sV[wave][mt * 32 + (lane & 31)] = a;
@@ -285,19 +269,19 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ 
             MSI t4 = sV[0][threadIdx.x];
 #pragma unroll
             for (int w = 1; w < 4; ++w) t4 = msi_merge(t4, sV[w][threadIdx.x]);
-            Vp[(size_t)(mt0 * 32 + threadIdx.x) * tiles_x + bx] = make_float4(t4.m, t4.s, __int_as_float(t4.i), 0.f);
+            Vp[(size_t)(mt0 * 32 + threadIdx.x) * g.tiles_x + bx] = make_float4(t4.m, t4.s, __int_as_float(t4.i), 0.f);
         }
-        if (!keep_logits) { __syncthreads(); continue; }
+        if (!g.keep_logits) { __syncthreads(); return; }
     }
     // C^T accumulator layout of the 32x32 MFMA: register r of lane l holds
     //   weight row n = 8*(r/4) + 4*(l/32) + r%4 of the tile, activation row m = l%32.
     // The tile goes through LDS (each wave its own slice, one or two m-tiles at a time) so that the global
     // stores are whole 128-byte lines of a row instead of 16-byte pieces of 32 different rows.
     constexpr int COLS = 32 * NT, LDT = COLS + 4;          // row stride in floats (16-byte aligned, conflict-free)
-    constexpr int MPP = NT <= 2 ? 2 : 1;                   // m-tiles per pass: four slices of 32 MPP rows must fit the 96 KiB
-    static_assert(4 * 32 * MPP * LDT * 4 <= (int)sizeof(lds), "store slices exceed the staging buffers");
+    constexpr int MPP = NT <= 2 && MT % 2 == 0 ? 2 : 1;    // m-tiles per pass: four slices of 32 MPP rows must fit the 96 KiB
+    static_assert(4 * 32 * MPP * LDT * 4 <= (3 * CHUNK_U4(MT_MAX) * 16), "store slices exceed the staging buffers");
     __syncthreads();                                        // all waves are done with the staged activations
-    float* tl = reinterpret_cast<float*>(&lds[0][0]) + wave * (32 * MPP * LDT);
+    float* tl = reinterpret_cast<float*>(lds_raw) + wave * (32 * MPP * LDT);
     float* Ps = P + (size_t)split_id * split_stride;
     const int x0 = (bx * 4 + wave) * NT;                    // first weight tile of this wave
 #pragma unroll
@@ -325,13 +309,52 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(const u32x4* __restrict__ 
         }
     }
     __syncthreads();                                        // the next tile's prologue overwrites the LDS slices
+}
+
+template <int NT, int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_kernel(GemmArgs g) {
+    __shared__ u32x4 lds[3 * CHUNK_U4(MT_MAX)];
+    // a workgroup walks the (column group, row group) tiles with the grid's stride: at most one round of
+    // workgroups is ever launched, the rest of the tiles are taken by the same workgroups
+    if constexpr (EPI == EPI_VOCAB) {       // (k is not split)
+        const int live_mt = min(g.mt_total, (*g.rows_live + 31) >> 5), groups = (live_mt + MT_MAX - 1) / MT_MAX;
+        const int per = live_mt / max(groups, 1), more = live_mt % max(groups, 1);         // the first `more` groups take one m-tile more
+        const int items = g.tiles_x * groups;
+        for (int base = 0; base < items; base += gridDim.x) {
+            const int n = min((int)gridDim.x, items - base), lin = blockIdx.x;
+            if (lin >= n) break;
+            const int e = lin & 7, item = base + e * (n >> 3) + min(e, n & 7) + (lin >> 3);
+            const int bx = item / groups, by = item % groups, mt0 = by * per + min(by, more), cnt = per + (by < more);
+            switch (cnt) {
+                case 1: gemm_tile<NT, EPI, 1>(g, lds, bx, mt0, 1, 0); break;
+                case 2: gemm_tile<NT, EPI, 2>(g, lds, bx, mt0, 2, 0); break;
+                case 3: gemm_tile<NT, EPI, 3>(g, lds, bx, mt0, 3, 0); break;
+                default: gemm_tile<NT, EPI, 4>(g, lds, bx, mt0, 4, 0);
+            }
+        }
+        return;
+    }
+    // Workgroups go to the 8 XCDs (each with its own L2) round robin by linear id.  With a k split the
+    // (column group, split) items are dealt out so that an XCD gets a contiguous run of them in split-major
+    // order: its workgroups then share one or two k ranges of the activation panel, which its L2 fetches
+    // once, instead of every XCD fetching the whole panel.
+    int first_tile = blockIdx.x, split_id = blockIdx.z;
+    if (gridDim.z > 1 && g.tiles_y == 1) {
+        const int n = gridDim.x * gridDim.z, lin = blockIdx.x + gridDim.x * blockIdx.z, e = lin & 7;
+        const int item = e * (n >> 3) + min(e, n & 7) + (lin >> 3);
+        first_tile = item % gridDim.x;
+        split_id = item / gridDim.x;
+    }
+    for (int tile = first_tile; tile < g.tiles_x * g.tiles_y; tile += gridDim.x) {
+        const int mt0 = tile / g.tiles_x * MT_MAX;
+        gemm_tile<NT, EPI, MT_MAX>(g, lds, tile % g.tiles_x, mt0, min(MT_MAX, g.mt_total - mt0), split_id);
     }
 }
 
 // nt: weight tiles of 32 rows per wave (workgroup tile = 128 * nt columns); forced values <= 0 = choose.
 GemmPlan gemm_plan(int m_rows, int N, int K, int forced_split, int forced_nt) {
     const int n_tiles = N / 32, mt_total = (m_rows + 31) / 32, ksteps = (K + 63) / 64 * 4;
-    const int m_groups = (mt_total + MT - 1) / MT, total_chunks = ksteps / KC;
+    const int m_groups = (mt_total + MT_MAX - 1) / MT_MAX, total_chunks = ksteps / KC;
     GemmPlan p;
     p.nt = forced_nt > 0 ? forced_nt : (n_tiles >= 8 ? 2 : 1);
     if (forced_nt <= 0 && m_groups == 1 && N <= 8192) p.nt = 1;     // few columns: narrower tiles, fewer splits
@@ -367,24 +390,23 @@ GemmPlan gemm_plan(int m_rows, int N, int K, int forced_split, int forced_nt) {
 
 void launch_gemm(const u32x4* Wt, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan, hipStream_t s,
                  GemmEpilogue epi, LaunchStamps st) {
-    const int n_tiles = N / 32, ksteps = (K + 63) / 64 * 4, m_groups = (mt_total + MT - 1) / MT;     // K padded to whole chunks
+    const int n_tiles = N / 32, ksteps = (K + 63) / 64 * 4, m_groups = (mt_total + MT_MAX - 1) / MT_MAX;     // K padded to whole chunks
     const size_t split_stride = (size_t)mt_total * 32 * N;
     const int tiles_x = (n_tiles + 4 * plan.nt - 1) / (4 * plan.nt);
     dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);
-#define GEMM_ARGS Wt, Apk, P, split_stride, N, mt_total, n_tiles, ksteps, plan.chunks_per_split, tiles_x, m_groups, epi.swiglu_out, epi.vocab_part, epi.mask_id, epi.keep_logits
+    const GemmArgs g = {Wt, Apk, P, split_stride, N, mt_total, n_tiles, ksteps, plan.chunks_per_split, tiles_x, m_groups, epi.swiglu_out, epi.vocab_part, epi.mask_id, epi.keep_logits, epi.rows_live};
     if (epi.swiglu_out)
-        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_SWIGLU>), grid, dim3(256), 0, s, st.start, st.stop, 0, GEMM_ARGS);
+        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_SWIGLU>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);
     else if (epi.vocab_part && plan.nt == 2)
-        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_VOCAB>), grid, dim3(256), 0, s, st.start, st.stop, 0, GEMM_ARGS);
+        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_VOCAB>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);
     else if (epi.vocab_part)
-        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<1, EPI_VOCAB>), grid, dim3(256), 0, s, st.start, st.stop, 0, GEMM_ARGS);
+        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<1, EPI_VOCAB>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);
     else if (plan.nt == 3)
-        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<3, EPI_PARTIAL>), grid, dim3(256), 0, s, st.start, st.stop, 0, GEMM_ARGS);
+        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<3, EPI_PARTIAL>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);
     else if (plan.nt == 2)
-        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_PARTIAL>), grid, dim3(256), 0, s, st.start, st.stop, 0, GEMM_ARGS);
+        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_PARTIAL>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);
     else
-        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<1, EPI_PARTIAL>), grid, dim3(256), 0, s, st.start, st.stop, 0, GEMM_ARGS);
-#undef GEMM_ARGS
+        hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<1, EPI_PARTIAL>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);
 }
 
 // The destination is laid out for K padded to a multiple of 64 (whole chunks); the padding must be zero.

@@ -10,6 +10,7 @@
 // weights stream L2 -> registers in a ring of three chunks.  A workgroup walks its (column group, row group) tiles
 // with the grid's stride.
 #include "bb_internal.h"
+#include "sched.h"
 #include <hip/hip_ext.h>
 #include <type_traits>
 #include <algorithm>
@@ -22,28 +23,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define KC 4                                    // fp16 k-steps (of 16) per chunk = weight fragments per (tile, chunk)
 #define DW 3                                    // weight chunks per wave in the register ring
-
-#define SG_MFMA 0x008
-#define SG_VMEM 0x020
-#define SG_DSR 0x100
-#define SG_DSW 0x200
-// One scheduling group per m-tile of a phase: NT MFMAs, then this group's share of the phase's LDS reads, LDS writes
-// and global loads (dealt out as evenly as possible, larger shares first).  The builtin wants constants, hence
-// templates.
-template <int MASK, int N> static __device__ __forceinline__ void sgb() {
-    if constexpr (N > 0) __builtin_amdgcn_sched_group_barrier(MASK, N, 0);
-}
-template <int GROUPS, int TOTAL, int I> constexpr int sg_share() { return TOTAL / GROUPS + (I < TOTAL % GROUPS ? 1 : 0); }
-template <int GROUPS, int NT, int DSR_TOTAL, int DSW_TOTAL, int VMEM_TOTAL, int I = 0>
-static __device__ __forceinline__ void sched_groups() {
-    if constexpr (I < GROUPS) {
-        sgb<SG_MFMA, NT>();
-        sgb<SG_DSR, sg_share<GROUPS, DSR_TOTAL, I>()>();
-        sgb<SG_DSW, sg_share<GROUPS, DSW_TOTAL, I>()>();
-        sgb<SG_VMEM, sg_share<GROUPS, VMEM_TOTAL, I>()>();
-        sched_groups<GROUPS, NT, DSR_TOTAL, DSW_TOTAL, VMEM_TOTAL, I + 1>();
-    }
-}
 
 #define WEPI_PARTIAL 0
 #define WEPI_SWIGLU 1

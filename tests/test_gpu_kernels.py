@@ -228,3 +228,38 @@ def test_swiglu_in_the_gemm_epilogue_with_the_deferred_norm_scale():
     for (K, V), (Kr, Vr) in zip(res[True][1], res[False][1]):
         assert np.abs(K - Kr).max() <= 1e-3 * max(1.0, np.abs(Kr).max())
         assert np.abs(V - Vr).max() <= 1e-3 * max(1.0, np.abs(Vr).max())
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 97, 129, 161, 225, 257])
+def test_lm_head_row_groups(n):
+    """n rows receive logits: 1, 2, 3 or 4 m-tiles in one row group, then two and three groups with the m-tiles dealt evenly
+    (129 rows = 3 + 2, 225 = 4 + 4, 257 = 3 + 3 + 3).  The launch is sized for 257.  Logits against the oracle (fp64);
+    token, confidence and log-sum-exp against a reduction of the returned logits in fp64: 1 / c and exp(lse - max) are
+    sums of up to 1024 exponentials in fp32, each good to 2 ulp of an argument below 2^7."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    from oracle.model import OracleModel
+    from oracle.blockbatch import OracleRequest
+    shape = ModelShape("lmtest", 1, 256, 4, 4, 64, 688, 1024)
+    decode = DecodeParams(0.9, 0.5, 4, 8)
+    weights = dict(gen_weights(shape, 11))
+    prompt = gen_prompt(shape, 11, 0, 20)
+    print("lm head rows", n, flush=True)
+    b = BlockBatch(shape, decode, Limits(1, 1, 20 + 257, 257, 64), poison_workspace=True)
+    try:
+        b.load_weights(weights.items())
+        b.keep_logits(True)
+        rid = b.request_open(prompt, n, (32,))
+        b.refresh([rid], BB_INIT)
+        v = b.latest_view()
+        assert v.m_lm == n
+        logits, am, conf, lse = v.logits().astype(np.float64), v.argmax(), v.conf(), v.lse()
+    finally:
+        b.close()
+    want = OracleRequest(OracleModel(shape, weights), prompt, n, (32,), decode).init_forward().logits
+    assert np.abs(logits[:, :-1] - want[:, :-1]).max() <= 3e-2
+    x = logits[:, :-1]                      # (the last column is the mask token)
+    assert np.array_equal(am, x.argmax(1))
+    ref = x.max(1) + np.log(np.exp(x - x.max(1, keepdims=True)).sum(1))
+    assert np.abs(lse - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+    assert np.abs(conf * np.exp(ref - x.max(1)) - 1).max() <= 2e-5
