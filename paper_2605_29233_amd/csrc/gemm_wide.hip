@@ -1,14 +1,20 @@
-// MFMA GEMM for passes with many activation rows (full-sequence refresh, initial forward, many requests):
+// Wide-format MFMA GEMM for passes of up to 256 rows (block steps; gemm_many.hip takes the others):
 //     C[m][n] = sum_k A[m][k] * W[n][k]          (fp32 accumulate)
 // with the operands in the wide format of bb_internal.h: the activation as fp16 + a scaled e5m2 remainder, the
 // weight as row-scaled fp16, converted in registers to e4m3 for the remainder's product.  Per 64 k and 32x32 tile
-// that is four 32x32x16 fp16 MFMAs and one 32x32x64 fp8 MFMA, three quarters of the matrix work of two bf16 terms,
-// and 56 KiB instead of 64 KiB fetched per workgroup and chunk (these passes are bound by what the L2 delivers to a
-// CU at least as much as by the matrix pipes), at an accuracy of about 2^-16 per product.  Structure as the two-term
+// that is four 32x32x16 fp16 MFMAs and one 32x32x64 fp8 MFMA, three quarters of the matrix work of two bf16 terms, at an
+// accuracy of about 2^-16 per product.  Structure as the two-term
 // kernel: C^T tiles with the weight fragment as the MFMA A-operand, one workgroup per CU, four waves that own
-// 32 * NT weight rows each and share the activation chunk (128 rows x 64 k = 24 KiB) through three LDS stages;
-// weights stream L2 -> registers in a ring of three chunks.  A workgroup walks its (column group, row group) tiles
+// 32 * NT weight rows each and share the activation chunk (32 MT rows x 64 k = 6 MT KiB) through LDS stages;
+// weights stream L2 -> registers in a ring.  A workgroup walks its (column group, row group) tiles
 // with the grid's stride.
+//
+// What bounds it: the weight stream, through the loads a CU can have in flight.  Some 64 KB per CU whatever the ring's
+// depth, so 45-60 GB/s per CU at the latency of a loaded HBM, of which a 256-column tile of 128 rows spends 24 of every
+// 56 KB on activations; with few rows also the issue of MFMAs and LDS reads.  Hence a body per number of m-tiles: rows
+// that are not there are neither fetched nor multiplied.  Measured, us per launch, body of 4 -> of 1 m-tile at
+// 32 rows: 12288 x 4096 26.7 -> 19.9, 24576 x 4096 45.0 -> 33.8, 4096 x 12288 27.6 -> 18.7 (5.4 TB/s; reading the weights
+// alone takes 17.6); of 2 at 56 rows: 27.5 -> 22.0, 45.5 -> 39.4, 27.6 -> 20.7; of 3 at 96 rows: 29.2 -> 24.0, 43.4 -> 41.6.
 #include "bb_internal.h"
 #include "sched.h"
 #include <hip/hip_ext.h>
@@ -22,7 +28,6 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define KC 4                                    // fp16 k-steps (of 16) per chunk = weight fragments per (tile, chunk)
-#define DW 3                                    // weight chunks per wave in the register ring
 
 #define WEPI_PARTIAL 0
 #define WEPI_SWIGLU 1
@@ -53,11 +58,16 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 // same features; NT == 2, k not split): writes SiLU(gate) * up as the wide-format panel Opk of the down projection.
 //
 // Chunk pipeline (one wave per SIMD, nothing else hides a stall), five phases per 64 k:
-//   fp16 k-step 0: MFMAs | LDS reads of step 1 | LDS writes of chunk c+1's activations (loaded during c-1)
-//   fp16 k-step 1: MFMAs | LDS reads of step 2 | global loads of chunk c+2's activations          -> barrier
-//   fp16 k-step 2: MFMAs | LDS reads of step 3 | global loads of chunk c+2's weight fragments 0, 1
+//   fp16 k-step 0: MFMAs | LDS reads of step 1 | LDS writes of chunk c+1's activations (loaded during c-AD)
+//   fp16 k-step 1: MFMAs | LDS reads of step 2 | global loads of chunk c+1+AD's activations       -> barrier
+//   fp16 k-step 2: MFMAs | LDS reads of step 3 | global loads of chunk c+DW-1's weight fragments 0, 1
 //   fp16 k-step 3: MFMAs | LDS reads of the fp8 fragments | weight fragments 2, 3 | this chunk's weights -> e4m3
 //   fp8 step:      MFMAs | LDS reads of step 0 of chunk c+1
+// With few accumulator tiles the registers hold a ring of four weight chunks, and activations that are requested two
+// chunks ahead instead of one (64-row body, 37888 x 3584: 62.5 -> 57.4 us; with more tiles the deeper ring gains nothing).
+template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
+    if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
+}
 template <int NT, int EPI, bool STREAM, int MT>
 __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restrict__ Wt, const float* __restrict__ wscale,
                                                            const u32x4* __restrict__ Apk, float* __restrict__ P,
@@ -67,9 +77,14 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
                                                            float inv_d, float eps) {
     static_assert(NT >= 1 && NT <= 3 && NT * MT <= 12, "one to three weight tiles per wave, at most 12 accumulator tiles");
     constexpr int WCHUNK_U4 = MT * BB_WFRAGS * 64;          // uint4 per staged activation chunk (6 KiB per m-tile)
-    constexpr int WA_PER_THREAD = WCHUNK_U4 / 256;
-    static_assert(WCHUNK_U4 % 256 == 0, "every thread stages the same number of pieces");
-    __shared__ u32x4 lds[DW][WCHUNK_U4];
+    constexpr int WA_PER_THREAD = (WCHUNK_U4 + 255) / 256;  // (an odd MT: the last half piece repeats valid data past the chunk's end)
+    constexpr bool DEEP = NT * MT <= 4 && MT < 4;
+    constexpr int DW = DEEP ? 4 : 3, AD = DEEP ? 2 : 1;     // chunks in the weight ring and LDS; activation chunks in registers
+    constexpr int COLS = 32 * NT, LDT = COLS + 4;           // store slices: row stride in floats (16-byte aligned, conflict-free)
+    constexpr int MPP = NT <= 2 && MT % 2 == 0 ? 2 : 1;     // m-tiles per store pass
+    constexpr int STAGES_U4 = DW * WA_PER_THREAD * 256, SLICES_U4 = 4 * 32 * MPP * LDT / 4;
+    __shared__ u32x4 lds_raw[STAGES_U4 > SLICES_U4 ? STAGES_U4 : SLICES_U4];
+    u32x4 (*lds)[WA_PER_THREAD * 256] = reinterpret_cast<u32x4 (*)[WA_PER_THREAD * 256]>(lds_raw);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // STREAM (one row group: every weight line is used once): weight loads carry the non-temporal hint, and with a k
     // split the (column group, split) items are dealt to the 8 XCDs in contiguous runs in split-major order, so that an
@@ -166,43 +181,42 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
             }
     };
 
-    u32x4 w[DW][KC][NT], a[WA_PER_THREAD], bh[2][MT], bl[MT][2];
+    u32x4 w[DW][KC][NT], a[AD][WA_PER_THREAD], bh[2][MT], bl[MT][2];
     i32x8 w8[NT];
-    // prologue: chunk c0 staged, chunk c0+1 in registers, weights of c0 and c0+1 in flight; loads in the order the
-    // loop issues them (activations of a chunk, then its weights), so that the wait counts at the loop head, the more
-    // cautious of the two ways in, are those of the steady state
-    load_a(a, c0);
-    load_w(w[0], c0, 0, KC);
+    // prologue: chunk c0 staged, AD chunks of activations in registers, weights of DW - 1 chunks in flight; loads in the
+    // order the loop issues them (activations of a chunk, then its weights), so that the wait counts at the loop head, the
+    // more cautious of the two ways in, are those of the steady state
+    unroll<AD>([&](auto I) { load_a(a[I], c0 + I); load_w(w[I], c0 + I, 0, KC); });
 #pragma unroll
-    for (int i = 0; i < WA_PER_THREAD; ++i) lds[0][i * 256 + threadIdx.x] = a[i];
-    load_a(a, c0 + 1);
-    load_w(w[1], c0 + 1, 0, KC);
+    for (int i = 0; i < WA_PER_THREAD; ++i) lds[0][i * 256 + threadIdx.x] = a[0][i];
+    load_a(a[0], c0 + AD);
+    unroll<DW - 1 - AD>([&](auto I) { load_w(w[AD + I], c0 + AD + I, 0, KC); });
     __syncthreads();
     read_bh(bh[0], 0, 0);
 
     auto chunk = [&](auto U, int c) {
-        constexpr int u = decltype(U)::value, st = u, st1 = (u + 1) % DW, slot2 = (u + 2) % DW;
+        constexpr int u = decltype(U)::value, st = u, st1 = (u + 1) % DW, slot2 = (u + DW - 1) % DW, as = (u + 1) % AD;
         __builtin_amdgcn_sched_barrier(0);  // (a conversion moved up from a later chunk would wait for that chunk's loads)
         // fp16 k-step 0
         read_bh(bh[1], st, 1);
 #pragma unroll
-        for (int i = 0; i < WA_PER_THREAD; ++i) lds[st1][i * 256 + threadIdx.x] = a[i];
+        for (int i = 0; i < WA_PER_THREAD; ++i) lds[st1][i * 256 + threadIdx.x] = a[as][i];
         mfma_hi(w[u][0], bh[0]);
         sched_groups<MT, NT, MT, WA_PER_THREAD, 0>();
         // fp16 k-step 1
         read_bh(bh[0], st, 2);
-        load_a(a, c + 2);
+        load_a(a[as], c + 1 + AD);
         mfma_hi(w[u][1], bh[1]);
         sched_groups<MT, NT, MT, 0, WA_PER_THREAD>();
-        __syncthreads();                    // chunk c+1 is staged; stage (c+2) mod 3 is free again
+        __syncthreads();                    // chunk c+1 is staged; the stage of chunk c-1 is free again
         // fp16 k-step 2
         read_bh(bh[1], st, 3);
-        load_w(w[slot2], c + 2, 0, 2);
+        load_w(w[slot2], c + DW - 1, 0, 2);
         mfma_hi(w[u][2], bh[0]);
         sched_groups<MT, NT, MT, 0, 2 * NT>();
         // fp16 k-step 3 (and the conversion of this chunk's weights for the fp8 step)
         read_bl(bl, st);
-        load_w(w[slot2], c + 2, 2, 4);
+        load_w(w[slot2], c + DW - 1, 2, 4);
         convert_w(w8, w[u]);
         mfma_hi(w[u][3], bh[1]);
         sched_groups<MT, NT, 2 * MT, 0, 2 * NT>();
@@ -212,13 +226,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
         sched_groups<MT, NT, MT, 0, 0>();
     };
     int c = c0;
-    for (; c + DW <= c1; c += DW) {
-        chunk(std::integral_constant<int, 0>{}, c);
-        chunk(std::integral_constant<int, 1>{}, c + 1);
-        chunk(std::integral_constant<int, 2>{}, c + 2);
-    }
-    if (c < c1) chunk(std::integral_constant<int, 0>{}, c);
-    if (c + 1 < c1) chunk(std::integral_constant<int, 1>{}, c + 1);
+    for (; c + DW <= c1; c += DW) unroll<DW>([&](auto U) { chunk(U, c + U); });
+    unroll<DW - 1>([&](auto U) { if (c + U < c1) chunk(U, c + U); });
 
     // undo the per-row weight scale: register r of lane (m = l % 32, g = l / 32) holds weight row 8 (r/4) + 4 g + r%4
     const int x0 = (bx * 4 + wave) * NT, g = lane >> 5;
@@ -277,10 +286,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
         continue;
     }
     // Partial tiles go out through LDS so that a wave stores whole 128-byte lines.
-    constexpr int COLS = 32 * NT, LDT = COLS + 4;          // row stride in floats (16-byte aligned, conflict-free)
-    constexpr int MPP = NT <= 2 ? 2 : 1;                   // m-tiles per pass: four slices of 32 MPP rows must fit the staging buffers
-    static_assert(4 * 32 * MPP * LDT * 4 <= (int)sizeof(lds), "store slices exceed the staging buffers");
-    float* tl = reinterpret_cast<float*>(&lds[0][0]) + wave * (32 * MPP * LDT);
+    float* tl = reinterpret_cast<float*>(lds_raw) + wave * (32 * MPP * LDT);
     float* Ps = P + (size_t)split_id * split_stride;
 #pragma unroll
     for (int pass = 0; pass < MT / MPP; ++pass) {
@@ -311,7 +317,10 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
 }
 
 // Plan of a wide-format GEMM.  Up to 256 rows the two-term kernel's plan (one or two groups of 128 rows, k split so
-// that one round of workgroups covers the chip).  With more rows (gemm_many_kernel) the candidates (128 or 192 rows per
+// that one round of workgroups covers the chip), except that up to 64 rows the tiles are 128 columns wide wherever one
+// round holds them: activations are then little of what a CU fetches, and half as many k splits are written and read back
+// (12288 x 4096 at 32 rows, two splits against five: 19.9 against 21.4 us and a shorter consumer; 24576 x 4096 33.8, unsplit,
+// against 35.9; at 96 rows 25.5 and 46.0 against 24.0 and 41.6).  With more rows (gemm_many_kernel) the candidates (128 or 192 rows per
 // workgroup, k split) are priced by a model fitted to 800 measured launches (272..4206 rows, N 3584..37888, K
 // 3584..18944; 4.6 % rms): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
 // workgroups except that a last round which leaves CUs idle runs at a higher clock (the chip is at its power limit), and
@@ -320,6 +329,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
 // can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
+    if (mt_total <= 2 && forced_nt <= 0 && (N / 32 + 3) / 4 <= 256) forced_nt = 1;
     if (mt_total <= 8 || forced_split > 0) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
@@ -345,18 +355,26 @@ void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, fl
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps,
                       const int* rows_live) {
     if (mt_total > 8) { launch_gemm_many(Wt, wscale, Apk, P, mt_total, N, K, plan, s, rows_live, swiglu_out, st); return; }
-    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, m_groups = (mt_total + plan.mt - 1) / plan.mt;
+    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, nt = plan.nt;
+    // row groups of at most four m-tiles, dealt evenly, each computed by the body for that number
+    const int m_groups = (mt_total + 3) / 4, mt = nt == 3 ? 4 : (mt_total + m_groups - 1) / m_groups;
     const size_t split_stride = (size_t)mt_total * 32 * N;
-    const int nt = plan.nt;
     const int tiles_x = (n_tiles + 4 * nt - 1) / (4 * nt);
     dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);
 #define WARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, tiles_x, m_groups, swiglu_out, ssq, nblk, 1.0f / (float)K, rms_eps
-#define WLAUNCH(NT_, EPI_, ST_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, 4>), grid, dim3(256), 0, s, st.start, st.stop, 0, WARGS)
-    const bool stream = m_groups == 1;
-    if (swiglu_out) { if (stream) WLAUNCH(2, WEPI_SWIGLU, true); else WLAUNCH(2, WEPI_SWIGLU, false); }
-    else if (nt == 3) { if (stream) WLAUNCH(3, WEPI_PARTIAL, true); else WLAUNCH(3, WEPI_PARTIAL, false); }
-    else if (nt == 2) { if (stream) WLAUNCH(2, WEPI_PARTIAL, true); else WLAUNCH(2, WEPI_PARTIAL, false); }
-    else { if (stream) WLAUNCH(1, WEPI_PARTIAL, true); else WLAUNCH(1, WEPI_PARTIAL, false); }
+#define WLAUNCH(NT_, EPI_, ST_, MT_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, MT_>), grid, dim3(256), 0, s, st.start, st.stop, 0, WARGS)
+#define WLAUNCH_MT(NT_, EPI_) do { \
+        if (m_groups > 1) { if (mt == 3) WLAUNCH(NT_, EPI_, false, 3); else WLAUNCH(NT_, EPI_, false, 4); } \
+        else if (mt == 1) WLAUNCH(NT_, EPI_, true, 1); \
+        else if (mt == 2) WLAUNCH(NT_, EPI_, true, 2); \
+        else if (mt == 3) WLAUNCH(NT_, EPI_, true, 3); \
+        else WLAUNCH(NT_, EPI_, true, 4); \
+    } while (0)
+    if (swiglu_out) WLAUNCH_MT(2, WEPI_SWIGLU);
+    else if (nt == 3) { if (m_groups > 1) WLAUNCH(3, WEPI_PARTIAL, false, 4); else WLAUNCH(3, WEPI_PARTIAL, true, 4); }
+    else if (nt == 2) WLAUNCH_MT(2, WEPI_PARTIAL);
+    else WLAUNCH_MT(1, WEPI_PARTIAL);
+#undef WLAUNCH_MT
 #undef WLAUNCH
 #undef WARGS
 }

@@ -230,6 +230,22 @@ def test_swiglu_in_the_gemm_epilogue_with_the_deferred_norm_scale():
         assert np.abs(V - Vr).max() <= 1e-3 * max(1.0, np.abs(Vr).max())
 
 
+@pytest.mark.parametrize("M", [1, 31, 33, 63, 65, 95, 97, 128, 129, 160, 191, 193, 256])
+@pytest.mark.parametrize("N,K", [(224, 64), (160, 208), (4640, 320), (608, 1040), (33280, 128)])
+def test_wide_format_gemm_for_every_number_of_row_tiles(bb, M, N, K):
+    """Up to 256 rows the wide-format kernel has a body per number of 32-row tiles (two groups of three or four above 128
+    rows), with tiles 128 or 256 columns wide: k ranges of 1, 4, 5 and 17 chunks (less than, equal to and beyond the rings
+    of three and four), column counts that fill no tile, rows that fill no 32.  Tolerance as in the test above."""
+    rng = np.random.default_rng(M * 13 + N)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    Wb = gen_normal_bf16(1, f"w{N}x{K}", N * K, 0.05).view(torch.int16).numpy().view(np.uint16).reshape(N, K)
+    W = (Wb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    print(f"wide gemm rows M={M} N={N} K={K}", flush=True)
+    err = np.abs(bb.debug_gemm(A, Wb, 0, wide=True) - A.astype(np.float64) @ W.T)
+    mag = np.abs(A).astype(np.float64) @ np.abs(W).T
+    assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
+
+
 @pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 97, 129, 161, 225, 257])
 def test_lm_head_row_groups(n):
     """n rows receive logits: 1, 2, 3 or 4 m-tiles in one row group, then two and three groups with the m-tiles dealt evenly
