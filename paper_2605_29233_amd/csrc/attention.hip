@@ -3,13 +3,12 @@
 // Work is cut into tiles of 32 "flattened" query rows (the query heads that share a kv head are
 // folded into the row dimension, so the K/V tiles a wave reads serve all of them), one kv head,
 // one branch segment.  K and V are found page by page (64 tokens) through the branch's page
-// table: shared or private physical row.  Two ways of using the four waves of a workgroup:
-//   SPLITQ = false (block steps: few query rows): one tile per workgroup, the waves take the
+// table: shared or private physical row.  Two kernels:
+//   attention_kernel (block steps: few query rows): one tile per workgroup, the waves take the
 //            row's pages round robin, each keeping a running max / sum / output (online
 //            softmax), and the partial results are combined through LDS in a fixed order;
-//   SPLITQ = true  (full-sequence refresh: many query rows): four tiles per workgroup, one per
-//            wave; the waves walk the pages together, so the fragments the first wave pulls
-//            into L2 serve the other three.
+//   attention_full_kernel (full-sequence passes: many query rows): four tiles per workgroup, one per
+//            wave; the waves walk the pages together, through LDS.
 // Either way the result does not depend on scheduling.
 //
 // Q, K, V and the probabilities P each enter as two fp16 terms (hi + lo); every product keeps
@@ -23,6 +22,7 @@
 //                                                    query), keys permuted consistently.
 #include "bb_internal.h"
 #include <algorithm>
+#include <type_traits>
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
@@ -78,7 +78,7 @@ static __device__ __forceinline__ void softmax_page(f32x16 (&s)[2], bool partial
     }
 }
 
-template <int HD, bool SPLITQ>
+template <int HD>
 __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* __restrict__ Q, u32x4* __restrict__ Apk,
                                                         int layer, int mt_total, int seg_base, int n_splits,
                                                         float* __restrict__ part, int wide) {
@@ -95,11 +95,9 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
     if (seg_rows == 0) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 5, c = lane & 31;
     const int group = D.hq / D.hkv, nflat = seg_rows * group;
-    // block steps may also split a row's pages over n_splits workgroups (blockIdx.y = tile * n_splits + split)
-    const int split = SPLITQ ? 0 : blockIdx.y % n_splits, qtile = SPLITQ ? blockIdx.y : blockIdx.y / n_splits;
-    const int wg_base = qtile * (SPLITQ ? 128 : 32);
+    // a row's pages may also be split over n_splits workgroups (blockIdx.y = tile * n_splits + split)
+    const int split = blockIdx.y % n_splits, qtile = blockIdx.y / n_splits, wg_base = qtile * 32;
     if (wg_base >= nflat) return;
-    const int tile_base = SPLITQ ? wg_base + 32 * wave : wg_base;     // this wave's 32 query rows
     const int kvh = blockIdx.x, seg_off = D.seg_off[gbr];
     const int L = D.hdr[gbr / D.max_br].L, n_pages = (L + BB_PAGE - 1) / BB_PAGE;
 
@@ -108,7 +106,7 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
     // of a row are one contiguous run of HD/2 values.  Rows past the end repeat the last row (never stored).
     u32x4 qf[2][KS];                    // [term][k-step]
     {
-        const int f = min(tile_base + c, nflat - 1);
+        const int f = min(wg_base + c, nflat - 1);
         const int hig = f / seg_rows, r = f % seg_rows;
         const half_t* qp = Q + ((size_t)(seg_off + r) * D.hq + kvh * group + hig) * 2 * HD + (HD / 2) * g;
 #pragma unroll
@@ -124,8 +122,7 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
         for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
 
     const int pps = (n_pages + n_splits - 1) / n_splits;           // pages per split
-    const int p0 = SPLITQ ? 0 : split * pps + wave, pstep = SPLITQ ? 1 : 4;
-    const int p1 = (SPLITQ ? tile_base < nflat : true) ? (SPLITQ ? n_pages : min(n_pages, (split + 1) * pps)) : 0;
+    const int p0 = split * pps + wave, pstep = 4, p1 = min(n_pages, (split + 1) * pps);
     // A page's K and V fragments (NF x 1 KiB each way) pass through one ring of NF registers-fragments in halves:
     // K tile 0 | K tile 1 -> V dims low | V dims high -> next page's K tile 0 | ...  Each half is requested as
     // soon as the MFMAs that read the half before it have been issued, so a wave always has 16-32 KiB in
@@ -195,11 +192,9 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
             for (int r = 0; r < 16; ++r) sO[wave][c][32 * dt + 8 * (r >> 2) + 4 * g + (r & 3)] = o[dt][r];
     }
     __syncthreads();
-    // normalise (after a fixed-order combine over the four waves when they split the pages), split into
-    // bf16 hi/lo and store as the O-projection's packed activation panel (row = packed query row,
-    // k = head * HD + d).
-    constexpr int ROWS = SPLITQ ? 128 : 32;
-    if (!SPLITQ && n_splits > 1) {
+    // normalise after a fixed-order combine over the four waves, split into two terms and store as the O-projection's
+    // packed activation panel (row = packed query row, k = head * HD + d).
+    if (n_splits > 1) {
         // unnormalised partial result of this split: max[32], sum[32], O[32][HD]; attention_combine_kernel finishes
         float* dst = part + ((((size_t)blockIdx.z * gridDim.x + blockIdx.x) * (gridDim.y / n_splits) + qtile) * n_splits + split) * (64 + 32 * HD);
         for (int item = threadIdx.x; item < 32 * (HD / 4); item += 256) {
@@ -221,35 +216,166 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
         }
         return;
     }
-    for (int item = threadIdx.x; item < ROWS * (HD / 8); item += 256) {
+    for (int item = threadIdx.x; item < 32 * (HD / 8); item += 256) {
         const int q = item / (HD / 8), d8 = item % (HD / 8);
         const int f = wg_base + q;
         if (f >= nflat) continue;
-        float y[8];
-        if (SPLITQ) {
-            const int w = q >> 5, qq = q & 31;
-            const float inv = 1.0f / sL[w][qq];
+        float M = sM[0][q];
+        for (int w = 1; w < 4; ++w) M = fmaxf(M, sM[w][q]);
+        float wgt[4], lsum = 0.f, y[8];
+        for (int w = 0; w < 4; ++w) {
+            wgt[w] = sM[w][q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w][q] - M);   // maxima are in the log2 domain
+            lsum += wgt[w] * sL[w][q];
+        }
+        const float inv = 1.0f / lsum;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) y[e] = sO[w][qq][d8 * 8 + e] * inv;
-        } else {
-            float M = sM[0][q];
-            for (int w = 1; w < 4; ++w) M = fmaxf(M, sM[w][q]);
-            float wgt[4], lsum = 0.f;
-            for (int w = 0; w < 4; ++w) {
-                wgt[w] = sM[w][q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w][q] - M);   // maxima are in the log2 domain
-                lsum += wgt[w] * sL[w][q];
-            }
-            const float inv = 1.0f / lsum;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float acc = 0.f;
-                for (int w = 0; w < 4; ++w) acc += wgt[w] * sO[w][q][d8 * 8 + e];
-                y[e] = acc * inv;
-            }
+        for (int e = 0; e < 8; ++e) {
+            float acc = 0.f;
+            for (int w = 0; w < 4; ++w) acc += wgt[w] * sO[w][q][d8 * 8 + e];
+            y[e] = acc * inv;
         }
         const int hig = f / seg_rows, r = f % seg_rows;
         const int m = seg_off + r, k8 = ((kvh * group + hig) * HD) / 8 + d8;
         store_panel8(Apk, m, k8, mt_total, y, wide);
+    }
+}
+
+// One 1 KiB fragment (64 lanes x 16 bytes) from src to the LDS byte offset dst without passing through registers; OFF is
+// added on both sides.  Written as assembly because the compiler, where it knows of such loads, lets every LDS read wait for
+// all outstanding ones: the waits are the explicit ones at the barriers.
+template <int OFF> static __device__ __forceinline__ void load_to_lds(const char* src, unsigned lane16, unsigned dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(dst), "v"(lane16), "s"(src), "n"(OFF) : "memory");
+}
+
+// Many query rows per segment (full-sequence passes): four waves, 32 query rows each, walk the row's pages together.
+// What bounds it: the matrix pipes (96 MFMAs per wave and page at HD = 128, 3072 cycles), beside some 1600 cycles of
+// exponentials and conversions and, per CU, the 64 KB of a page.  So a page is fetched once per workgroup into LDS, by
+// direct-to-LDS loads (with every wave fetching it for itself, a page step was 256 KB through the CU's load path: 4096 cycles
+// and more, the longest of the three), and two workgroups share a CU, so that one's softmax runs beside the other's MFMAs:
+// hence 64 KB of LDS each, K and V once, no second buffers.  K of the next page is on its way while V is being used, and V
+// while K is:
+//   [K landed] barrier | request V | scores | barrier | request next K | softmax | [V landed] barrier | P.V
+// Measured, us per launch (heads of 128; before = every wave fetching for itself, one workgroup per CU): 4 x 5120 rows and
+// keys, 32 heads 5443 -> 4041 (1.27 PFLOP/s in MFMAs; the pipes alone sustain 1.67 with such MFMAs at the power limit), 4 x 768
+// 156 -> 118, 3 x 1402 with 28 query and 4 kv heads 327 -> 240; 768 x 768 (192 workgroups) 47 -> 48.
+// A higher wave priority around the MFMAs was slower (4222).
+template <int HD>
+__global__ __launch_bounds__(256, 2) void attention_full_kernel(Dev D, const half_t* __restrict__ Q, u32x4* __restrict__ Apk,
+                                                                int layer, int mt_total, int seg_base, int wide) {
+    constexpr int KS = HD / 16, DT = HD / 32, NF = 4 * KS;         // k-steps of the scores, output tiles, fragments of a K (or V) page
+    constexpr int PAGE_BYTES = NF * 1024, LDO = 64 + 1;            // store slice: 32 rows x 64 dims, odd row stride
+    __shared__ __attribute__((aligned(16))) char lds[2 * PAGE_BYTES > 4 * 32 * LDO * 4 ? 2 * PAGE_BYTES : 4 * 32 * LDO * 4];
+    const int gbr = seg_base + blockIdx.z, seg_rows = D.seg_rows[gbr];
+    if (seg_rows == 0) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 5, c = lane & 31;
+    const int group = D.hq / D.hkv, nflat = seg_rows * group, wg_base = blockIdx.y * 128;
+    if (wg_base >= nflat) return;
+    const int tile_base = wg_base + 32 * wave;      // (waves past the end repeat the last row, take part in the loads and store nothing)
+    const int kvh = blockIdx.x, seg_off = D.seg_off[gbr];
+    const int L = D.hdr[gbr / D.max_br].L, n_pages = (L + BB_PAGE - 1) / BB_PAGE;
+    const unsigned lane16 = lane * 16, lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)lds;
+    // this wave's quarter of a page: KS fragments in a row
+    auto request = [&](const half_t* cache, int phys, int page, int buf) {
+        const char* src = reinterpret_cast<const char*>(cache + kv_block_off(D, layer, phys, page, kvh)) + wave * (KS * 1024);
+        const unsigned dst = lds0 + buf * PAGE_BYTES + wave * (KS * 1024);
+#pragma unroll
+        for (int q = 0; q < KS / 4; ++q) {
+            load_to_lds<0>(src + q * 4096, lane16, dst + q * 4096);
+            load_to_lds<1024>(src + q * 4096, lane16, dst + q * 4096);
+            load_to_lds<2048>(src + q * 4096, lane16, dst + q * 4096);
+            load_to_lds<3072>(src + q * 4096, lane16, dst + q * 4096);
+        }
+    };
+    // all but the latest `Later` requests of this wave have landed and its LDS reads are done; after the barrier so are the others'
+    auto landed = [&](auto Later) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(Later)::value) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    typedef std::integral_constant<int, 0> None;
+    typedef std::integral_constant<int, KS> OnePage;
+    u32x4 qf[2][KS];                    // Q fragments as in attention_kernel
+    {
+        const int f = min(tile_base + c, nflat - 1), hig = f / seg_rows, r = f % seg_rows;
+        const half_t* qp = Q + ((size_t)(seg_off + r) * D.hq + kvh * group + hig) * 2 * HD + (HD / 2) * g;
+#pragma unroll
+        for (int term = 0; term < 2; ++term)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) qf[term][ks] = *reinterpret_cast<const u32x4*>(qp + term * HD + 8 * ks);
+    }
+    // the page table, 64 entries at a time, one per lane (a load per page would stand in line behind the page's own)
+    const int* table = D.table + (size_t)gbr * D.n_pages;
+    int entries = table[min(lane, n_pages - 1)], phys = __builtin_amdgcn_readlane(entries, 0);
+    request(D.Kc, phys, 0, 0);
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x16 o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+    const u32x4 *kl = reinterpret_cast<const u32x4*>(lds) + lane, *vl = kl + NF * 64;
+    for (int page = 0; page < n_pages; ++page) {
+        landed(None{});                     // K
+        request(D.Vt, phys, page, 1);
+        if (((page + 1) & 63) == 0) entries = table[min(page + 1 + lane, n_pages - 1)];
+        phys = __builtin_amdgcn_readlane(entries, min(page + 1, n_pages - 1) & 63);
+        f32x16 s[2];
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[kt][r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            f16x8 kh[2], klo[2];
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) { kh[kt] = as_f16x8(kl[((kt * KS + ks) * 2) * 64]); klo[kt] = as_f16x8(kl[((kt * KS + ks) * 2 + 1) * 64]); }
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) s[kt] = MFMA16(klo[kt], as_f16x8(qf[0][ks]), s[kt]);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) s[kt] = MFMA16(kh[kt], as_f16x8(qf[1][ks]), s[kt]);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) s[kt] = MFMA16(kh[kt], as_f16x8(qf[0][ks]), s[kt]);
+        }
+        landed(OnePage{});                  // (V may still be on its way: every wave is done with K)
+        request(D.Kc, phys, min(page + 1, n_pages - 1), 0);        // (past the end: the last page again, which nothing reads)
+        f16x8 ph[4], pl[4];
+        softmax_page<DT>(s, page * BB_PAGE + BB_PAGE > L, page * BB_PAGE, L, g, m_run, l_run, o, ph, pl);
+        landed(OnePage{});                  // V
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            f16x8 vh[DT], vlo[DT];
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) { vh[dt] = as_f16x8(vl[((dt * 4 + kk) * 2) * 64]); vlo[dt] = as_f16x8(vl[((dt * 4 + kk) * 2 + 1) * 64]); }
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt] = MFMA16(vlo[dt], ph[kk], o[dt]);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt] = MFMA16(vh[dt], pl[kk], o[dt]);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt] = MFMA16(vh[dt], ph[kk], o[dt]);
+        }
+    }
+    // Normalise and store as the O-projection's panel (row = packed query row, k = head * HD + d), 64 dims at a time through
+    // this wave's slice of LDS.  o[dt][r] is O^T[d = 32 dt + 8 (r/4) + 4 g + r%4][query c]; a lane then takes 8 dims of one
+    // row, neighbouring lanes neighbouring rows, which are adjacent in the panel.
+    const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32, 64));
+    landed(None{});                                         // all waves are done with V, and no request is on its way
+    float* so = reinterpret_cast<float*>(lds) + wave * (32 * LDO);
+    const int f = tile_base + c, hig = min(f, nflat - 1) / seg_rows, m = seg_off + min(f, nflat - 1) % seg_rows;
+#pragma unroll
+    for (int half = 0; half < DT / 2; ++half) {
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) so[c * LDO + 32 * dt + 8 * (r >> 2) + 4 * g + (r & 3)] = o[2 * half + dt][r] * inv;
+        // (the same wave wrote and reads: no barrier needed, the LDS counter orders them)
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int d8 = 2 * it + g;
+            float y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = so[c * LDO + d8 * 8 + e];
+            if (f < nflat) store_panel8(Apk, m, ((kvh * group + hig) * HD + 64 * half) / 8 + d8, mt_total, y, wide);
+        }
     }
 }
 
@@ -295,8 +421,8 @@ void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int 
     const int group = D.hq / D.hkv, nflat = max_seg_rows * group;
     if (nflat >= 512) {     // many query rows per segment: waves take different query tiles
         dim3 grid(D.hkv, (nflat + 127) / 128, n_segs);
-        if (D.hd == 128) attention_kernel<128, true><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, 1, nullptr, wide);
-        else attention_kernel<64, true><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, 1, nullptr, wide);
+        if (D.hd == 128) attention_full_kernel<128><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
+        else attention_full_kernel<64><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
         return;
     }
     // few query rows: one workgroup per tile unless that leaves most of the 256 CUs idle; then the pages of a
@@ -307,10 +433,10 @@ void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int 
     if (n_splits < 1) n_splits = 1;
     dim3 grid(D.hkv, qtiles * n_splits, n_segs), cgrid(D.hkv, qtiles, n_segs);
     if (D.hd == 128) {
-        attention_kernel<128, false><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide);
+        attention_kernel<128><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide);
         if (n_splits > 1) attention_combine_kernel<128><<<cgrid, 256, 0, s>>>(D, part, Apk, mt_total, seg_base, n_splits, wide);
     } else {
-        attention_kernel<64, false><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide);
+        attention_kernel<64><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide);
         if (n_splits > 1) attention_combine_kernel<64><<<cgrid, 256, 0, s>>>(D, part, Apk, mt_total, seg_base, n_splits, wide);
     }
 }

@@ -154,6 +154,19 @@ def test_last_page_holds_one_key():
     check_report(s)
 
 
+@pytest.mark.parametrize("prompt_len,gen_len,head_dim", [
+    (40, 24, 128), (41, 24, 128), (70, 57, 128), (96, 33, 64), (100, 91, 64), (30, 35, 64)])
+def test_full_pass_attention_tiles(prompt_len, gen_len, head_dim):
+    """Full passes with at least 512 flattened query rows per branch (eight query heads per kv head): one page, a second page
+    with a single key, a ragged last page; row counts that leave the last workgroup of four 32-row tiles with one, two or
+    three of them, the last partly filled.  Refreshes every second step, against the oracle in fp64."""
+    shape = ModelShape("fullatt", 2, 256, 1024 // head_dim, 128 // head_dim, head_dim, 688, 1024)
+    assert (prompt_len + gen_len) * 8 >= 512
+    s = run_case(shape, DecodeParams(0.9, 0.5, 4, 2, 0), prompt_len, gen_len, (8, 16), seed=21, max_steps=5)
+    assert s.rep.max_logit_err <= 3e-2
+    check_report(s)
+
+
 def test_long_row_with_empty_attention_splits():
     """L = 64 * 64 + 1 = 4097 keys against at most 32 query rows per branch: the block-step attention cuts the 65
     pages of a row into 16 splits of 5 pages, of which the last three are empty, the last page holds one key, and
