@@ -78,14 +78,24 @@ static __device__ __forceinline__ void softmax_page(f32x16 (&s)[2], bool partial
     }
 }
 
-template <int HD>
-__global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* __restrict__ Q, u32x4* __restrict__ Apk,
+// WAVES waves per workgroup, two per SIMD either way: eight of one workgroup, or four each of two.  What bounds it: the K,V
+// stream, at the HBM's rate where it is long enough, otherwise at what a CU can have in flight (some 64 KB, so about 50 GB/s)
+// and at each wave's own chain of loads, MFMAs and exponentials, which the second wave of its SIMD fills.  So a wave keeps to
+// 256 registers: two quarters of a K or V page in flight, and Q in LDS (all waves use the same fragments), in the space
+// that the waves' results take after the last page.
+// Measured, us per launch (heads of 128; before = four waves with 512 registers each, half pages in flight): 768 keys, 320 tiles
+// 46.8 -> 43.3, 160 tiles 27.3 -> 26.5, 32 tiles in three splits 14.2 -> 13.1; 5120 keys, 256 tiles 149 -> 149.
+template <int HD, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void attention_kernel(Dev D, const half_t* __restrict__ Q, u32x4* __restrict__ Apk,
                                                         int layer, int mt_total, int seg_base, int n_splits,
                                                         float* __restrict__ part, int wide) {
     constexpr int KS = HD / 16;         // k-steps of the score contraction
     constexpr int DT = HD / 32;         // 32-wide tiles of the output's head dimension
-    __shared__ float sO[4][32][HD + 1];
-    __shared__ float sM[4][32], sL[4][32];
+    constexpr int THREADS = 64 * WAVES;
+    __shared__ u32x4 sQO[(WAVES * 32 * (HD + 1) + 3) / 4];
+    static_assert(2 * KS * 64 <= (int)(sizeof(sQO) / 16), "Q fragments exceed the results' space");
+    float (*sO)[32][HD + 1] = reinterpret_cast<float (*)[32][HD + 1]>(sQO);
+    __shared__ float sM[WAVES][32], sL[WAVES][32];
 
     // Grid = (kv head, query tile [x split], segment).  The kv head is the fastest index on purpose: workgroups go
     // to the eight XCDs round robin by linear id, so with a multiple of eight kv heads all query tiles and page
@@ -101,90 +111,86 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
     const int kvh = blockIdx.x, seg_off = D.seg_off[gbr];
     const int L = D.hdr[gbr / D.max_br].L, n_pages = (L + BB_PAGE - 1) / BB_PAGE;
 
+    const int pps = (n_pages + n_splits - 1) / n_splits;           // pages per split
+    const int p0 = split * pps + wave, p1 = min(n_pages, (split + 1) * pps);
+    // A page's K and V fragments (NF x 1 KiB each way) pass through a ring of two quarters: a quarter is requested as soon as
+    // the MFMAs that read its place in the ring have been issued.
+    constexpr int NF = 4 * KS, QF = NF / 4;         // (NF = DT * 4 * 2 as well)
+    u32x4 kv[2][QF];
+    auto block = [&](const half_t* cache, int page) {
+        const int phys = D.table[(size_t)gbr * D.n_pages + page];
+        return reinterpret_cast<const u32x4*>(cache + kv_block_off(D, layer, phys, page, kvh)) + lane;
+    };
+    auto fetch = [&](int q, const u32x4* src) {     // quarter q of a block
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < QF; ++i) kv[q & 1][i] = src[(q * QF + i) * 64];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const u32x4* Kp = block(D.Kc, min(p0, D.n_pages - 1));
+    if (p0 < p1) { fetch(0, Kp); fetch(1, Kp); }
     // Q fragments (B operand).  The contraction index may be enumerated in any order as long as K uses the
     // same one: k-step ks, lane group g, slot j  <->  head dim (HD/2) g + 8 ks + j, so a lane's KS fragments
     // of a row are one contiguous run of HD/2 values.  Rows past the end repeat the last row (never stored).
-    u32x4 qf[2][KS];                    // [term][k-step]
-    {
-        const int f = min(wg_base + c, nflat - 1);
-        const int hig = f / seg_rows, r = f % seg_rows;
-        const half_t* qp = Q + ((size_t)(seg_off + r) * D.hq + kvh * group + hig) * 2 * HD + (HD / 2) * g;
-#pragma unroll
-        for (int term = 0; term < 2; ++term)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) qf[term][ks] = *reinterpret_cast<const u32x4*>(qp + term * HD + 8 * ks);
+    for (int i = wave; i < 2 * KS; i += WAVES) {    // fragment i = term * KS + ks
+        const int f = min(wg_base + c, nflat - 1), hig = f / seg_rows, r = f % seg_rows;
+        sQO[i * 64 + lane] = *reinterpret_cast<const u32x4*>(Q + ((size_t)(seg_off + r) * D.hq + kvh * group + hig) * 2 * HD + (HD / 2) * g +
+                                                             (i / KS) * HD + 8 * (i % KS));
     }
+    __syncthreads();
     float m_run = -INFINITY, l_run = 0.f;
     f32x16 o[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-
-    const int pps = (n_pages + n_splits - 1) / n_splits;           // pages per split
-    const int p0 = split * pps + wave, pstep = 4, p1 = min(n_pages, (split + 1) * pps);
-    // A page's K and V fragments (NF x 1 KiB each way) pass through one ring of NF registers-fragments in halves:
-    // K tile 0 | K tile 1 -> V dims low | V dims high -> next page's K tile 0 | ...  Each half is requested as
-    // soon as the MFMAs that read the half before it have been issued, so a wave always has 16-32 KiB in
-    // flight and pays the memory latency per half page, not per fragment.
-    constexpr int NF = 2 * KS * 2, H = NF / 2;      // NF = DT * 4 * 2 as well
-    u32x4 kv[NF];
-    auto block = [&](const half_t* cache, int page) {
-        const int phys = D.table[(size_t)gbr * D.n_pages + page];
-        return reinterpret_cast<const u32x4*>(cache + kv_block_off(D, layer, phys, page, kvh)) + lane;
-    };
-    auto fetch_half = [&](int h, const u32x4* src) {
-#pragma unroll
-        for (int i = 0; i < H; ++i) kv[h * H + i] = src[(h * H + i) * 64];
-    };
-    if (p0 < p1) { const u32x4* Kp = block(D.Kc, p0); fetch_half(0, Kp); fetch_half(1, Kp); }
-    for (int page = p0; page < p1; page += pstep) {
-        const int t0 = page * BB_PAGE, nxt = page + pstep;
+    for (int page = p0; page < p1; page += WAVES) {
+        const int t0 = page * BB_PAGE, nxt = page + WAVES;
         const u32x4* Vp = block(D.Vt, page);
         const u32x4* Kn = block(D.Kc, min(nxt, D.n_pages - 1));
         // scores: two tiles of 32 keys.  The cache stores MFMA row i of a tile as key pi(i) = i%4 + 4 (i/8) + 16 ((i/4)%2),
         // which makes the 16 accumulator registers of a lane the 16 consecutive keys t0 + 32 kt + 16 g + r
-        // (query c): the order of the V^T fragments' contraction index.  Fragment (kt, ks, term) = kv[(kt KS + ks) 2 + term].
+        // (query c): the order of the V^T fragments' contraction index.  Fragment pair (kt, ks) = pair kt KS + ks of the page.
         f32x16 s[2];
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+        for (int q = 0; q < 4; ++q) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[kt][r] = 0.f;
+            for (int i = 0; i < QF / 2; ++i) {
+                const int kt = (q * (QF / 2) + i) / KS, ks = (q * (QF / 2) + i) % KS;
+                if (ks == 0)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const f16x8 kh = as_f16x8(kv[(kt * KS + ks) * 2 + 0]);
-                const f16x8 kl = as_f16x8(kv[(kt * KS + ks) * 2 + 1]);
-                s[kt] = MFMA16(kl, as_f16x8(qf[0][ks]), s[kt]);
-                s[kt] = MFMA16(kh, as_f16x8(qf[1][ks]), s[kt]);
-                s[kt] = MFMA16(kh, as_f16x8(qf[0][ks]), s[kt]);
+                    for (int r = 0; r < 16; ++r) s[kt][r] = 0.f;
+                const f16x8 qh = as_f16x8(sQO[ks * 64 + lane]), ql = as_f16x8(sQO[(KS + ks) * 64 + lane]);
+                const f16x8 kh = as_f16x8(kv[q & 1][2 * i]), kl = as_f16x8(kv[q & 1][2 * i + 1]);
+                s[kt] = MFMA16(kl, qh, s[kt]);
+                s[kt] = MFMA16(kh, ql, s[kt]);
+                s[kt] = MFMA16(kh, qh, s[kt]);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            fetch_half(kt, Vp);
-            __builtin_amdgcn_sched_barrier(0);
+            if (q < 2) fetch(q + 2, Kp);
+            else fetch(q - 2, Vp);
         }
         f16x8 ph[4], pl[4];
         softmax_page<DT>(s, t0 + BB_PAGE > L, t0, L, g, m_run, l_run, o, ph, pl);
-        // fragment (dt, kk, term) = kv[(dt 4 + kk) 2 + term]
+        // fragment pair (dt, kk) = pair dt 4 + kk of the page
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
+        for (int q = 0; q < 4; ++q) {
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const f16x8 vh = as_f16x8(kv[(dt * 4 + kk) * 2 + 0]);
-                const f16x8 vl = as_f16x8(kv[(dt * 4 + kk) * 2 + 1]);
+            for (int i = 0; i < QF / 2; ++i) {
+                const int dt = (q * (QF / 2) + i) / 4, kk = (q * (QF / 2) + i) % 4;
+                const f16x8 vh = as_f16x8(kv[q & 1][2 * i]), vl = as_f16x8(kv[q & 1][2 * i + 1]);
                 o[dt] = MFMA16(vl, ph[kk], o[dt]);
                 o[dt] = MFMA16(vh, pl[kk], o[dt]);
                 o[dt] = MFMA16(vh, ph[kk], o[dt]);
             }
-            if (dt % (DT / 2) == DT / 2 - 1) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (nxt < p1) fetch_half(dt / (DT / 2), Kn);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            if (q < 2) fetch(q + 2, Vp);
+            else if (nxt < p1) fetch(q - 2, Kn);
         }
+        Kp = Kn;
     }
+    __syncthreads();                                // all waves are done with Q
     // per-wave results -> LDS.  o[dt][r] is O^T[d = 32 dt + 8 (r/4) + 4 g + r%4][query c].
     {
-        float l = l_run + __shfl_xor(l_run, 32, 64);
+        const float l = l_run + __shfl_xor(l_run, 32, 64);
         if (g == 0) { sM[wave][c] = m_run; sL[wave][c] = l; }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -192,22 +198,29 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
             for (int r = 0; r < 16; ++r) sO[wave][c][32 * dt + 8 * (r >> 2) + 4 * g + (r & 3)] = o[dt][r];
     }
     __syncthreads();
-    // normalise after a fixed-order combine over the four waves, split into two terms and store as the O-projection's
-    // packed activation panel (row = packed query row, k = head * HD + d).
+    // a row's results, combined over the waves in a fixed order
+    auto combine = [&](int q, float (&wgt)[WAVES], float& M) {
+        M = sM[0][q];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sM[w][q]);
+        float lsum = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            wgt[w] = sM[w][q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w][q] - M);           // maxima are in the log2 domain
+            lsum += wgt[w] * sL[w][q];
+        }
+        return lsum;
+    };
     if (n_splits > 1) {
         // unnormalised partial result of this split: max[32], sum[32], O[32][HD]; attention_combine_kernel finishes
         float* dst = part + ((((size_t)blockIdx.z * gridDim.x + blockIdx.x) * (gridDim.y / n_splits) + qtile) * n_splits + split) * (64 + 32 * HD);
-        for (int item = threadIdx.x; item < 32 * (HD / 4); item += 256) {
+        for (int item = threadIdx.x; item < 32 * (HD / 4); item += THREADS) {
             const int q = item / (HD / 4), d4 = item % (HD / 4);
-            float M = sM[0][q];
-            for (int w = 1; w < 4; ++w) M = fmaxf(M, sM[w][q]);
-            float wgt[4], lsum = 0.f;
-            for (int w = 0; w < 4; ++w) {
-                wgt[w] = sM[w][q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w][q] - M);   // maxima are in the log2 domain
-                lsum += wgt[w] * sL[w][q];
-            }
+            float wgt[WAVES], M;
+            const float lsum = combine(q, wgt, M);
             float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int w = 0; w < 4; ++w) {
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
                 acc.x += wgt[w] * sO[w][q][d4 * 4 + 0]; acc.y += wgt[w] * sO[w][q][d4 * 4 + 1];
                 acc.z += wgt[w] * sO[w][q][d4 * 4 + 2]; acc.w += wgt[w] * sO[w][q][d4 * 4 + 3];
             }
@@ -216,27 +229,22 @@ __global__ __launch_bounds__(256, 1) void attention_kernel(Dev D, const half_t* 
         }
         return;
     }
-    for (int item = threadIdx.x; item < 32 * (HD / 8); item += 256) {
-        const int q = item / (HD / 8), d8 = item % (HD / 8);
-        const int f = wg_base + q;
+    // normalise, split into two terms and store as the O-projection's packed activation panel (row = packed query row,
+    // k = head * HD + d); neighbouring lanes take neighbouring rows, which are adjacent there.
+    for (int item = threadIdx.x; item < 32 * (HD / 8); item += THREADS) {
+        const int q = item & 31, d8 = item >> 5, f = wg_base + q;
         if (f >= nflat) continue;
-        float M = sM[0][q];
-        for (int w = 1; w < 4; ++w) M = fmaxf(M, sM[w][q]);
-        float wgt[4], lsum = 0.f, y[8];
-        for (int w = 0; w < 4; ++w) {
-            wgt[w] = sM[w][q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w][q] - M);   // maxima are in the log2 domain
-            lsum += wgt[w] * sL[w][q];
-        }
-        const float inv = 1.0f / lsum;
+        float wgt[WAVES], M, y[8];
+        const float inv = 1.0f / combine(q, wgt, M);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             float acc = 0.f;
-            for (int w = 0; w < 4; ++w) acc += wgt[w] * sO[w][q][d8 * 8 + e];
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) acc += wgt[w] * sO[w][q][d8 * 8 + e];
             y[e] = acc * inv;
         }
         const int hig = f / seg_rows, r = f % seg_rows;
-        const int m = seg_off + r, k8 = ((kvh * group + hig) * HD) / 8 + d8;
-        store_panel8(Apk, m, k8, mt_total, y, wide);
+        store_panel8(Apk, seg_off + r, ((kvh * group + hig) * HD) / 8 + d8, mt_total, y, wide);
     }
 }
 
@@ -415,9 +423,10 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const flo
     }
 }
 
-// max_pages: pages of the longest row among the segments; part / part_elems: scratch for split partial results.
+// max_pages: pages of the longest row among the segments; seg_tiles: 32-row tiles over all segments (an upper bound);
+// part / part_elems: scratch for split partial results.
 void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int mt_total, int max_seg_rows,
-                      int seg_base, int n_segs, int max_pages, float* part, size_t part_elems, int wide, hipStream_t s) {
+                      int seg_base, int n_segs, int max_pages, int seg_tiles, float* part, size_t part_elems, int wide, hipStream_t s) {
     const int group = D.hq / D.hkv, nflat = max_seg_rows * group;
     if (nflat >= 512) {     // many query rows per segment: waves take different query tiles
         dim3 grid(D.hkv, (nflat + 127) / 128, n_segs);
@@ -425,18 +434,24 @@ void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int 
         else attention_full_kernel<64><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
         return;
     }
-    // few query rows: one workgroup per tile unless that leaves most of the 256 CUs idle; then the pages of a
-    // row are split over several workgroups (each wave keeps at least one page) and a second kernel merges them
-    const int qtiles = (nflat + 31) / 32, tiles = qtiles * D.hkv * n_segs;
-    int n_splits = std::min(std::min(256 / tiles, (max_pages + 3) / 4), 16);
+    // Few query rows: a workgroup per tile, of four waves (two workgroups to a CU) up to 16 pages, of eight above: with one
+    // workgroup per CU four waves leave the CU's loads idle (80 pages, 256 tiles: 236 us against 149; 24 pages, 200
+    // workgroups: 27.5 against 19.8), with few pages eight have too little each (12 pages, 320 tiles: 44.9 us against 43.3).
+    // Where the tiles leave CUs idle the pages of a row are split over several workgroups and a second kernel merges the
+    // partial results: worth it once the share of a CU's own stream that it saves (about 50 KB per us) exceeds that launch
+    // (100 tiles, 24 pages: 31.0 us unsplit, 19.8 + 5.7 in two).
+    const int qtiles = (nflat + 31) / 32, tiles = qtiles * D.hkv * n_segs, wgs = std::max(1, seg_tiles * D.hkv), waves = max_pages > 16 ? 8 : 4;
+    const double stream_us = max_pages * (D.hd * 512.0) / 50e3, combine_us = 7.0;
+    int n_splits = std::min(std::min(256 / wgs, (max_pages + waves - 1) / waves), 16);
     while (n_splits > 1 && (size_t)tiles * n_splits * (64 + 32 * D.hd) > part_elems) --n_splits;
-    if (n_splits < 1) n_splits = 1;
+    if (n_splits < 1 || stream_us - stream_us / n_splits < combine_us) n_splits = 1;
     dim3 grid(D.hkv, qtiles * n_splits, n_segs), cgrid(D.hkv, qtiles, n_segs);
-    if (D.hd == 128) {
-        attention_kernel<128><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide);
-        if (n_splits > 1) attention_combine_kernel<128><<<cgrid, 256, 0, s>>>(D, part, Apk, mt_total, seg_base, n_splits, wide);
-    } else {
-        attention_kernel<64><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide);
-        if (n_splits > 1) attention_combine_kernel<64><<<cgrid, 256, 0, s>>>(D, part, Apk, mt_total, seg_base, n_splits, wide);
-    }
+#define ATT(HD_) do { \
+        if (waves == 8) attention_kernel<HD_, 8><<<grid, 512, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide); \
+        else attention_kernel<HD_, 4><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide); \
+        if (n_splits > 1) attention_combine_kernel<HD_><<<cgrid, 256, 0, s>>>(D, part, Apk, mt_total, seg_base, n_splits, wide); \
+    } while (0)
+    if (D.hd == 128) ATT(128);
+    else ATT(64);
+#undef ATT
 }

@@ -467,7 +467,7 @@ static int check_reqs(bb_ctx* c, const int* ids, int n, bool need_init) {
 // ---- the forward -----------------------------------------------------------------------------------
 // mode 0: block step with LM head; 1: initial full forward with LM head over lm_cap rows
 // (results broadcast to all branches); 2: cache-only refresh (stops after the last K,V write).
-static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, int n_segs, int max_seg_rows, int max_pages) {
+static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, int n_segs, int max_seg_rows, int max_pages, int seg_tiles) {
     const bb_model_cfg& m = c->m; const Dev& D = c->D; hipStream_t s = c->stream;
     const int d = m.d_model, nq = m.n_q_heads * m.head_dim, f = m.d_ffn, nqkv = D.nqkv, ngu = c->ngu;
     const int mt = (rows_cap + 31) / 32, rows_pad = mt * 32;
@@ -515,7 +515,7 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
         { PROF(BB_K_GLUE, 0, 0);
           launch_qkv_epilogue(D, c->qkv, s_qkv, (size_t)rows_pad * nqkv, m.qkv_bias ? W.bqkv : nullptr, c->Q, li, rows_cap, ssq, nblk, s); }
         if (mode == 2 && li == m.n_layers - 1) break;
-        { PROF(BB_K_ATTENTION, 0, 0); launch_attention(D, c->Q, c->Apk, li, mt, max_seg_rows, seg_base, n_segs, max_pages, c->attn_part, c->attn_part_elems, wide, s); }
+        { PROF(BB_K_ATTENTION, 0, 0); launch_attention(D, c->Q, c->Apk, li, mt, max_seg_rows, seg_base, n_segs, max_pages, seg_tiles, c->attn_part, c->attn_part_elems, wide, s); }
         const int s_o = gemm(1, W.wo, W.wo_w, W.s_o, c->Apk, c->part, d, nq, rows_cap, mt, gk);
         { PROF(BB_K_GLUE, 0, 0);
           if (defer) nblk = launch_residual_pack(D, c->h, c->part, s_o, pstride, W.g_ffn, c->Apk, mt, c->ssq, wide, s);
@@ -553,6 +553,9 @@ static int upload_req_list(bb_ctx* c, const int* ids, int n) {
     return BB_OK;
 }
 
+// 32-row attention tiles of a segment of `rows` packed rows (per kv head)
+static int att_tiles(const bb_ctx* c, int rows) { return (rows * (c->m.n_q_heads / c->m.n_kv_heads) + 31) / 32; }
+
 static int bb_refresh_impl(bb_ctx* c, const int* ids, int n, int mode) {
     int rc = check_reqs(c, ids, n, mode == BB_PERIODIC);
     if (rc != BB_OK) return rc;
@@ -563,16 +566,16 @@ static int bb_refresh_impl(bb_ctx* c, const int* ids, int n, int mode) {
     // request of the largest shape): consecutive requests share a forward while their rows fit.
     const int rows_max = std::max(c->lim.max_step_rows, c->refresh_rows_cap), lm_max = c->D.lm_cap;
     for (int i = 0; i < n;) {
-        int j = i, rows = 0, lm = 0, maxL = 0;
+        int j = i, rows = 0, lm = 0, maxL = 0, tiles = 0;
         while (j < n) {
             const HostReq& R = c->reqs[ids[j]];
             const int r = mode == BB_INIT ? R.L : R.N * R.L, g = mode == BB_INIT ? R.G : 0;
             if (j > i && (rows + r > rows_max || lm + g > lm_max)) break;
-            rows += r; lm += g; maxL = std::max(maxL, R.L); ++j;
+            rows += r; lm += g; maxL = std::max(maxL, R.L); tiles += (mode == BB_INIT ? 1 : R.N) * att_tiles(c, R.L); ++j;
         }
         if ((rc = upload_req_list(c, ids + i, j - i)) != BB_OK) return rc;
         launch_pack_refresh(c->D, j - i, mode, c->stream);
-        rc = forward(c, rows, lm, mode == BB_INIT ? 1 : 2, 0, c->D.max_req * c->D.max_br, maxL, (maxL + BB_PAGE - 1) / BB_PAGE);
+        rc = forward(c, rows, lm, mode == BB_INIT ? 1 : 2, 0, c->D.max_req * c->D.max_br, maxL, (maxL + BB_PAGE - 1) / BB_PAGE, tiles);
         if (rc != BB_OK) return rc;
         if (mode == BB_INIT) for (int k = i; k < j; ++k) c->reqs[ids[k]].initialised = 1;
         i = j;
@@ -590,17 +593,20 @@ static void fill_view(bb_ctx* c, bb_step_view* v) {
 static int bb_denoise_step_impl(bb_ctx* c, const int* ids, int n, bb_step_view* view) {
     int rc = check_reqs(c, ids, n, true);
     if (rc != BB_OK) return rc;
-    int rows = 0, maxb = 0, maxL = 0;
+    int rows = 0, maxb = 0, maxL = 0, tiles = 0;
     for (int i = 0; i < n; ++i) {
         const HostReq& R = c->reqs[ids[i]];
         maxL = std::max(maxL, R.L);
-        for (int k = 0; k < R.N; ++k) { rows += std::min(R.blocks[k], R.G); maxb = std::max(maxb, std::min(R.blocks[k], R.G)); }
+        for (int k = 0; k < R.N; ++k) {
+            const int b = std::min(R.blocks[k], R.G);
+            rows += b; maxb = std::max(maxb, b); tiles += att_tiles(c, b);
+        }
     }
     if (rows > c->lim.max_step_rows) return fail(c, BB_ENOMEM, "step rows exceed max_step_rows");
     if ((rc = upload_req_list(c, ids, n)) != BB_OK) return rc;
     { PROF(BB_K_GLUE, 0, 0); launch_pack_step(c->D, n, c->stream); }
     { PROF(BB_K_POLICY, 0, 0); launch_page_copies(c->D, c->stream); }
-    rc = forward(c, rows, rows, 0, 0, c->D.max_req * c->D.max_br, maxb, (maxL + BB_PAGE - 1) / BB_PAGE);
+    rc = forward(c, rows, rows, 0, 0, c->D.max_req * c->D.max_br, maxb, (maxL + BB_PAGE - 1) / BB_PAGE, tiles);
     if (rc == BB_OK && view) fill_view(c, view);
     return rc;
 }

@@ -167,6 +167,17 @@ def test_full_pass_attention_tiles(prompt_len, gen_len, head_dim):
     check_report(s)
 
 
+@pytest.mark.parametrize("prompt_len", [192, 449, 960, 961])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_block_step_attention_waves_and_splits(prompt_len, head_dim):
+    """Block steps against rows of 4 (one page per wave), 9 (a wave with three, a split with a short last range), 16 and 17
+    pages (the last row length with four waves per workgroup and the first with eight; its last page holds one key)."""
+    shape = ModelShape("blockatt", 1, 256, 256 // head_dim, 256 // head_dim, head_dim, 688, 1024)
+    s = run_case(shape, DecodeParams(0.9, 0.5, 8, 8, 0), prompt_len, 64, (8, 16, 48), seed=22, max_steps=2, kv=False)
+    assert s.rep.max_logit_err <= 3e-2
+    check_report(s)
+
+
 def test_long_row_with_empty_attention_splits():
     """L = 64 * 64 + 1 = 4097 keys against at most 32 query rows per branch: the block-step attention cuts the 65
     pages of a row into 16 splits of 5 pages, of which the last three are empty, the last page holds one key, and
