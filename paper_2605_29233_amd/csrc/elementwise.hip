@@ -13,6 +13,15 @@ static __device__ __forceinline__ float wg_sum(float v, float* sh) {
     return t;
 }
 
+// Workgroups go to the eight XCDs round robin by linear id; this deals n items to them in contiguous runs.  A packed panel's
+// 128-byte lines hold 16-byte pieces of eight consecutive rows: with the rows of a line on one XCD its L2 puts the
+// line together, otherwise several L2s write parts of it.  Measured, us per launch: norm + pack of 1920 rows 41.9 -> 33.9, of
+// 768 rows and four partial tiles 20.6 -> 17.5, residual + pack of 120 rows 7.3 -> 6.9.
+static __device__ __forceinline__ int xcd_run_item(int lin, int n) {
+    const int e = lin & 7;
+    return e * (n >> 3) + min(e, n & 7) + (lin >> 3);
+}
+
 static __device__ __forceinline__ void zero_packed_row(u32x4* Apk, int m, int k8s, int mt_total, int wide) {
     for (int k8 = threadIdx.x; k8 < k8s; k8 += blockDim.x) zero_panel8(Apk, m, k8, mt_total, wide);
 }
@@ -66,7 +75,7 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
                                                            const float* __restrict__ gain, u32x4* __restrict__ Apk,
                                                            int mt_total, int gather, int bcast, int wide) {
     __shared__ float sh[4];
-    const int j = blockIdx.x, d = D.d, k8s = d >> 3;
+    const int j = xcd_run_item(blockIdx.x, gridDim.x), d = D.d, k8s = d >> 3;
     const int count = gather ? D.counts[1] : D.counts[0];
     if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
     const int r = gather ? D.lm_row[j] : j;
@@ -226,7 +235,8 @@ __global__ __launch_bounds__(256) void residual_pack_kernel(Dev D, float* __rest
                                                             const float* __restrict__ gain, u32x4* __restrict__ Apk,
                                                             int mt_total, float* __restrict__ ssq, int nblk, int wide) {
     __shared__ float sh[4];
-    const int j = blockIdx.x / nblk, b = blockIdx.x % nblk, d = D.d, k8 = b * (BB_SSQ_BLOCK / 8) + threadIdx.x;
+    const int item = xcd_run_item(blockIdx.x, gridDim.x), unit = item >> 3;         // eight rows of one column block in a row
+    const int j = unit / nblk * 8 + (item & 7), b = unit % nblk, d = D.d, k8 = b * (BB_SSQ_BLOCK / 8) + threadIdx.x;
     const bool live = k8 < (d >> 3);
     if (j >= D.counts[0]) {
         if (live) zero_panel8(Apk, j, k8, mt_total, wide);
@@ -419,10 +429,10 @@ void launch_qkv_epilogue(const Dev& D, const float* qkv, int n_partial, size_t p
 __global__ __launch_bounds__(256) void swiglu_epilogue_kernel(Dev D, const float* __restrict__ gu, int n_partial,
                                                               size_t partial_stride, int ldp, u32x4* __restrict__ Apk,
                                                               int mt_total, int wide, const float* __restrict__ ssq, int nblk) {
-    const int f8s = (D.f + 63) / 64 * 8;                   // the panel's K is padded to whole chunks of 64 with zeros
-    const size_t it = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int m = (int)(it / f8s), f = (int)(it % f8s) * 8;
-    if (m >= mt_total * 32) return;
+    // A workgroup fills one 32-row x 64-k chunk of the panel (6 KiB in one piece); a wave reads 8 rows x 512 bytes of gate and
+    // up and stores whole 128-byte lines.  (The panel's K is padded to whole chunks of 64 with zeros.)
+    // 120 rows x 12288 features, two partial tiles: 11.2 -> 8.4 us (before: a row per run of workgroups, 16-byte pieces).
+    const int m = (blockIdx.x % mt_total) * 32 + threadIdx.x / 8, f = blockIdx.x / mt_total * 64 + threadIdx.x % 8 * 8;
     if (m >= D.counts[0] || f >= D.f) {
         zero_panel8(Apk, m, f >> 3, mt_total, wide);
         return;
@@ -444,8 +454,7 @@ __global__ __launch_bounds__(256) void swiglu_epilogue_kernel(Dev D, const float
 void launch_swiglu_epilogue(const Dev& D, const float* gu, int n_partial, size_t partial_stride, int ldp, u32x4* Apk,
                             int rows_cap, int mt_total, int wide, const float* ssq, int nblk, hipStream_t s) {
     (void)rows_cap;
-    const size_t items = (size_t)mt_total * 32 * ((D.f + 63) / 64 * 8);
-    swiglu_epilogue_kernel<<<(unsigned)((items + 255) / 256), 256, 0, s>>>(D, gu, n_partial, partial_stride, ldp, Apk, mt_total, wide, ssq, nblk);
+    swiglu_epilogue_kernel<<<mt_total * ((D.f + 63) / 64), 256, 0, s>>>(D, gu, n_partial, partial_stride, ldp, Apk, mt_total, wide, ssq, nblk);
 }
 
 // Second half of the vocabulary reduction.  The LM-head GEMM leaves one (max, rescaled sum of exponentials,
