@@ -112,13 +112,9 @@ static size_t buf_elems(int rows_cap, int N, int K, int forced_nt_wide = 0) {
         // (both operand formats: the wide format can be switched off at run time)
         for (int variant = 0; variant < 3; ++variant) {
             auto plan = [&](int nt) { return variant == 0 ? gemm_plan(rows, N, K, 0, nt) : gemm_plan_wide(rows, N, K, 0, nt, variant == 2); };
-            GemmPlan p = plan(rows > 128 ? forced_nt_wide : 0);
-            size_t e = (size_t)p.split_k * rows * N;
-            if (e > best) best = e;
-            if (rows > BB_DEFER_ROWS) {         // gate/up with the fused SwiGLU epilogue: two tiles per wave
-                p = plan(forced_nt_wide);
-                e = (size_t)p.split_k * rows * N;
-                if (e > best) best = e;
+            for (int nt : {0, forced_nt_wide}) {        // (gate/up with the fused SwiGLU epilogue of the two-term kernel: two tiles per wave)
+                const GemmPlan p = plan(nt);
+                best = std::max(best, (size_t)p.split_k * rows * N);
             }
         }
     }
@@ -481,11 +477,11 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
     // is not split (then 0 is returned and no partial sums exist)
     auto gemm = [&](int kind, const u32x4* W, const u32x4* Ww, const float* wscale, const u32x4* A, float* P, int N, int K,
                     int rows, int mtt, int klass, u32x4* swiglu_out = nullptr, const float* ssq = nullptr, int nblk = 0) {
-        // tile width: the fused SwiGLU epilogue pairs two tiles per wave (passes with more than 128 rows); otherwise the
-        // plan picks it.  With at most 128 rows the norm's scale is deferred: the wide-format kernel's SwiGLU epilogue
+        // tile width: the two-term kernel's fused SwiGLU epilogue pairs two tiles per wave (passes with more than 128 rows);
+        // otherwise the plan picks it.  With at most 128 rows the norm's scale is deferred: the wide-format kernel's SwiGLU epilogue
         // applies it (ssq) where the plan comes out with two tiles per wave and k whole (many columns: the Dream
         // shape), the two-term kernel leaves it to the separate SwiGLU kernel.
-        const int nt = c->force_nt[kind] > 0 ? c->force_nt[kind] : (swiglu_out && !defer ? 2 : 0);
+        const int nt = c->force_nt[kind] > 0 ? c->force_nt[kind] : (swiglu_out && !defer && !wide ? 2 : 0);
         GemmPlan p = wide ? gemm_plan_wide(rows, N, K, 0, nt, swiglu_out && !defer) : gemm_plan(rows, N, K, 0, nt);
         if (c->force_split[kind] > 0 && rows <= 128) p = gemm_plan(rows, N, K, c->force_split[kind], c->force_nt[kind]);
         const bool fused = swiglu_out && (wide || !defer) && p.split_k == 1 && p.nt == 2;
@@ -1078,7 +1074,7 @@ extern "C" int bb_debug_gemm_wide(bb_ctx* c, const float* A, const uint16_t* W, 
 extern "C" int bb_debug_gemm_plan(int M, int N, int K, int wide, int fusable, int out[5]) {
     if (M < 1 || N < 32 || K < 16 || N % 32 || K % 16 || !out) return BB_EINVAL;
     const GemmPlan p = wide ? gemm_plan_wide(M, N, K, 0, 0, fusable != 0) : gemm_plan(M, N, K, 0, 0);
-    const int mt_total = (M + 31) / 32, n_groups = (N / 32 + 4 * p.nt - 1) / (4 * p.nt), m_groups = (mt_total + p.mt - 1) / p.mt;
+    const int mt_total = (M + 31) / 32, n_groups = (N / 32 + p.wv * p.nt - 1) / (p.wv * p.nt), m_groups = (mt_total + p.mt - 1) / p.mt;
     out[0] = p.split_k; out[1] = p.chunks_per_split; out[2] = p.nt; out[3] = p.mt;
     out[4] = wide && mt_total > 8 ? std::min(n_groups * m_groups * p.split_k, 256) : std::min(n_groups * m_groups, 256) * p.split_k;
     return BB_OK;

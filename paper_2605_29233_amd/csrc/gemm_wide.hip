@@ -68,23 +68,24 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
 }
-template <int NT, int EPI, bool STREAM, int MT>
-__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restrict__ Wt, const float* __restrict__ wscale,
+template <int NT, int EPI, bool STREAM, int MT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* __restrict__ Wt, const float* __restrict__ wscale,
                                                            const u32x4* __restrict__ Apk, float* __restrict__ P,
                                                            size_t split_stride, int ldp, int mt_total, int n_tiles,
                                                            int total_chunks, int chunks_per_split, int tiles_x, int tiles_y,
                                                            u32x4* __restrict__ Opk, const float* __restrict__ ssq, int nblk,
                                                            float inv_d, float eps) {
     static_assert(NT >= 1 && NT <= 3 && NT * MT <= 12, "one to three weight tiles per wave, at most 12 accumulator tiles");
+    constexpr int THREADS = 64 * WAVES;
     constexpr int WCHUNK_U4 = MT * BB_WFRAGS * 64;          // uint4 per staged activation chunk (6 KiB per m-tile)
-    constexpr int WA_PER_THREAD = (WCHUNK_U4 + 255) / 256;  // (an odd MT: the last half piece repeats valid data past the chunk's end)
+    constexpr int WA_PER_THREAD = (WCHUNK_U4 + THREADS - 1) / THREADS;  // (an odd MT: the last half piece repeats valid data past the chunk's end)
     constexpr bool DEEP = NT * MT <= 4 && MT < 4;
     constexpr int DW = DEEP ? 4 : 3, AD = DEEP ? 2 : 1;     // chunks in the weight ring and LDS; activation chunks in registers
     constexpr int COLS = 32 * NT, LDT = COLS + 4;           // store slices: row stride in floats (16-byte aligned, conflict-free)
     constexpr int MPP = NT <= 2 && MT % 2 == 0 ? 2 : 1;     // m-tiles per store pass
-    constexpr int STAGES_U4 = DW * WA_PER_THREAD * 256, SLICES_U4 = 4 * 32 * MPP * LDT / 4;
+    constexpr int STAGES_U4 = DW * WA_PER_THREAD * THREADS, SLICES_U4 = WAVES * 32 * MPP * LDT / 4;
     __shared__ u32x4 lds_raw[STAGES_U4 > SLICES_U4 ? STAGES_U4 : SLICES_U4];
-    u32x4 (*lds)[WA_PER_THREAD * 256] = reinterpret_cast<u32x4 (*)[WA_PER_THREAD * 256]>(lds_raw);
+    u32x4 (*lds)[WA_PER_THREAD * THREADS] = reinterpret_cast<u32x4 (*)[WA_PER_THREAD * THREADS]>(lds_raw);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // STREAM (one row group: every weight line is used once): weight loads carry the non-temporal hint, and with a k
     // split the (column group, split) items are dealt to the 8 XCDs in contiguous runs in split-major order, so that an
@@ -107,13 +108,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
     const u32x4* wbase[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int x = min((bx * 4 + wave) * NT + t, n_tiles - 1);      // clamped loads; stores are guarded
+        const int x = min((bx * WAVES + wave) * NT + t, n_tiles - 1);      // clamped loads; stores are guarded
         wbase[t] = Wt + (size_t)x * total_chunks * (KC * 64) + lane;
     }
     int aoff[WA_PER_THREAD];
 #pragma unroll
     for (int i = 0; i < WA_PER_THREAD; ++i) {
-        const int idx = i * 256 + threadIdx.x, mt = idx / (BB_WFRAGS * 64), rem = idx % (BB_WFRAGS * 64);
+        const int idx = i * THREADS + threadIdx.x, mt = idx / (BB_WFRAGS * 64), rem = idx % (BB_WFRAGS * 64);
         aoff[i] = min(mt, mt_cnt - 1) * (BB_WFRAGS * 64) + rem;        // missing m-tiles read a valid one
     }
     const u32x4* abase = Apk + (size_t)mt0 * (BB_WFRAGS * 64);
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
     // more cautious of the two ways in, are those of the steady state
     unroll<AD>([&](auto I) { load_a(a[I], c0 + I); load_w(w[I], c0 + I, 0, KC); });
 #pragma unroll
-    for (int i = 0; i < WA_PER_THREAD; ++i) lds[0][i * 256 + threadIdx.x] = a[0][i];
+    for (int i = 0; i < WA_PER_THREAD; ++i) lds[0][i * THREADS + threadIdx.x] = a[0][i];
     load_a(a[0], c0 + AD);
     unroll<DW - 1 - AD>([&](auto I) { load_w(w[AD + I], c0 + AD + I, 0, KC); });
     __syncthreads();
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
         // fp16 k-step 0
         read_bh(bh[1], st, 1);
 #pragma unroll
-        for (int i = 0; i < WA_PER_THREAD; ++i) lds[st1][i * 256 + threadIdx.x] = a[as][i];
+        for (int i = 0; i < WA_PER_THREAD; ++i) lds[st1][i * THREADS + threadIdx.x] = a[as][i];
         mfma_hi(w[u][0], bh[0]);
         sched_groups<MT, NT, MT, WA_PER_THREAD, 0>();
         // fp16 k-step 1
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
     unroll<DW - 1>([&](auto U) { if (c + U < c1) chunk(U, c + U); });
 
     // undo the per-row weight scale: register r of lane (m = l % 32, g = l / 32) holds weight row 8 (r/4) + 4 g + r%4
-    const int x0 = (bx * 4 + wave) * NT, g = lane >> 5;
+    const int x0 = (bx * WAVES + wave) * NT, g = lane >> 5;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int x = min(x0 + t, n_tiles - 1);
@@ -316,11 +317,44 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
     }
 }
 
-// Plan of a wide-format GEMM.  Up to 256 rows the two-term kernel's plan (one or two groups of 128 rows, k split so
-// that one round of workgroups covers the chip), except that up to 64 rows the tiles are 128 columns wide wherever one
-// round holds them: activations are then little of what a CU fetches, and half as many k splits are written and read back
-// (12288 x 4096 at 32 rows, two splits against five: 19.9 against 21.4 us and a shorter consumer; 24576 x 4096 33.8, unsplit,
-// against 35.9; at 96 rows 25.5 and 46.0 against 24.0 and 41.6).  With more rows (gemm_many_kernel) the candidates (128 or 192 rows per
+static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
+    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, groups = (mt_total + 3) / 4, body = (mt_total + groups - 1) / groups;
+    GemmPlan best;
+    double best_t = 1e30;
+    for (int nt = 1; nt <= (groups > 1 ? 3 : 2); ++nt) {
+        if (nt > 1 && n_tiles < 4 * nt) continue;
+        const int base = (n_tiles + 4 * nt - 1) / (4 * nt) * groups;
+        for (int sp = 1; sp <= BB_MAX_SPLITK && sp <= std::max(1, total_chunks / 4) && (sp == 1 || base * sp <= 256); ++sp) {
+            const int cps = (total_chunks + sp - 1) / sp;
+            if ((total_chunks + cps - 1) / cps != sp) continue;
+            const double live = std::min(base * sp, 256), weights_kb = 16.4 * nt, acts_kb = 6.1 * body;
+            const double own_us = (nt == 1 ? 0.68 : nt == 2 ? (groups > 1 ? 1.15 : 1.08) : 1.95) * (body == 4 ? 1.0 : 0.88);
+            const double chunk_us = std::max(own_us, live * std::max(weights_kb / groups / 6.0e3, (weights_kb + acts_kb) / 15e3));
+            const bool fused = fusable && sp == 1 && nt == 2;
+            const double partial_mb = (double)sp * mt_total * 32 * N * 4e-6;
+            const double t = ((base * sp + 255) / 256) * (cps * chunk_us + 6.0) + (fused ? 3.0 : 0.34 * partial_mb + (fusable ? 8.0 : 0.0));
+            if (t < best_t) { best_t = t; best.nt = nt; best.split_k = sp; best.chunks_per_split = cps; }
+        }
+    }
+    return best;
+}
+
+// Plan of a wide-format GEMM.
+//
+// Up to 64 rows: tiles 128 columns wide wherever one round holds them: activations are then little of what a CU
+// fetches, and few k splits are written and read back (12288 x 4096 at 32 rows, two splits against five of 256 columns: 19.9
+// against 21.4 us and a shorter consumer; 24576 x 4096 33.8, unsplit, against 35.9).  Else 192 (three waves) if that is one
+// round: 198 of the CUs have work instead of 148 (37888 x 3584, 56 rows, with SwiGLU: 50.1 against 57.5 us; at 120 rows, where
+// the waves' own work sets the pace, 74.2 against 68.2).
+//
+// 65 to 256 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 and 240 rows:
+// time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of everything the L2s
+// deliver, 15 TB/s), 6 us of prologue and store per tile, and the partial tiles, written here and read by the consumer.
+// (12288 x 4096 at 120 rows: four splits on 192 CUs 27.6 us, five on 240 27.5 and a longer consumer; 4096 x 4096 at 240 rows:
+// 128 columns in four splits 19.4 us, 256 in eight 21.2 and twice the partial tiles; 37888 x 3584 at 240 rows: one round of
+// 384 columns 117 us and a SwiGLU launch, two rounds with SwiGLU in the epilogue 147.)
+//
+// With more rows (gemm_many_kernel) the candidates (128 or 192 rows per
 // workgroup, k split) are priced by a model fitted to 800 measured launches (272..4206 rows, N 3584..37888, K
 // 3584..18944; 4.6 % rms): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
 // workgroups except that a last round which leaves CUs idle runs at a higher clock (the chip is at its power limit), and
@@ -329,8 +363,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const u32x4* __restri
 // can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
-    if (mt_total <= 2 && forced_nt <= 0 && (N / 32 + 3) / 4 <= 256) forced_nt = 1;
-    if (mt_total <= 8 || forced_split > 0) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
+    if (forced_split > 0 || (mt_total <= 8 && forced_nt > 0)) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
+    if (mt_total <= 2) {
+        GemmPlan p = gemm_plan(m_rows, N, K, 0, (N / 32 + 3) / 4 <= 256 ? 1 : 0);
+        if (p.nt == 2 && p.split_k == 1 && (N / 32 + 5) / 6 <= 256) p.wv = 3;
+        return p;
+    }
+    if (mt_total <= 8) return plan_block_step(mt_total, N, K, fusable);
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
     best.nt = 2;
@@ -359,19 +398,22 @@ void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, fl
     // row groups of at most four m-tiles, dealt evenly, each computed by the body for that number
     const int m_groups = (mt_total + 3) / 4, mt = nt == 3 ? 4 : (mt_total + m_groups - 1) / m_groups;
     const size_t split_stride = (size_t)mt_total * 32 * N;
-    const int tiles_x = (n_tiles + 4 * nt - 1) / (4 * nt);
+    const int tiles_x = (n_tiles + plan.wv * nt - 1) / (plan.wv * nt);
     dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);
 #define WARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, tiles_x, m_groups, swiglu_out, ssq, nblk, 1.0f / (float)K, rms_eps
-#define WLAUNCH(NT_, EPI_, ST_, MT_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, MT_>), grid, dim3(256), 0, s, st.start, st.stop, 0, WARGS)
+#define WLAUNCH(NT_, EPI_, ST_, MT_, WV_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, MT_, WV_>), grid, dim3(64 * WV_), 0, s, st.start, st.stop, 0, WARGS)
 #define WLAUNCH_MT(NT_, EPI_) do { \
-        if (m_groups > 1) { if (mt == 3) WLAUNCH(NT_, EPI_, false, 3); else WLAUNCH(NT_, EPI_, false, 4); } \
-        else if (mt == 1) WLAUNCH(NT_, EPI_, true, 1); \
-        else if (mt == 2) WLAUNCH(NT_, EPI_, true, 2); \
-        else if (mt == 3) WLAUNCH(NT_, EPI_, true, 3); \
-        else WLAUNCH(NT_, EPI_, true, 4); \
+        if (m_groups > 1) { if (mt == 3) WLAUNCH(NT_, EPI_, false, 3, 4); else WLAUNCH(NT_, EPI_, false, 4, 4); } \
+        else if (mt == 1) WLAUNCH(NT_, EPI_, true, 1, 4); \
+        else if (mt == 2) WLAUNCH(NT_, EPI_, true, 2, 4); \
+        else if (mt == 3) WLAUNCH(NT_, EPI_, true, 3, 4); \
+        else WLAUNCH(NT_, EPI_, true, 4, 4); \
     } while (0)
-    if (swiglu_out) WLAUNCH_MT(2, WEPI_SWIGLU);
-    else if (nt == 3) { if (m_groups > 1) WLAUNCH(3, WEPI_PARTIAL, false, 4); else WLAUNCH(3, WEPI_PARTIAL, true, 4); }
+    if (plan.wv == 3) {
+        if (swiglu_out) { if (mt == 1) WLAUNCH(2, WEPI_SWIGLU, true, 1, 3); else WLAUNCH(2, WEPI_SWIGLU, true, 2, 3); }
+        else { if (mt == 1) WLAUNCH(2, WEPI_PARTIAL, true, 1, 3); else WLAUNCH(2, WEPI_PARTIAL, true, 2, 3); }
+    } else if (swiglu_out) WLAUNCH_MT(2, WEPI_SWIGLU);
+    else if (nt == 3) { if (m_groups > 1) WLAUNCH(3, WEPI_PARTIAL, false, 4, 4); else WLAUNCH(3, WEPI_PARTIAL, true, 4, 4); }
     else if (nt == 2) WLAUNCH_MT(2, WEPI_PARTIAL);
     else WLAUNCH_MT(1, WEPI_PARTIAL);
 #undef WLAUNCH_MT
