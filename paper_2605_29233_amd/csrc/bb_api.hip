@@ -495,8 +495,6 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
         return fused ? 0 : p.split_k;
     };
     c->prof_chain = false;              // the first launch records its own start
-    { PROF(BB_K_GLUE, 0, 0); launch_embed(D, c->emb, c->h, rows_cap, s); }
-    c->prof_chain = true;
     int s_down = 0;
     const size_t pstride = (size_t)rows_pad * d;
     for (int li = 0; li < m.n_layers; ++li) {
@@ -505,8 +503,10 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
         const float* ssq = defer ? c->ssq : nullptr;
         int nblk = 0;
         { PROF(BB_K_GLUE, 0, 0);
-          if (defer) nblk = launch_residual_pack(D, c->h, c->part, s_down, pstride, W.g_attn, c->Apk, mt, c->ssq, wide, s);
-          else launch_rmsnorm_pack(D, c->h, c->part, s_down, pstride, W.g_attn, c->Apk, mt, 0, 0, wide, s); }
+          const uint16_t* emb = li == 0 ? c->emb : nullptr;
+          if (defer) nblk = launch_residual_pack(D, c->h, c->part, s_down, pstride, W.g_attn, c->Apk, mt, c->ssq, wide, s, emb);
+          else launch_rmsnorm_pack(D, c->h, c->part, s_down, pstride, W.g_attn, c->Apk, mt, 0, 0, wide, s, emb); }
+        c->prof_chain = true;
         const int s_qkv = gemm(3, W.wqkv, W.wqkv_w, W.s_qkv, c->Apk, c->qkv, nqkv, d, rows_cap, mt, gk);
         { PROF(BB_K_GLUE, 0, 0);
           launch_qkv_epilogue(D, c->qkv, s_qkv, (size_t)rows_pad * nqkv, m.qkv_bias ? W.bqkv : nullptr, c->Q, li, rows_cap, ssq, nblk, s); }

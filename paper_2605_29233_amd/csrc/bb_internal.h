@@ -256,15 +256,17 @@ void launch_tile_weights_wide(const uint16_t* src, int rows, int K, u32x4* dst, 
                               hipStream_t s);
 void launch_pack_rows_wide(const float* A, int M, int K, u32x4* Apk, int mt_total, hipStream_t s);
 
-void launch_embed(const Dev& D, const uint16_t* emb, float* h, int rows_cap, hipStream_t s);
 // Panels a kernel writes are two bf16 terms, or the wide format when its `wide` argument is set.
+// emb (before the first layer): h = the embedding rows of the packed tokens instead of what h holds.
 // h += sum of split-K partials; out = packed rmsnorm(h) * gain.  gather != 0: rows are the masked (LM-head) rows.
 void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_partial, size_t partial_stride,
-                         const float* gain, u32x4* Apk, int mt_total, int gather, int bcast, int wide, hipStream_t s);
+                         const float* gain, u32x4* Apk, int mt_total, int gather, int bcast, int wide, hipStream_t s,
+                         const uint16_t* emb = nullptr);
 // Few rows: h += sum of split-K partials; out = packed h * gain WITHOUT the norm's 1 / rms, whose
 // ingredients go to ssq[row][block] (returns the blocks per row); the consumers below apply it after the projection.
 int launch_residual_pack(const Dev& D, float* h, const float* partial, int n_partial, size_t partial_stride,
-                         const float* gain, u32x4* Apk, int mt_total, float* ssq, int wide, hipStream_t s);
+                         const float* gain, u32x4* Apk, int mt_total, float* ssq, int wide, hipStream_t s,
+                         const uint16_t* emb = nullptr);
 // q,k,v = sum of partials (* 1 / rms of the row if ssq) + bias; RoPE; q -> Q, k,v -> cache rows (two fp16 terms each)
 void launch_qkv_epilogue(const Dev& D, const float* qkv, int n_partial, size_t partial_stride, const float* bias,
                          half_t* Q, int layer, int rows_cap, const float* ssq, int nblk, hipStream_t s);

@@ -1,4 +1,4 @@
-// Memory-bound glue kernels of the forward: embedding gather, the consumers of the GEMMs'
+// Memory-bound glue kernels of the forward: the consumers of the GEMMs'
 // split-K partial results (residual add + RMSNorm + packing into MFMA fragments, bias + RoPE +
 // KV-cache write, SwiGLU), and the second half of the vocabulary reduction.
 #include "bb_internal.h"
@@ -26,20 +26,18 @@ static __device__ __forceinline__ void zero_packed_row(u32x4* Apk, int m, int k8
     for (int k8 = threadIdx.x; k8 < k8s; k8 += blockDim.x) zero_panel8(Apk, m, k8, mt_total, wide);
 }
 
-// h0 = E[x]: one workgroup per packed row.
-__global__ void embed_kernel(Dev D, const uint16_t* __restrict__ emb, float* __restrict__ h) {
-    int row = blockIdx.x;
-    float* dst = h + (size_t)row * D.d;
-    if (row >= D.counts[0]) {
-        for (int k = threadIdx.x; k < D.d; k += blockDim.x) dst[k] = 0.f;
-        return;
+// Eight columns of a row of the residual stream: from h, or, before the first layer (emb given), the token's embedding.  (The
+// gather is part of the first norm / residual kernel: a launch of its own took 8.8 us for 120 rows of 4096, 2.6 us for 56 of 256.)
+static __device__ __forceinline__ void load_stream8(const Dev& D, const float* __restrict__ hr, const uint16_t* __restrict__ emb, int row, int k8,
+                                                    float4& a, float4& b) {
+    if (emb) {
+        const u32x4 e = *reinterpret_cast<const u32x4*>(emb + (size_t)D.row_tok[row] * D.d + k8 * 8);
+        a = make_float4(bf16_to_f32((uint16_t)e[0]), bf16_to_f32((uint16_t)(e[0] >> 16)), bf16_to_f32((uint16_t)e[1]), bf16_to_f32((uint16_t)(e[1] >> 16)));
+        b = make_float4(bf16_to_f32((uint16_t)e[2]), bf16_to_f32((uint16_t)(e[2] >> 16)), bf16_to_f32((uint16_t)e[3]), bf16_to_f32((uint16_t)(e[3] >> 16)));
+    } else {
+        a = reinterpret_cast<const float4*>(hr)[2 * k8];
+        b = reinterpret_cast<const float4*>(hr)[2 * k8 + 1];
     }
-    const uint16_t* src = emb + (size_t)D.row_tok[row] * D.d;
-    for (int k = threadIdx.x; k < D.d; k += blockDim.x) dst[k] = bf16_to_f32(src[k]);
-}
-
-void launch_embed(const Dev& D, const uint16_t* emb, float* h, int rows_cap, hipStream_t s) {
-    embed_kernel<<<rows_cap, 256, 0, s>>>(D, emb, h);
 }
 
 // Sum of split-K partial results in split order, for N offsets at once: the loads of a batch (4 splits x N
@@ -73,7 +71,8 @@ static __device__ __forceinline__ void part_sum4n(const float* __restrict__ P, i
 __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restrict__ h, const float* __restrict__ partial,
                                                            int n_partial, size_t partial_stride,
                                                            const float* __restrict__ gain, u32x4* __restrict__ Apk,
-                                                           int mt_total, int gather, int bcast, int wide) {
+                                                           int mt_total, int gather, int bcast, int wide,
+                                                           const uint16_t* __restrict__ emb) {
     __shared__ float sh[4];
     const int j = xcd_run_item(blockIdx.x, gridDim.x), d = D.d, k8s = d >> 3;
     const int count = gather ? D.counts[1] : D.counts[0];
@@ -88,7 +87,8 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
     for (int i = 0; i < MAXG; ++i) {
         const int k8 = threadIdx.x + 256 * i;
         if (k8 < k8s) {
-            const float4 a = reinterpret_cast<const float4*>(hr)[2 * k8], b = reinterpret_cast<const float4*>(hr)[2 * k8 + 1];
+            float4 a, b;
+            load_stream8(D, hr, emb, r, k8, a, b);
             float4 p[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
             if (n_partial) {
                 const size_t off[2] = {(size_t)r * d + k8 * 8, (size_t)r * d + k8 * 8 + 4};
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
             }
             v[i][0] = a.x + p[0].x; v[i][1] = a.y + p[0].y; v[i][2] = a.z + p[0].z; v[i][3] = a.w + p[0].w;
             v[i][4] = b.x + p[1].x; v[i][5] = b.y + p[1].y; v[i][6] = b.z + p[1].z; v[i][7] = b.w + p[1].w;
-            if (n_partial) {
+            if (n_partial || emb) {
                 reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
                 reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
             }
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
 __global__ __launch_bounds__(256) void rmsnorm_pack8_kernel(Dev D, float* __restrict__ h, const float* __restrict__ partial,
                                                             int n_partial, size_t partial_stride,
                                                             const float* __restrict__ gain, u32x4* __restrict__ Apk, int mt_total,
-                                                            int wide) {
+                                                            int wide, const uint16_t* __restrict__ emb) {
     constexpr int R = 8, G = 2;
     __shared__ float sh[4][R];
     const int j0 = blockIdx.x * R, d = D.d, k8s = d >> 3, count = D.counts[0], t = threadIdx.x;
@@ -155,7 +155,8 @@ __global__ __launch_bounds__(256) void rmsnorm_pack8_kernel(Dev D, float* __rest
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[r][i][q] = 0.f;
             if (j < count && k8 < k8s) {
-                const float4 a = reinterpret_cast<const float4*>(hr)[2 * k8], b = reinterpret_cast<const float4*>(hr)[2 * k8 + 1];
+                float4 a, b;
+                load_stream8(D, hr, emb, j, k8, a, b);
                 float4 p[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
                 if (n_partial) {
                     const size_t off[2] = {(size_t)j * d + k8 * 8, (size_t)j * d + k8 * 8 + 4};
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(256) void rmsnorm_pack8_kernel(Dev D, float* __rest
                 }
                 v[r][i][0] = a.x + p[0].x; v[r][i][1] = a.y + p[0].y; v[r][i][2] = a.z + p[0].z; v[r][i][3] = a.w + p[0].w;
                 v[r][i][4] = b.x + p[1].x; v[r][i][5] = b.y + p[1].y; v[r][i][6] = b.z + p[1].z; v[r][i][7] = b.w + p[1].w;
-                if (n_partial) {
+                if (n_partial || emb) {
                     reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[r][i][0], v[r][i][1], v[r][i][2], v[r][i][3]);
                     reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[r][i][4], v[r][i][5], v[r][i][6], v[r][i][7]);
                 }
@@ -214,13 +215,14 @@ __global__ __launch_bounds__(256) void rmsnorm_pack8_kernel(Dev D, float* __rest
 }
 
 void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_partial, size_t partial_stride,
-                         const float* gain, u32x4* Apk, int mt_total, int gather, int bcast, int wide, hipStream_t s) {
+                         const float* gain, u32x4* Apk, int mt_total, int gather, int bcast, int wide, hipStream_t s,
+                         const uint16_t* emb) {
     // eight rows per workgroup once that still gives every CU a workgroup, or when a row is too short to occupy
     // one (d <= 512: at most 64 of the 256 threads have a column group)
     if (!gather && D.d <= 4096 && mt_total * 32 > 256 && (mt_total * 4 >= 256 || D.d <= 512))
-        rmsnorm_pack8_kernel<<<mt_total * 4, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, wide);
+        rmsnorm_pack8_kernel<<<mt_total * 4, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, wide, emb);
     else
-        rmsnorm_pack_kernel<<<mt_total * 32, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide);
+        rmsnorm_pack_kernel<<<mt_total * 32, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
 }
 
 // Few rows (block steps): the norm's row-wide sum would leave one workgroup per row with the whole row's partial tiles
@@ -233,7 +235,8 @@ void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_par
 __global__ __launch_bounds__(256) void residual_pack_kernel(Dev D, float* __restrict__ h, const float* __restrict__ partial,
                                                             int n_partial, size_t partial_stride,
                                                             const float* __restrict__ gain, u32x4* __restrict__ Apk,
-                                                            int mt_total, float* __restrict__ ssq, int nblk, int wide) {
+                                                            int mt_total, float* __restrict__ ssq, int nblk, int wide,
+                                                            const uint16_t* __restrict__ emb) {
     __shared__ float sh[4];
     const int item = xcd_run_item(blockIdx.x, gridDim.x), unit = item >> 3;         // eight rows of one column block in a row
     const int j = unit / nblk * 8 + (item & 7), b = unit % nblk, d = D.d, k8 = b * (BB_SSQ_BLOCK / 8) + threadIdx.x;
@@ -246,14 +249,15 @@ __global__ __launch_bounds__(256) void residual_pack_kernel(Dev D, float* __rest
     float ss = 0.f;
     if (live) {
         float* hr = h + (size_t)j * d;
-        const float4 a = reinterpret_cast<const float4*>(hr)[2 * k8], c = reinterpret_cast<const float4*>(hr)[2 * k8 + 1];
+        float4 a, c;
+        load_stream8(D, hr, emb, j, k8, a, c);
         float4 p[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
         if (n_partial) {
             const size_t off[2] = {(size_t)j * d + k8 * 8, (size_t)j * d + k8 * 8 + 4};
             part_sum4n<2>(partial, n_partial, partial_stride, off, p);
         }
         const float v[8] = {a.x + p[0].x, a.y + p[0].y, a.z + p[0].z, a.w + p[0].w, c.x + p[1].x, c.y + p[1].y, c.z + p[1].z, c.w + p[1].w};
-        if (n_partial) {
+        if (n_partial || emb) {
             reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[0], v[1], v[2], v[3]);
             reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[4], v[5], v[6], v[7]);
         }
@@ -269,9 +273,10 @@ __global__ __launch_bounds__(256) void residual_pack_kernel(Dev D, float* __rest
 }
 
 int launch_residual_pack(const Dev& D, float* h, const float* partial, int n_partial, size_t partial_stride,
-                         const float* gain, u32x4* Apk, int mt_total, float* ssq, int wide, hipStream_t s) {
+                         const float* gain, u32x4* Apk, int mt_total, float* ssq, int wide, hipStream_t s,
+                         const uint16_t* emb) {
     const int nblk = (D.d + BB_SSQ_BLOCK - 1) / BB_SSQ_BLOCK;
-    residual_pack_kernel<<<mt_total * 32 * nblk, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, ssq, nblk, wide);
+    residual_pack_kernel<<<mt_total * 32 * nblk, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, ssq, nblk, wide, emb);
     return nblk;
 }
 
