@@ -524,7 +524,8 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
     if (mode != 2) {
         const int mt_lm = (lm_cap + 31) / 32;
         { PROF(BB_K_GLUE, 0, 0);
-          launch_rmsnorm_pack(D, c->h, c->part, s_down, pstride, c->g_final, c->Apk, mt_lm, 1, mode == 1, 0, s); }
+          launch_rmsnorm_pack(D, c->h, c->part, s_down, pstride, c->g_final, c->Apk, mt_lm, 1, mode == 1, 0, s,
+                              m.n_layers == 0 ? c->emb : nullptr); }      // (no layer has brought the embeddings in)
         {   // LM head with the vocabulary reduction in its epilogue: no k split, 256-column tiles (128 for tiny vocabularies)
             GemmPlan p = gemm_plan(lm_cap, m.vocab, d, 1, m.vocab / 32 >= 8 ? 2 : 1);
             GemmEpilogue epi; epi.vocab_part = D.vr_part; epi.mask_id = m.mask_id; epi.keep_logits = c->keep_logits; epi.rows_live = D.counts + 1;

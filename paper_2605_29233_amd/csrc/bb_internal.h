@@ -257,7 +257,7 @@ void launch_tile_weights_wide(const uint16_t* src, int rows, int K, u32x4* dst, 
 void launch_pack_rows_wide(const float* A, int M, int K, u32x4* Apk, int mt_total, hipStream_t s);
 
 // Panels a kernel writes are two bf16 terms, or the wide format when its `wide` argument is set.
-// emb (before the first layer): h = the embedding rows of the packed tokens instead of what h holds.
+// emb (the first norm of a forward): h = the embedding rows of the packed tokens instead of what h holds.
 // h += sum of split-K partials; out = packed rmsnorm(h) * gain.  gather != 0: rows are the masked (LM-head) rows.
 void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_partial, size_t partial_stride,
                          const float* gain, u32x4* Apk, int mt_total, int gather, int bcast, int wide, hipStream_t s,

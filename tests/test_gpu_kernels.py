@@ -279,3 +279,37 @@ def test_lm_head_row_groups(n):
     ref = x.max(1) + np.log(np.exp(x - x.max(1, keepdims=True)).sum(1))
     assert np.abs(lse - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
     assert np.abs(conf * np.exp(ref - x.max(1)) - 1).max() <= 2e-5
+
+
+def test_a_model_without_layers_sees_its_embeddings():
+    """No layer: the final norm and the LM head work on the token embeddings, in the initial forward and in a block step
+    after tokens were committed.  Logits against the same in fp64."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("nolayer", 0, 256, 4, 4, 64, 688, 1024)
+    decode = DecodeParams(0.9, 0.5, 4, 8)
+    weights = dict(gen_weights(shape, 17))
+    print("model without layers", flush=True)
+    b = BlockBatch(shape, decode, Limits(1, 2, 84, 64, 40), poison_workspace=True)
+    try:
+        b.load_weights(weights.items())
+        b.keep_logits(True)
+        rid = b.request_open(gen_prompt(shape, 17, 0, 20), 64, (8, 32))
+        b.refresh([rid], BB_INIT)
+        init = b.latest_view().logits()
+        b.merge_commit([rid])
+        X = b.get_tokens(rid)
+        v = b.denoise_step([rid])
+        gbr, pos = (a[v.lm_rows()] for a in v.rows())
+        step = v.logits()
+    finally:
+        b.close()
+    E, g, W = (weights[n].double().numpy() for n in ("tok_emb", "final_norm", "lm_head"))
+
+    def logits(tokens):
+        h = E[tokens]
+        return h / np.sqrt((h * h).mean(1, keepdims=True) + shape.rms_eps) * g.reshape(-1) @ W.T
+
+    for got, tokens in ((init, np.full(64, shape.mask_id)), (step, X[gbr, pos])):
+        want = logits(tokens)
+        assert got.shape == want.shape and np.abs(got - want)[:, :-1].max() <= 3e-2
