@@ -273,8 +273,9 @@ int bb_debug_set_gemm_plan(bb_ctx* ctx, int kind, int nt, int split_k);
 
 /* Host-only query (no device is touched): the launch plan the library takes for C[M][N] = A[M][K] W[N][K]^T with
  * the heuristics on (wide != 0: the fp16 + fp8 operand kernel; fusable != 0: the caller could take SiLU(gate) * up
- * from the epilogue).  out[0] = k splits, out[1] = 64-k chunks per split, out[2] = weight tiles of 32 rows per wave
- * (workgroup tile = 128 out[2] columns), out[3] = m-tiles of 32 rows per workgroup, out[4] = workgroups launched.
+ * from the epilogue).  out[0] = k splits, out[1] = 64-k chunks per split, out[2] = weight tiles of 32 rows per wave,
+ * out[3] = m-tiles of 32 rows per workgroup, out[4] = workgroups launched.  A workgroup's tile has 128 out[2] columns, except
+ * that with wide != 0, M <= 64, out[2] == 2 and N <= 49152 it has 192 (three waves instead of four).
  * Returns BB_EINVAL for M < 1, N < 32, K < 16, N % 32, K % 16 or out == NULL. */
 int bb_debug_gemm_plan(int M, int N, int K, int wide, int fusable, int out[5]);
 

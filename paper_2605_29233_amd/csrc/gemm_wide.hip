@@ -317,8 +317,15 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     }
 }
 
+// Up to 256 rows: row groups of at most four m-tiles, dealt evenly, each computed by the body for that number (384-column tiles
+// have the body of four only).
+static int block_step_body(int mt_total, int nt) {
+    const int groups = (mt_total + 3) / 4;
+    return nt == 3 ? 4 : (mt_total + groups - 1) / groups;
+}
+
 static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
-    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, groups = (mt_total + 3) / 4, body = (mt_total + groups - 1) / groups;
+    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, groups = (mt_total + 3) / 4, body = block_step_body(mt_total, 1);
     GemmPlan best;
     double best_t = 1e30;
     for (int nt = 1; nt <= (groups > 1 ? 3 : 2); ++nt) {
@@ -363,13 +370,17 @@ static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
 // can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
-    if (forced_split > 0 || (mt_total <= 8 && forced_nt > 0)) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
-    if (mt_total <= 2) {
-        GemmPlan p = gemm_plan(m_rows, N, K, 0, (N / 32 + 3) / 4 <= 256 ? 1 : 0);
-        if (p.nt == 2 && p.split_k == 1 && (N / 32 + 5) / 6 <= 256) p.wv = 3;
+    if (mt_total <= 8) {
+        GemmPlan p;
+        if (forced_split > 0 || forced_nt > 0) p = gemm_plan(m_rows, N, K, forced_split, forced_nt);
+        else if (mt_total <= 2) {
+            p = gemm_plan(m_rows, N, K, 0, (N / 32 + 3) / 4 <= 256 ? 1 : 0);
+            if (p.nt == 2 && p.split_k == 1 && (N / 32 + 5) / 6 <= 256) p.wv = 3;
+        } else p = plan_block_step(mt_total, N, K, fusable);
+        p.mt = block_step_body(mt_total, p.nt);
         return p;
     }
-    if (mt_total <= 8) return plan_block_step(mt_total, N, K, fusable);
+    if (forced_split > 0) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
     best.nt = 2;
@@ -395,8 +406,7 @@ void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, fl
                       const int* rows_live) {
     if (mt_total > 8) { launch_gemm_many(Wt, wscale, Apk, P, mt_total, N, K, plan, s, rows_live, swiglu_out, st); return; }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64, nt = plan.nt;
-    // row groups of at most four m-tiles, dealt evenly, each computed by the body for that number
-    const int m_groups = (mt_total + 3) / 4, mt = nt == 3 ? 4 : (mt_total + m_groups - 1) / m_groups;
+    const int m_groups = (mt_total + 3) / 4, mt = block_step_body(mt_total, nt);
     const size_t split_stride = (size_t)mt_total * 32 * N;
     const int tiles_x = (n_tiles + plan.wv * nt - 1) / (plan.wv * nt);
     dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);

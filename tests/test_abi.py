@@ -94,21 +94,31 @@ def test_static_gemm_rejects_bad_sizes_before_touching_a_device(lib):
 def test_gemm_plans_cover_k_fit_the_chip_and_the_register_file(lib):
     """Host logic of the launch plans (no device): for every shape the k splits cover all 64-k chunks without an
     empty split, a workgroup holds at most 12 accumulator tiles (the AGPR budget of the wide kernel), the fused
-    SwiGLU candidate keeps two tiles per wave, a single row group keeps the 128-row tile, and no plan launches more
-    than one workgroup per CU and k split."""
-    shapes = [(n, k) for n in (512, 4096, 4608, 12288, 24576, 37888) for k in (512, 3584, 4096, 12288, 18944)]
+    SwiGLU candidate keeps two tiles per wave, and the tile the query states (rows and columns of a workgroup, as the
+    header describes it) gives the number of workgroups it states, at most one per CU and k split."""
+    shapes = [(n, k) for n in (512, 4096, 4608, 12288, 24576, 37888, 49152, 49184) for k in (512, 3584, 4096, 12288, 18944)]
     for wide in (False, True):
-        for M in (1, 32, 120, 128, 129, 252, 256, 257, 300, 768, 1920, 3072, 4608, 20480):
+        for M in (1, 32, 56, 64, 65, 120, 128, 129, 160, 192, 252, 256, 257, 300, 768, 1920, 3072, 4608, 20480):
             for N, K in shapes:
                 for fusable in (False, True):
                     p = binding.gemm_plan(M, N, K, wide, fusable)
                     chunks = (K + 63) // 64
-                    assert 1 <= p["split_k"] <= 16 and p["nt"] in (1, 2, 3) and p["mt"] in (4, 6), (M, N, K, p)
+                    assert 1 <= p["split_k"] <= 16 and p["nt"] in (1, 2, 3), (M, N, K, p)
                     assert p["split_k"] * p["chunks_per_split"] >= chunks > (p["split_k"] - 1) * p["chunks_per_split"], (M, N, K, p)
                     assert p["nt"] * p["mt"] <= 12, (M, N, K, p)
-                    assert p["workgroups"] <= 256 * p["split_k"], (M, N, K, p)
-                    if not wide or M <= 256:
+                    m_tiles, columns = (M + 31) // 32, 128 * p["nt"]
+                    if not wide:
                         assert p["mt"] == 4, (M, N, K, p)
+                    elif M > 256:
+                        assert p["mt"] in (4, 6) and p["nt"] == 2, (M, N, K, p)
+                    else:           # a body per number of m-tiles, two groups of them above 128 rows; 384 columns: the body of four
+                        groups = (m_tiles + 3) // 4
+                        assert p["mt"] == (4 if p["nt"] == 3 else (m_tiles + groups - 1) // groups), (M, N, K, p)
+                        if M <= 64 and p["nt"] == 2 and N <= 49152:
+                            columns = 192
+                    tiles = -(-N // columns) * -(-m_tiles // p["mt"])
+                    want = min(tiles * p["split_k"], 256) if wide and M > 256 else min(tiles, 256) * p["split_k"]
+                    assert p["workgroups"] == want, (M, N, K, p, want)
     # the shapes the fused SwiGLU epilogue is used on: gate/up of the refresh and of the 16-request step
     for M in (768, 1920, 3072):
         p = binding.gemm_plan(M, 24576, 4096, True, True)
