@@ -21,6 +21,7 @@
 //                                                    accumulators (same lane owns the same
 //                                                    query), keys permuted consistently.
 #include "bb_internal.h"
+#include "lds.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -248,13 +249,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attention_kernel(Dev D, const h
     }
 }
 
-// One 1 KiB fragment (64 lanes x 16 bytes) from src to the LDS byte offset dst without passing through registers; OFF is
-// added on both sides.  Written as assembly because the compiler, where it knows of such loads, lets every LDS read wait for
-// all outstanding ones: the waits are the explicit ones at the barriers.
-template <int OFF> static __device__ __forceinline__ void load_to_lds(const char* src, unsigned lane16, unsigned dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(dst), "v"(lane16), "s"(src), "n"(OFF) : "memory");
-}
-
 // Many query rows per segment (full-sequence passes): four waves, 32 query rows each, walk the row's pages together.
 // What bounds it: the matrix pipes (96 MFMAs per wave and page at HD = 128, 3072 cycles), beside some 1600 cycles of
 // exponentials and conversions and, per CU, the 64 KB of a page.  So a page is fetched once per workgroup into LDS, by
@@ -281,7 +275,7 @@ __global__ __launch_bounds__(256, 2) void attention_full_kernel(Dev D, const hal
     const int tile_base = wg_base + 32 * wave;      // (waves past the end repeat the last row, take part in the loads and store nothing)
     const int kvh = blockIdx.x, seg_off = D.seg_off[gbr];
     const int L = D.hdr[gbr / D.max_br].L, n_pages = (L + BB_PAGE - 1) / BB_PAGE;
-    const unsigned lane16 = lane * 16, lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)lds;
+    const unsigned lane16 = lane * 16, lds0 = lds_offset(lds);
     // this wave's quarter of a page: KS fragments in a row
     auto request = [&](const half_t* cache, int phys, int page, int buf) {
         const char* src = reinterpret_cast<const char*>(cache + kv_block_off(D, layer, phys, page, kvh)) + wave * (KS * 1024);

@@ -13,6 +13,7 @@
 // 775 -> 700 us, down (4096 x 12288) 370 -> 332 us, 1.33 PFLOP/s in bf16 equivalents; 20480 rows of gate/up 5.13 -> 4.61 ms;
 // 4206 rows, 3584 x 18944: 861 -> 665 us.  The matrix pipes are busy 0.81 of the cycles at 1.71 GHz (0.66 at 1.74).
 #include "bb_internal.h"
+#include "lds.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <type_traits>
@@ -23,20 +24,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 static __device__ __forceinline__ f16x8 as_f16x8(const u32x4& v) { return __builtin_bit_cast(f16x8, v); }
 
-// One 1 KiB fragment (64 lanes x 16 bytes) from src to the LDS byte offset dst without passing through registers; OFF is
-// added on both sides.  Written as assembly because the compiler, where it knows of such loads, lets every LDS read
-// wait for all outstanding ones: the waits for these loads are the explicit ones at the barriers.
-template <int OFF> static __device__ __forceinline__ void load_to_lds(const char* src, unsigned lane16, unsigned dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(dst), "v"(lane16), "s"(src), "n"(OFF));
-}
-// The same by the first N waves only (a branch inside the assembly: one in the loop body would split the pipeline's block).
-template <int N> static __device__ __forceinline__ void load_to_lds_first(int wave, const char* src, unsigned lane16, unsigned dst) {
-    asm volatile("s_cmp_ge_u32 %3, %4\n\ts_cbranch_scc1 1f\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n1:"
-                 ::"s"(dst), "v"(lane16), "s"(src), "s"(wave), "n"(N) : "scc");
-}
-static __device__ __forceinline__ unsigned lds_offset(const void* p) {
-    return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
-}
 template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
 }
