@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256, 2) void attention_full_kernel(Dev D, const hal
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) so[c * LDO + 32 * dt + 8 * (r >> 2) + 4 * g + (r & 3)] = o[2 * half + dt][r] * inv;
-        // (the same wave wrote and reads: no barrier needed, the LDS counter orders them)
+        wave_lds_order();                                   // (the same wave wrote and reads: no barrier needed)
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int d8 = 2 * it + g;
@@ -378,6 +378,7 @@ __global__ __launch_bounds__(256, 2) void attention_full_kernel(Dev D, const hal
             for (int e = 0; e < 8; ++e) y[e] = so[c * LDO + d8 * 8 + e];
             if (f < nflat) store_panel8(Apk, m, ((kvh * group + hig) * HD + 64 * half) / 8 + d8, mt_total, y, wide);
         }
+        wave_lds_order();                                   // (the next half overwrites the slice)
     }
 }
 

@@ -10,6 +10,7 @@
 // is split over several workgroups to occupy every CU; each writes its partial tile and the
 // consumer kernel (residual + norm, SwiGLU, bias + RoPE + cache write) sums them in split order.
 #include "bb_internal.h"
+#include "lds.h"
 #include "sched.h"
 #include <hip/hip_ext.h>
 #include <type_traits>
@@ -296,7 +297,7 @@ static __device__ __forceinline__ void gemm_tile(const GemmArgs& g, u32x4* lds_r
                     *reinterpret_cast<float4*>(&tl[(mh * 32 + (lane & 31)) * LDT + t * 32 + 8 * q + 4 * (lane >> 5)]) =
                         make_float4(a4[4 * q], a4[4 * q + 1], a4[4 * q + 2], a4[4 * q + 3]);
                 }
-        // (same wave wrote and reads: no barrier needed, the LDS counter orders them)
+        wave_lds_order();                                   // (the same wave wrote and reads: no barrier needed)
         constexpr int LPR = COLS / 4;                       // lanes per row
         const int rows_valid = min(32 * MPP, (mt_cnt - MPP * pass) * 32);
 #pragma unroll
@@ -307,6 +308,7 @@ static __device__ __forceinline__ void gemm_tile(const GemmArgs& g, u32x4* lds_r
             if (r < rows_valid && n < n_tiles * 32)
                 *reinterpret_cast<float4*>(&Ps[(size_t)((mt0 + MPP * pass) * 32 + r) * ldp + n]) = v;
         }
+        wave_lds_order();                                   // (the next pass overwrites the slice)
     }
     __syncthreads();                                        // the next tile's prologue overwrites the LDS slices
 }

@@ -259,13 +259,14 @@ __global__ __launch_bounds__(512, 2) void gemm_many_kernel(const u32x4* __restri
             for (int s = 0; s < 2; ++s)
                 *reinterpret_cast<float4*>(&tl[(s * 16 + c16) * LDT + t * 16 + 4 * g]) =
                     make_float4(acc[t][2 * mt + s][0], acc[t][2 * mt + s][1], acc[t][2 * mt + s][2], acc[t][2 * mt + s][3]);
-        // (the same wave wrote and reads: no barrier needed, the LDS counter orders them)
+        wave_lds_order();                                   // (the same wave wrote and reads: no barrier needed)
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
             const int r = it * 4 + g, c4 = c16 * 4;
             const float4 v = *reinterpret_cast<const float4*>(&tl[r * LDT + c4]);
             if (x0 * 32 + c4 < n_tiles * 32) *reinterpret_cast<float4*>(&Ps[(size_t)((mtw0 + mt) * 32 + r) * ldp + x0 * 32 + c4]) = v;
         }
+        wave_lds_order();                                   // (the next m-tile overwrites the slice)
     }
     __syncthreads();                                        // the next tile's loads overwrite the LDS slices
     }

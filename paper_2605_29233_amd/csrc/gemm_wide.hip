@@ -16,6 +16,7 @@
 // 32 rows: 12288 x 4096 26.7 -> 19.9, 24576 x 4096 45.0 -> 33.8, 4096 x 12288 27.6 -> 18.7 (5.4 TB/s; reading the weights
 // alone takes 17.6); of 2 at 56 rows: 27.5 -> 22.0, 45.5 -> 39.4, 27.6 -> 20.7; of 3 at 96 rows: 29.2 -> 24.0, 43.4 -> 41.6.
 #include "bb_internal.h"
+#include "lds.h"
 #include "sched.h"
 #include <hip/hip_ext.h>
 #include <type_traits>
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
                     *reinterpret_cast<float4*>(&tl[(mh * 32 + (lane & 31)) * LDT + t * 32 + 8 * q + 4 * g]) =
                         make_float4(a4[4 * q], a4[4 * q + 1], a4[4 * q + 2], a4[4 * q + 3]);
                 }
-        // (the same wave wrote and reads: no barrier needed, the LDS counter orders them)
+        wave_lds_order();                                   // (the same wave wrote and reads: no barrier needed)
         constexpr int LPR = COLS / 4;                       // lanes per row
         const int rows_valid = min(32 * MPP, (mt_cnt - MPP * pass) * 32);
 #pragma unroll
@@ -312,6 +313,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
             if (r < rows_valid && n < n_tiles * 32)
                 *reinterpret_cast<float4*>(&Ps[(size_t)((mt0 + MPP * pass) * 32 + r) * ldp + n]) = v;
         }
+        wave_lds_order();                                   // (the next pass overwrites the slice)
     }
     __syncthreads();                                        // the next tile's prologue overwrites the LDS slices
     }

@@ -1,4 +1,4 @@
-// Direct-to-LDS loads.
+// Direct-to-LDS loads, and the order of a wave's own LDS accesses.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -17,6 +17,14 @@ template <int N> static __device__ __forceinline__ void load_to_lds_first(int wa
                  ::"s"(dst), "v"(lane16), "s"(src), "s"(wave), "n"(N) : "m0", "scc", "memory");
 }
 #pragma clang diagnostic pop
+// Between the stores and the loads by which the lanes of one wave exchange data through a slice of LDS that is theirs.  The
+// LDS unit takes a wave's instructions in order, but seen per thread the addresses differ, so without this the compiler may
+// move a load before the store of the lane it reads from.  Costs no instruction.
+static __device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 static __device__ __forceinline__ unsigned lds_offset(const void* p) {
     return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
 }
