@@ -313,3 +313,33 @@ def test_a_model_without_layers_sees_its_embeddings():
     for got, tokens in ((init, np.full(64, shape.mask_id)), (step, X[gbr, pos])):
         want = logits(tokens)
         assert got.shape == want.shape and np.abs(got - want)[:, :-1].max() <= 3e-2
+
+
+def test_plan_overrides_leave_larger_panels_alone():
+    """The tuning override is for panels of at most 128 rows (the buffers of partial tiles hold any of its splits only up
+    to there): block steps of 240 rows have the same logits and tokens, bit for bit, whatever it is set to."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("overtest", 2, 512, 8, 2, 64, 1376, 2048)
+    weights = dict(gen_weights(shape, 19))
+    G, blocks = 128, (16, 96, 128)
+    b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 2), Limits(1, 3, 22 + G, G, 240), poison_workspace=True)
+    try:
+        b.load_weights(weights.items())
+        b.keep_logits(True)
+        rid = b.request_open(gen_prompt(shape, 19, 0, 22), G, blocks)
+        b.refresh([rid], BB_INIT)
+        ref = None
+        for kind, nt, split in [(0, 0, 0), (1, 1, 0), (1, 3, 0), (2, 1, 2), (2, 3, 0), (3, 1, 4), (3, 3, 0)]:
+            print("override", kind, nt, split, flush=True)
+            if kind:
+                b.set_gemm_plan(kind, nt, split)
+            v = b.denoise_step([rid])
+            assert v.m_q == 240
+            got = v.logits(), v.argmax()
+            ref = ref or got
+            assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]), (kind, nt, split)
+            if kind:
+                b.set_gemm_plan(kind, 0, 0)
+    finally:
+        b.close()
