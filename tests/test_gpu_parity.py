@@ -178,6 +178,64 @@ def test_block_step_attention_waves_and_splits(prompt_len, head_dim):
     check_report(s)
 
 
+@pytest.mark.parametrize("d_ffn,tile_rows,requests", [
+    # per request: (window, tokens still masked in it) of each branch, None = the branch has finished
+    (688, 128, [(None, ((256, 320), 20), ((0, 160), 150))]),            # 224 rows of 352, 170 of them to the LM head
+    (8192, 192, [(None, ((256, 320), 20), ((0, 160), 150)),             # 448 of 704 and 300 (10 m-tiles: 4 + 3 + 3)
+                 (((0, 64), 30), None, ((160, 320), 100))]),
+])
+def test_step_with_fewer_live_rows_than_it_is_sized_for(d_ffn, tile_rows, requests):
+    """Block steps sized for more than 256 rows in which branches have finished, last windows are clipped and only a part
+    of the rows is masked: whole row groups of the layer GEMMs are skipped (gate/up with tiles of 128 and of 192 rows), and
+    the LM head's live m-tiles are dealt to fewer row groups than are launched.  Logits, tokens, K,V and the commit
+    against the oracle in fp64, from a poisoned workspace."""
+    from paper_2605_29233_amd import BB_INIT, BB_PERIODIC
+    from paper_2605_29233_amd.binding import gemm_plan
+    shape = ModelShape("livetest", 2, 256, 4, 4, 64, d_ffn, 1024)
+    blocks, G, L_p, n = (64, 128, 160), 320, 20, len(requests)
+    decode = DecodeParams(0.9, 0.5, 400, 8, 0)
+    bound = n * sum(blocks)
+    assert gemm_plan(bound, (d_ffn + 63) // 64 * 128, 256, True, True)["mt"] == tile_rows // 32
+    weights = dict(gen_weights(shape, 23))
+    om = OracleModel(shape, weights, np.float64)
+    print("live rows, ffn", d_ffn, flush=True)
+    bb = make_bb(shape, decode, weights, 3, L_p + G, G, bound, max_requests=n, poison=True)
+    try:
+        rng = np.random.default_rng(23)
+        sides = [SideBySide(bb, om, gen_prompt(shape, 23, i, L_p), G, blocks, decode, conf_tol=5e-4) for i in range(n)]
+        rows = masked = 0
+        for s, windows in zip(sides, requests):
+            s.init()
+            s.commit()
+            for k, w in enumerate(windows):
+                (a, b), m = w or ((G, G), 0)
+                X = s.o.X[k]
+                X[L_p:L_p + b] = rng.integers(0, shape.vocab - 1, b)
+                X[L_p + b:] = shape.mask_id
+                X[L_p + a + rng.permutation(b - a)[:m]] = shape.mask_id
+                s.o.br[k].start, s.o.br[k].end, s.o.br[k].done = L_p + a, L_p + b, w is None
+                rows, masked = rows + b - a, masked + m
+            bb.set_state(s.rid, s.o.X, s.o.br)
+        ids = [s.rid for s in sides]
+        bb.refresh(ids, BB_PERIODIC)
+        for s in sides:
+            s.o.refresh()
+            s.oracle_step()
+        view = bb.denoise_step(ids)
+        assert (view.m_q, view.m_lm) == (rows, masked) and rows + 32 <= bound
+        for s in sides:
+            s.check_step(view)
+            for b in s.o.active():
+                s.compare_kv(b.k, 0)
+                s.compare_kv(b.k, shape.n_layers - 1)
+            s.oracle_commit()
+        for s, st in zip(sides, bb.merge_commit(ids)):
+            s.check_commit(st)
+            assert s.rep.max_logit_err <= 3e-2
+    finally:
+        bb.close()
+
+
 def test_long_row_with_empty_attention_splits():
     """L = 64 * 64 + 1 = 4097 keys against at most 32 query rows per branch: the block-step attention cuts the 65
     pages of a row into 16 splits of 5 pages, of which the last three are empty, the last page holds one key, and
