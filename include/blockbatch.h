@@ -279,6 +279,12 @@ int bb_debug_set_gemm_plan(bb_ctx* ctx, int kind, int nt, int split_k);
  * Returns BB_EINVAL for M < 1, N < 32, K < 16, N % 32, K % 16 or out == NULL. */
 int bb_debug_gemm_plan(int M, int N, int K, int wide, int fusable, int out[5]);
 
+/* Host-only query: how one layer's attention is launched for a forward in which n branches have rows_host[i] packed rows
+ * each and the longest row among them holds seq_len tokens, in a context of this shape and these limits.  out[0] =
+ * workgroups that share the pages of a row, out[1] = waves of such a workgroup (0: the kernel of the full-sequence passes).
+ * Returns BB_EINVAL for shapes or limits bb_create refuses, n < 1, a row count < 1 or seq_len < 1. */
+int bb_debug_attention_plan(const bb_model_cfg* model, const bb_limits* limits, const int* rows_host, int n, int seq_len, int out[2]);
+
 /* Measurement aid: copy `bytes` (a multiple of 16) from src_dev to dst_dev (device pointers, disjoint,
  * 16-byte aligned) on the context's stream with a plain kernel that moves 16 bytes per lane, the access
  * width of the library's kernels.  A known-size reference for scaling hardware traffic counters, whose

@@ -64,7 +64,7 @@ def lib_path():
 _LIB = None
 EXPORTS = ("bb_workspace_bytes", "bb_create", "bb_destroy", "bb_last_error", "bb_load_weights", "bb_request_open",
            "bb_request_close", "bb_refresh", "bb_denoise_step", "bb_merge_commit", "bb_get_tokens", "bb_get_stats",
-           "bb_get_view", "bb_set_state", "bb_get_kv", "bb_set_kv", "bb_read_device", "bb_synchronize", "bb_debug_gemm", "bb_debug_gemm_wide", "bb_debug_wide_format", "bb_profile_enable", "bb_profile_read", "bb_debug_set_gemm_plan", "bb_debug_gemm_plan", "bb_debug_copy16", "bb_generate", "bb_kv_diag_scratch_bytes", "bb_kv_diagnostics", "bb_gemm_static", "bb_debug_mfma_rate", "bb_debug_keep_logits")
+           "bb_get_view", "bb_set_state", "bb_get_kv", "bb_set_kv", "bb_read_device", "bb_synchronize", "bb_debug_gemm", "bb_debug_gemm_wide", "bb_debug_wide_format", "bb_profile_enable", "bb_profile_read", "bb_debug_set_gemm_plan", "bb_debug_gemm_plan", "bb_debug_attention_plan", "bb_debug_copy16", "bb_generate", "bb_kv_diag_scratch_bytes", "bb_kv_diagnostics", "bb_gemm_static", "bb_debug_mfma_rate", "bb_debug_keep_logits")
 KERNEL_CLASSES = ("gemm_skinny", "gemm_wide", "attention", "glue", "policy")
 
 
@@ -108,6 +108,7 @@ def load_library():
         lib.bb_debug_gemm_wide.argtypes = lib.bb_debug_gemm.argtypes
         lib.bb_debug_wide_format.argtypes = [C.c_void_p, C.c_int]
         lib.bb_debug_gemm_plan.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
+        lib.bb_debug_attention_plan.argtypes = [C.POINTER(bb_model_cfg), C.POINTER(bb_limits), C.c_void_p, C.c_int, C.c_int, C.POINTER(C.c_int)]
         lib.bb_kv_diag_scratch_bytes.restype = C.c_size_t
         lib.bb_kv_diag_scratch_bytes.argtypes = [C.c_void_p, C.c_int]
         lib.bb_kv_diagnostics.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p, C.c_void_p]
@@ -386,6 +387,13 @@ class BlockBatch:
         self._chk(fn(self._ctx, A.ctypes.data_as(C.c_void_p), W.ctypes.data_as(C.c_void_p),
                      out.ctypes.data_as(C.c_void_p), M, N, K, split_k), "bb_debug_gemm_wide" if wide else "bb_debug_gemm")
         return out
+
+    def attention_plan(self, rows, seq_len):
+        """bb_debug_attention_plan for this context: (page splits, waves per workgroup) of a forward with these row counts."""
+        a, p, n = self._ids(rows)
+        out = (C.c_int * 2)()
+        self._chk(self.lib.bb_debug_attention_plan(C.byref(self._mc), C.byref(self._lim), p, n, int(seq_len), out), "bb_debug_attention_plan")
+        return out[0], out[1]
 
     def wide_format(self, on=True):
         self._chk(self.lib.bb_debug_wide_format(self._ctx, int(on)), "bb_debug_wide_format")

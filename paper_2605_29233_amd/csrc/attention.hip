@@ -418,17 +418,9 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const flo
     }
 }
 
-// max_pages: pages of the longest row among the segments; seg_tiles: 32-row tiles over all segments (an upper bound);
-// part / part_elems: scratch for split partial results.
-void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int mt_total, int max_seg_rows,
-                      int seg_base, int n_segs, int max_pages, int seg_tiles, float* part, size_t part_elems, int wide, hipStream_t s) {
-    const int group = D.hq / D.hkv, nflat = max_seg_rows * group;
-    if (nflat >= 512) {     // many query rows per segment: waves take different query tiles
-        dim3 grid(D.hkv, (nflat + 127) / 128, n_segs);
-        if (D.hd == 128) attention_full_kernel<128><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
-        else attention_full_kernel<64><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
-        return;
-    }
+AttentionPlan attention_plan(const Dev& D, int max_seg_rows, int n_segs, int max_pages, int seg_tiles, size_t part_elems) {
+    const int nflat = max_seg_rows * (D.hq / D.hkv);
+    if (nflat >= 512) return {0, 1};        // many query rows per segment: waves take different query tiles
     // Few query rows: a workgroup per tile, of four waves (two workgroups to a CU) up to 16 pages, of eight above: with one
     // workgroup per CU four waves leave the CU's loads idle (80 pages, 256 tiles: 236 us against 149; 24 pages, 200
     // workgroups: 27.5 against 19.8), with few pages eight have too little each (12 pages, 320 tiles: 44.9 us against 43.3).
@@ -440,9 +432,23 @@ void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int 
     int n_splits = std::min(std::min(256 / wgs, (max_pages + waves - 1) / waves), 16);
     while (n_splits > 1 && (size_t)tiles * n_splits * (64 + 32 * D.hd) > part_elems) --n_splits;
     if (n_splits < 1 || stream_us - stream_us / n_splits < combine_us) n_splits = 1;
+    return {waves, n_splits};
+}
+
+void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int mt_total, int max_seg_rows,
+                      int seg_base, int n_segs, int max_pages, int seg_tiles, float* part, size_t part_elems, int wide, hipStream_t s) {
+    const int nflat = max_seg_rows * (D.hq / D.hkv), qtiles = (nflat + 31) / 32;
+    const AttentionPlan p = attention_plan(D, max_seg_rows, n_segs, max_pages, seg_tiles, part_elems);
+    const int n_splits = p.n_splits;
+    if (p.waves == 0) {
+        dim3 grid(D.hkv, (nflat + 127) / 128, n_segs);
+        if (D.hd == 128) attention_full_kernel<128><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
+        else attention_full_kernel<64><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, wide);
+        return;
+    }
     dim3 grid(D.hkv, qtiles * n_splits, n_segs), cgrid(D.hkv, qtiles, n_segs);
 #define ATT(HD_) do { \
-        if (waves == 8) attention_kernel<HD_, 8><<<grid, 512, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide); \
+        if (p.waves == 8) attention_kernel<HD_, 8><<<grid, 512, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide); \
         else attention_kernel<HD_, 4><<<grid, 256, 0, s>>>(D, Q, Apk, layer, mt_total, seg_base, n_splits, part, wide); \
         if (n_splits > 1) attention_combine_kernel<HD_><<<cgrid, 256, 0, s>>>(D, part, Apk, mt_total, seg_base, n_splits, wide); \
     } while (0)

@@ -1083,6 +1083,24 @@ extern "C" int bb_debug_gemm_plan(int M, int N, int K, int wide, int fusable, in
     return BB_OK;
 }
 
+extern "C" int bb_debug_attention_plan(const bb_model_cfg* model, const bb_limits* limits, const int* rows, int n, int seq_len, int out[2]) {
+    try {
+        if (check_cfg(model, limits, nullptr) != BB_OK || !rows || !out || n < 1 || seq_len < 1) return BB_EINVAL;
+        bb_ctx tmp{};
+        tmp.m = *model; tmp.lim = *limits; tmp.dc = bb_decode_cfg{};
+        size_t total = 0;
+        layout(&tmp, nullptr, &total);
+        int longest = 0, tiles = 0;
+        for (int i = 0; i < n; ++i) {
+            if (rows[i] < 1) return BB_EINVAL;
+            longest = std::max(longest, rows[i]); tiles += att_tiles(&tmp, rows[i]);
+        }
+        const AttentionPlan p = attention_plan(tmp.D, longest, tmp.D.max_req * tmp.D.max_br, (seq_len + BB_PAGE - 1) / BB_PAGE, tiles, tmp.attn_part_elems);
+        out[0] = p.n_splits; out[1] = p.waves;
+        return BB_OK;
+    } catch (...) { return BB_ENOMEM; }
+}
+
 extern "C" int bb_debug_wide_format(bb_ctx* c, int on) {
     if (!c) return BB_EINVAL;
     c->wide_off = !on;

@@ -273,6 +273,11 @@ void launch_qkv_epilogue(const Dev& D, const float* qkv, int n_partial, size_t p
 // act = SiLU(gate) * up from the fused (32-row interleaved) gate/up projection -> packed panel with K = f
 void launch_swiglu_epilogue(const Dev& D, const float* gu, int n_partial, size_t partial_stride, int ldp, u32x4* Apk,
                             int rows_cap, int mt_total, int wide, const float* ssq, int nblk, hipStream_t s);
+// Which attention kernel runs, and how: waves of a workgroup of the block-step kernel (0: the full-pass kernel) and the
+// workgroups that share a row's pages.  max_pages: pages of the longest row among the segments; seg_tiles: 32-row tiles over all
+// segments (an upper bound); part_elems: scratch for split partial results.
+struct AttentionPlan { int waves, n_splits; };
+AttentionPlan attention_plan(const Dev& D, int max_seg_rows, int n_segs, int max_pages, int seg_tiles, size_t part_elems);
 void launch_attention(const Dev& D, const half_t* Q, u32x4* Apk, int layer, int mt_total, int max_seg_rows,
                       int seg_base, int n_segs, int max_pages, int seg_tiles, float* part, size_t part_elems, int wide, hipStream_t s);
 void launch_vocab_finish(const Dev& D, int lm_cap, int bcast, hipStream_t s);

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 def run_case(model, decode, prompt_len, gen_len, blocks, seed=0, max_steps=10 ** 9, kv=True, dtype=np.float64,
-             weights_device="cpu", conf_tol=5e-4, import_cache=False):
+             weights_device="cpu", conf_tol=5e-4, import_cache=False, attention=None):
     """conf_tol: with the oracle in fp64 on these small models the confidences agree to a few 1e-5, so a
     tenth of the general bound is asserted and the pairwise guard band shrinks with it."""
     print(f"parity case {model.name} blocks={blocks} L_p={prompt_len} G={gen_len} seed={seed}", flush=True)
@@ -22,6 +22,8 @@ def run_case(model, decode, prompt_len, gen_len, blocks, seed=0, max_steps=10 **
     bb = make_bb(model, decode, weights, len(blocks), prompt_len + gen_len, gen_len, sum(min(b, gen_len) for b in blocks))
     try:
         sbs = SideBySide(bb, om, prompt, gen_len, blocks, decode, conf_tol=conf_tol)
+        if attention:           # (page splits, waves) of a block step that the case is there for
+            assert bb.attention_plan(blocks, prompt_len + gen_len) == attention
 
         def check_kv(s):
             for k in range(s.o.N):
@@ -167,13 +169,15 @@ def test_full_pass_attention_tiles(prompt_len, gen_len, head_dim):
     check_report(s)
 
 
-@pytest.mark.parametrize("prompt_len", [192, 449, 960, 961])
-@pytest.mark.parametrize("head_dim", [64, 128])
-def test_block_step_attention_waves_and_splits(prompt_len, head_dim):
-    """Block steps against rows of 4 (one page per wave), 9 (a wave with three, a split with a short last range), 16 and 17
-    pages (the last row length with four waves per workgroup and the first with eight; its last page holds one key)."""
+@pytest.mark.parametrize("prompt_len,head_dim,splits,waves", [
+    (192, 64, 1, 4), (192, 128, 1, 4), (449, 64, 1, 4), (449, 128, 3, 4), (960, 64, 4, 4), (960, 128, 4, 4), (961, 64, 3, 8), (961, 128, 3, 8)])
+def test_block_step_attention_waves_and_splits(prompt_len, head_dim, splits, waves):
+    """Block steps against rows of 4 (one page per wave), 9 (whole: a wave with three; in three splits of 3, a wave without
+    any), 16 and 17 pages (the last row length with four waves per workgroup and the first with eight; three splits of 6, 6
+    and 5, the last page holds one key)."""
     shape = ModelShape("blockatt", 1, 256, 256 // head_dim, 256 // head_dim, head_dim, 688, 1024)
-    s = run_case(shape, DecodeParams(0.9, 0.5, 8, 8, 0), prompt_len, 64, (8, 16, 48), seed=22, max_steps=2, kv=False)
+    s = run_case(shape, DecodeParams(0.9, 0.5, 8, 8, 0), prompt_len, 64, (8, 16, 48), seed=22, max_steps=2, kv=False,
+                 attention=(splits, waves))
     assert s.rep.max_logit_err <= 3e-2
     check_report(s)
 
@@ -237,13 +241,43 @@ def test_step_with_fewer_live_rows_than_it_is_sized_for(d_ffn, tile_rows, reques
 
 
 def test_long_row_with_empty_attention_splits():
-    """L = 64 * 64 + 1 = 4097 keys against at most 32 query rows per branch: the block-step attention cuts the 65
-    pages of a row into 16 splits of 5 pages, of which the last three are empty, the last page holds one key, and
-    inside a split some waves get no page."""
+    """A row of L = 64 * 64 + 1 = 4097 keys (65 pages) beside one of 100 (2 pages) in the same block steps: the pages of every row
+    are cut into nine ranges.  The long row's last range is one page that holds one key, so seven of its eight waves get
+    nothing; of the short row's ranges the last seven are empty.  Each against its own oracle."""
+    from paper_2605_29233_amd import BB_PERIODIC
     w = workload("tiny")
-    s = run_case(w.model, DecodeParams(0.9, 0.5, 8, 3, 0), 4033, 64, (8, 16, 32), seed=10, max_steps=4, kv=False)
-    assert s.o.L == 4097 and s.rep.max_logit_err <= 3e-2
-    check_report(s)
+    weights = dict(gen_weights(w.model, 10))
+    om = OracleModel(w.model, weights, np.float64)
+    decode = DecodeParams(0.9, 0.5, 8, 3, 0)
+    bb = make_bb(w.model, decode, weights, 3, 4097, 64, 112, max_requests=2)
+    try:
+        print("long and short row", flush=True)
+        assert bb.attention_plan(w.block_sizes * 2, 4097) == (9, 8)
+        sides = [SideBySide(bb, om, gen_prompt(w.model, 10, i, lp), 64, w.block_sizes, decode, conf_tol=5e-4) for i, lp in enumerate((4033, 36))]
+        assert [s.o.L for s in sides] == [4097, 100]
+        for s in sides:
+            s.init()
+            s.commit()
+        ids = [s.rid for s in sides]
+        for step in range(4):
+            if step == 3:
+                bb.refresh(ids, BB_PERIODIC)
+            for s in sides:
+                if step == 3:
+                    s.o.refresh()
+                s.oracle_step()
+            view = bb.denoise_step(ids)
+            for s in sides:
+                s.check_step(view)
+                s.oracle_commit()
+            for s, st in zip(sides, bb.merge_commit(ids)):
+                s.check_commit(st)
+        for s in sides:
+            assert not s.o.finished and s.rep.max_logit_err <= 3e-2
+            s.final = bb.get_stats(s.rid)
+            check_report(s)
+    finally:
+        bb.close()
 
 
 def test_vocabulary_reduction_ties_take_the_lowest_token_id():
