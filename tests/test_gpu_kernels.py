@@ -50,12 +50,12 @@ def test_mfma_gemm_matches_fp64(bb, M, N, K, split):
 @pytest.mark.parametrize("M,N,K,split", [
     (32, 32, 16, 1), (1, 64, 32, 1), (56, 768, 256, 0), (37, 256, 688, 0), (130, 1024, 256, 0),
     (300, 96, 4096, 7), (384, 1376, 256, 0), (700, 4608, 512, 0), (1536, 5632, 128, 0), (3000, 512, 2752, 2),
-    # shapes whose plan takes the 192-row workgroup tile: two tiles per wave with a ragged last row group; one tile
-    # per wave with k split in two; one tile per wave with a number of column tiles that is no multiple of four
+    # shapes whose plan takes the 192-row workgroup tile: a ragged last row group; k split in four; a number of column
+    # tiles that is no multiple of eight
     (3000, 4096, 1024, 0), (740, 4096, 4096, 0), (1100, 4192, 768, 0),
 ])
 def test_wide_format_gemm_matches_fp64(bb, M, N, K, split):
-    """The fp16 + fp8 operand kernel of the passes with many rows: activation = fp16 term + e5m2 remainder,
+    """The fp16 + fp8 operand kernels: activation = fp16 term + e5m2 remainder,
     weight = row-scaled fp16 (exact) and e4m3.  Per product the error is about 2^-16 relative (e4m3 rounding of
     the weight times the 2^-12 remainder, e5m2 rounding of the remainder), random in sign."""
     rng = np.random.default_rng(M * 11 + N)
@@ -75,16 +75,25 @@ def test_wide_format_gemm_matches_fp64(bb, M, N, K, split):
     assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
 
 
-@pytest.mark.parametrize("M,N,K,split", [
-    (257, 32, 64, 0),            # nine m-tiles, one column tile, a single chunk of 64 k: half a unit of the fp8 step
-    (289, 288, 192, 0),          # an odd number of chunks, column tiles that are no multiple of eight
-    (385, 96, 688, 3),           # splits of four chunks, the last one of three with a padded end
-    (520, 512, 1088, 3),         # splits of an odd number of chunks
-    (1030, 256, 128, 0),         # one unit; row groups past a multiple of both tile heights
+@pytest.mark.parametrize("M,N,K,split,tile_rows", [
+    (257, 32, 64, 0, 128),          # nine m-tiles, one column tile, a single chunk of 64 k: half a unit of the fp8 step
+    (289, 288, 192, 0, 128),        # an odd number of chunks, column tiles that are no multiple of eight
+    (385, 96, 688, 3, 128),         # splits of four chunks, the last one of three with a padded end
+    (520, 512, 1088, 3, 128),       # splits of an odd number of chunks
+    (1030, 256, 128, 0, 128),       # one unit; the last row group is one m-tile
+    (390, 2080, 64, 0, 192),        # a single chunk; row groups of 6, 6 and 1 m-tiles; column tiles that are no multiple of eight
+    (1100, 4192, 192, 0, 192),      # three chunks: a unit and a half; the last row group has five m-tiles
+    (1190, 2080, 1088, 0, 192),     # three splits of 6, 6 and 5 chunks; the last row group has two m-tiles
 ])
-def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split):
-    """The eight-wave kernel (more than 256 rows) where units, k splits, row and column groups end: against fp64, bound as
-    in test_wide_format_gemm_matches_fp64."""
+def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split, tile_rows):
+    """The eight-wave kernel (more than 256 rows) with both tile heights, where units, k splits, row and column groups end:
+    against fp64, bound as in test_wide_format_gemm_matches_fp64.  (A forced split takes the 128-row tile.)"""
+    if split == 0:
+        from paper_2605_29233_amd.binding import gemm_plan
+        p = gemm_plan(M, N, K, wide=True)
+        chunks = (K + 63) // 64
+        assert p["mt"] == tile_rows // 32, p
+        assert tile_rows == 128 or (chunks - (p["split_k"] - 1) * p["chunks_per_split"]) % 2, "the 192-row cases end in half a unit"
     rng = np.random.default_rng(M * 13 + K)
     A = rng.standard_normal((M, K)).astype(np.float32)
     Wb = gen_normal_bf16(2, f"m{N}x{K}", N * K, 0.05).view(torch.int16).numpy().view(np.uint16).reshape(N, K)
