@@ -12,7 +12,8 @@ timed region is opened again, so every counted step is a real block forward).  B
   * `roofline`: the weight-streaming MFMA GEMM launches of the block forward against the HBM peak, from
     per-launch HIP events on the library's stream (raw, and with the measured cost of the event packets
     taken off), with the HBM traffic per launch that rocprofv3 counters gave for the same kernels;
-  * `roofline_kv`: the block forward's attention launches against the HBM peak (K,V streamed per step);
+  * `roofline_kv`: the block forward's attention launches against the HBM peak (K,V of every branch row, and of every
+    distinct page: right after the initial forward the branches share all pages but those under their windows);
   * `measured_peaks`: what a plain 16-byte-per-lane copy and a pure MFMA loop reach on this very GPU;
   * `other_workloads`: steady step, refresh and both rooflines for the long-context and 16-request shapes;
   * `cpu_baseline`: the CPU oracle timed on the host for reference.
@@ -102,6 +103,9 @@ def steady_state(bb, w, ids, steps, warmup, profile_steps, torch):
         bb.denoise_step(ids, want_view=False)
     prof = bb.profile_read()
     bb.profile_enable(False)
+    # the launches' flops count the rows they are sized for: here every one of them is live and masked
+    live, sized = bb.latest_view(), sum(min(b, w.gen_len) for b in w.block_sizes) * w.n_requests
+    assert (live.m_q, live.m_lm) == (sized, sized), (live.m_q, live.m_lm, sized)
     g = prof["gemm_skinny"] if prof["gemm_skinny"]["launches"] else prof["gemm_wide"]
     # the event packet after every launch lengthens the profiled forward; its cost per launch is what the
     # profiled forward takes beyond the unprofiled one, spread over the launches
@@ -118,8 +122,8 @@ def steady_state(bb, w, ids, steps, warmup, profile_steps, torch):
     gbs = g["bytes"] / 1e9 / (raw_ms / 1e3)
     tfl = g["flops"] / 1e12 / (raw_ms / 1e3)
     roof = {"bound": "hbm" if hbm_bound else "mfma",
-            "kernel": "gemm_wide_kernel and the LM head's gemm_kernel (MFMA GEMM launches of the block forward: %s)"
-                      % ("weight streaming" if hbm_bound else "many rows"),
+            "kernel": "%s and the LM head's gemm_kernel (MFMA GEMM launches of the block forward: %s)"
+                      % (("gemm_wide_kernel", "weight streaming") if hbm_bound else ("gemm_many_kernel", "many rows")),
             "achieved": gbs if hbm_bound else tfl, "peak": HBM_PEAK_GBS if hbm_bound else MFMA_BF16_PEAK_TFLOPS,
             "unit": "GB/s" if hbm_bound else "TFLOP/s",
             "frac": gbs / HBM_PEAK_GBS if hbm_bound else tfl / MFMA_BF16_PEAK_TFLOPS,
@@ -134,16 +138,20 @@ def steady_state(bb, w, ids, steps, warmup, profile_steps, torch):
                     "fp8 terms of the layer GEMMs (x2 for the LM head, which keeps two bf16 activation terms)"}
     # attention of the block forward: K and V of every active branch row are streamed once per layer.  Algorithmic
     # bytes = 2 B per cached element (n_kv_heads * head_dim keys + as many values per token); the cache holds two
-    # fp16 terms per element, so the kernel actually streams twice that.
+    # fp16 terms per element, so the kernel actually streams twice that; pages that branches share are counted once per
+    # branch there and once in the distinct bytes.
     at = prof["attention"]
     rows_tokens = sum(lp + w.gen_len for lp in w.prompt_lens) * len(w.block_sizes)
     kv_bytes = 2.0 * m.n_kv_heads * m.head_dim * 2 * rows_tokens * m.n_layers
+    pages = sum(-(-(lp + w.gen_len) // 64) + sum((lp + min(b, w.gen_len) - 1) // 64 - lp // 64 + 1 for b in w.block_sizes) for lp in w.prompt_lens)
+    distinct = 4.0 * m.n_kv_heads * m.head_dim * 2 * 64 * pages * m.n_layers
     at_ms = at["total_ms"] / profile_steps
     kv = {"bound": "hbm", "kernel": "attention_kernel (block forward, paged K,V of every branch row)",
           "achieved": kv_bytes / 1e9 / (at_ms / 1e3), "peak": HBM_PEAK_GBS, "unit": "GB/s",
           "frac": kv_bytes / 1e9 / (at_ms / 1e3) / HBM_PEAK_GBS,
           "algorithmic_bytes_per_forward": kv_bytes, "streamed_bytes_per_forward": 2 * kv_bytes,
           "frac_of_streamed_bytes": 2 * kv_bytes / 1e9 / (at_ms / 1e3) / HBM_PEAK_GBS,
+          "distinct_bytes_per_forward": distinct, "frac_of_distinct_bytes": distinct / 1e9 / (at_ms / 1e3) / HBM_PEAK_GBS,
           "attention_ms_per_forward": at_ms, "launches_per_forward": at["launches"] / profile_steps}
 
     # refresh alone

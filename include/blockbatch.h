@@ -225,8 +225,10 @@ int bb_synchronize(bb_ctx* ctx);
 typedef struct {
     int klass, launches;
     double total_ms;
-    double bytes;            /* algorithmic bytes: weights streamed (GEMM), K/V read (attention)     */
-    double flops;            /* algorithmic flops of the contraction (GEMM, attention)               */
+    double bytes;            /* algorithmic bytes: weights streamed (GEMM)                            */
+    double flops;            /* of the contraction over the rows the launch is sized for (GEMM): the LM head, and
+                                launches of more than 256 rows, compute the live ones only, so this is an upper
+                                bound where tokens are committed, windows clipped or branches finished         */
 } bb_profile_entry;
 int bb_profile_enable(bb_ctx* ctx, int on);
 int bb_profile_read(bb_ctx* ctx, bb_profile_entry* out_host, int max_entries, int* n_out);
@@ -236,7 +238,7 @@ int bb_profile_read(bb_ctx* ctx, bb_profile_entry* out_host, int max_entries, in
  * split_k = 0 lets the library choose. */
 int bb_debug_gemm(bb_ctx* ctx, const float* A_host, const uint16_t* W_host, float* C_host,
                   int M, int N, int K, int split_k);
-/* The same product through the kernel that passes with many rows use: activations as fp16 + a scaled e5m2 remainder,
+/* The same product through the kernels of the layer GEMMs (one up to 256 rows, one above): activations as fp16 + a scaled e5m2 remainder,
  * weights as row-scaled fp16, converted to e4m3 in the kernel for the remainder's product (about 2^-16 relative
  * accuracy per product instead of 2^-17). */
 int bb_debug_gemm_wide(bb_ctx* ctx, const float* A_host, const uint16_t* W_host, float* C_host,
