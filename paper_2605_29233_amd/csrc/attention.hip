@@ -420,8 +420,14 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const flo
 
 AttentionPlan attention_plan(const Dev& D, int max_seg_rows, int n_segs, int max_pages, int seg_tiles, size_t part_elems) {
     const int nflat = max_seg_rows * (D.hq / D.hkv);
-    if (nflat >= 512) return {0, 1};        // many query rows per segment: waves take different query tiles
-    // Few query rows: a workgroup per tile, of four waves (two workgroups to a CU) up to 16 pages, of eight above: with one
+    // Many query rows per segment: the waves of a workgroup take different tiles and share each page.  Only where these workgroups
+    // outnumber the CUs: one alone on its CU has nothing to run at its three barriers per page, while a workgroup per tile, its
+    // waves on different pages, has four times the workgroups and walks a quarter (or an eighth) of the pages.  us per launch,
+    // this kernel / a workgroup per tile, by 128-row workgroups: heads of 64: 64 (4096 keys, 4 heads: 128) 129 / 64, 256 (32 pages)
+    // 75 / 68, 288 (47 pages) 119 / 112, 376 141 / 147, 512 205 / 250; heads of 128: 128 32 / 22, 168 44 / 37, 192 46 / 39, 224 57 /
+    // 60, 256 63 / 65, 352 115 / 141, 512 189 / 257.
+    if (nflat >= 512 && seg_tiles * D.hkv > 4 * (D.hd == 64 ? 256 : 192)) return {0, 1};
+    // Otherwise a workgroup per tile, of four waves (two workgroups to a CU) up to 16 pages, of eight above: with one
     // workgroup per CU four waves leave the CU's loads idle (80 pages, 256 tiles: 236 us against 149; 24 pages, 200
     // workgroups: 27.5 against 19.8), with few pages eight have too little each (12 pages, 320 tiles: 44.9 us against 43.3).
     // Where the tiles leave CUs idle the pages of a row are split over several workgroups and a second kernel merges the

@@ -127,3 +127,24 @@ def test_gemm_plans_cover_k_fit_the_chip_and_the_register_file(lib):
         binding.gemm_plan(0, 4096, 4096)
     with pytest.raises(ValueError):
         binding.gemm_plan(64, 4100, 4096)
+
+
+@pytest.mark.parametrize("hq,hkv,hd,L,branches,full", [
+    (4, 4, 64, 4096, 1, False),         # 128 workgroups of four tiles
+    (4, 4, 64, 2048, 4, False),         # 256: one for each CU
+    (4, 4, 64, 2176, 4, True),          # 272
+    (32, 32, 128, 768, 1, False),       # 192
+    (32, 32, 128, 896, 1, True),        # 224
+    (28, 4, 128, 768, 1, False),        # 168
+    (28, 4, 128, 1536, 3, True),
+    (28, 4, 128, 128, 1, False),        # a wide window of a block step with grouped heads
+    (32, 32, 128, 511, 4, False),       # fewer than 512 query rows per branch: a workgroup per tile whatever their number
+])
+def test_attention_shares_pages_in_a_workgroup_only_with_more_workgroups_than_cus(lib, hq, hkv, hd, L, branches, full):
+    mc = binding.bb_model_cfg(2, 256, hq, hkv, hd, 256, 1024, 10000.0, 1e-5, 0, 1023)
+    lim = binding.bb_limits(1, 4, 4160, 64, 256)
+    rows, out = (C.c_int * branches)(*([L] * branches)), (C.c_int * 2)()
+    assert lib.bb_debug_attention_plan(C.byref(mc), C.byref(lim), rows, branches, L, out) == 0
+    assert (out[1] == 0) == full and out[0] >= 1 and out[1] in (0, 4, 8)
+    rows[0] = 0
+    assert lib.bb_debug_attention_plan(C.byref(mc), C.byref(lim), rows, branches, L, out) == -1

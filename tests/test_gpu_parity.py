@@ -22,8 +22,8 @@ def run_case(model, decode, prompt_len, gen_len, blocks, seed=0, max_steps=10 **
     bb = make_bb(model, decode, weights, len(blocks), prompt_len + gen_len, gen_len, sum(min(b, gen_len) for b in blocks))
     try:
         sbs = SideBySide(bb, om, prompt, gen_len, blocks, decode, conf_tol=conf_tol)
-        if attention:           # (page splits, waves) of a block step that the case is there for
-            assert bb.attention_plan(blocks, prompt_len + gen_len) == attention
+        if attention:           # what the case is there for: rows per branch, (page splits, waves)
+            assert bb.attention_plan(attention[0], prompt_len + gen_len) == attention[1]
 
         def check_kv(s):
             for k in range(s.o.N):
@@ -158,13 +158,18 @@ def test_last_page_holds_one_key():
 
 @pytest.mark.parametrize("prompt_len,gen_len,head_dim", [
     (40, 24, 128), (41, 24, 128), (70, 57, 128), (96, 33, 64), (100, 91, 64), (30, 35, 64)])
-def test_full_pass_attention_tiles(prompt_len, gen_len, head_dim):
+@pytest.mark.parametrize("n_kv_heads", [2, 20])
+def test_full_pass_attention_tiles(prompt_len, gen_len, head_dim, n_kv_heads):
     """Full passes with at least 512 flattened query rows per branch (eight query heads per kv head): one page, a second page
     with a single key, a ragged last page; row counts that leave the last workgroup of four 32-row tiles with one, two or
-    three of them, the last partly filled.  Refreshes every second step, against the oracle in fp64."""
-    shape = ModelShape("fullatt", 2, 256, 1024 // head_dim, 128 // head_dim, head_dim, 688, 1024)
-    assert (prompt_len + gen_len) * 8 >= 512
-    s = run_case(shape, DecodeParams(0.9, 0.5, 4, 2, 0), prompt_len, gen_len, (8, 16), seed=21, max_steps=5)
+    three of them, the last partly filled.  Refreshes every second step, against the oracle in fp64.  With 20 kv heads the
+    refreshes of four branches have more workgroups than CUs and take the kernel that shares pages through LDS, with two
+    they take a workgroup per tile."""
+    shape = ModelShape("fullatt", 2, 256, 8 * n_kv_heads, n_kv_heads, head_dim, 688, 1024)
+    L, blocks = prompt_len + gen_len, (4, 8, 12, 16)
+    assert L * 8 >= 512
+    s = run_case(shape, DecodeParams(0.9, 0.5, 4, 2, 0), prompt_len, gen_len, blocks, seed=21, max_steps=5,
+                 attention=((L,) * 4, (1, 0) if n_kv_heads == 20 else (1, 4)))
     assert s.rep.max_logit_err <= 3e-2
     check_report(s)
 
@@ -177,7 +182,7 @@ def test_block_step_attention_waves_and_splits(prompt_len, head_dim, splits, wav
     and 5, the last page holds one key)."""
     shape = ModelShape("blockatt", 1, 256, 256 // head_dim, 256 // head_dim, head_dim, 688, 1024)
     s = run_case(shape, DecodeParams(0.9, 0.5, 8, 8, 0), prompt_len, 64, (8, 16, 48), seed=22, max_steps=2, kv=False,
-                 attention=(splits, waves))
+                 attention=((8, 16, 48), (splits, waves)))
     assert s.rep.max_logit_err <= 3e-2
     check_report(s)
 
