@@ -226,7 +226,7 @@ static __device__ __forceinline__ MSI msi_merge(MSI a, MSI b) {
 }
 
 // ---- kernel launchers (each enqueues on `s`) -----------------------------------------------------
-struct GemmPlan { int split_k; int chunks_per_split; int nt; int mt = 4; int wv = 4; };      // mt: m-tiles of 32 rows per workgroup; wv: its waves (wide format up to 256 rows)
+struct GemmPlan { int split_k; int chunks_per_split; int nt; int mt = 4; int wv = 4; };      // mt: m-tiles of 32 rows per workgroup; wv: its waves (wide format: 3 or 4, 8 = gemm_many_kernel)
 GemmPlan gemm_plan(int m_rows, int N, int K, int forced_split, int forced_nt);
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable = false);     // wide-format kernel: may take mt = 6
 // Epilogue of launch_gemm: partial tiles P[split][m][n] (default); SiLU(gate) * up as the down projection's panel

@@ -1,4 +1,5 @@
-// Wide-format MFMA GEMM for passes of up to 256 rows (block steps; gemm_many.hip takes the others):
+// Wide-format MFMA GEMM for passes of up to 256 rows (block steps), and of more rows over small matrices; gemm_many.hip
+// takes the others:
 //     C[m][n] = sum_k A[m][k] * W[n][k]          (fp32 accumulate)
 // with the operands in the wide format of bb_internal.h: the activation as fp16 + a scaled e5m2 remainder, the
 // weight as row-scaled fp16, converted in registers to e4m3 for the remainder's product.  Per 64 k and 32x32 tile
@@ -363,13 +364,17 @@ static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
 // 128 columns in four splits 19.4 us, 256 in eight 21.2 and twice the partial tiles; 37888 x 3584 at 240 rows: one round of
 // 384 columns 117 us and a SwiGLU launch, two rounds with SwiGLU in the epilogue 147.)
 //
-// With more rows (gemm_many_kernel) the candidates (128 or 192 rows per
+// With more rows the candidates of gemm_many_kernel (128 or 192 rows per
 // workgroup, k split) are priced by a model fitted to 800 measured launches (272..4206 rows, N 3584..37888, K
 // 3584..18944; 4.6 % rms): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
 // workgroups except that a last round which leaves CUs idle runs at a higher clock (the chip is at its power limit), and
 // the partial tiles, written here and read by the consumer launch once per k split.  Splits take whole units of 128 k.
 // Where both tiles price within 5 % the larger one is taken: it fetches a fifth less per product.  fusable: the caller
 // can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
+// Beside them this file's kernel with tiles of 128 columns, where they and their k splits fit one round: small matrices leave
+// most CUs without work either way, and the smaller tile with fewer waves is through sooner.  Its price is fitted to 175
+// shapes (272..4096 rows, N 128..4096, K 64..4096) measured with both; us of eight waves / of four: 768 x 256 at 384 rows 8.3 /
+// 6.5, 256 x 688 9.7 / 7.6, 256 x 2048 8.5 / 6.9, 4096 x 512 at 640 rows 11.7 / 10.6, but 768 x 4096 15.2 / 17.9, 4096 x 4096 37 / 49.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
     if (mt_total <= 8) {
@@ -382,10 +387,14 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
         p.mt = block_step_body(mt_total, p.nt);
         return p;
     }
-    if (forced_split > 0) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
+    if (forced_split > 0) {
+        GemmPlan p = gemm_plan(m_rows, N, K, forced_split, forced_nt);
+        p.wv = 8;
+        return p;
+    }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
-    best.nt = 2;
+    best.nt = 2; best.wv = 8;
     double best_t = 1e30;
     for (int mt = 4; mt <= 6; mt += 2) {
         const double chunk_us = mt == 6 ? 1.67 : 1.18, tile_us = 3.8;
@@ -400,13 +409,21 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
             if (t < best_t) { best_t = t; best.split_k = sp_eff; best.chunks_per_split = cps; best.mt = mt; }
         }
     }
+    const int base = (n_tiles + 3) / 4 * ((mt_total + 3) / 4);
+    for (int sp = 1; sp <= BB_MAX_SPLITK && sp <= std::max(1, total_chunks / 4) && base * sp <= 256; ++sp) {
+        const int cps = (total_chunks + sp - 1) / sp;
+        if ((total_chunks + cps - 1) / cps != sp) continue;
+        const double fill = base * sp / 256.0, partial = sp * (double)mt_total * 32 * N * 4 * (sp == 1 ? 0.166e-6 : 0.25e-6);
+        const double t = 4.0 + cps * 0.585 * (1.0 + 0.8 * fill * fill * fill) + partial + (fusable ? 8.0 : 0.0);
+        if (t < best_t) { best_t = t; best.split_k = sp; best.chunks_per_split = cps; best.nt = 1; best.wv = 4; best.mt = block_step_body(mt_total, 1); }
+    }
     return best;
 }
 
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps,
                       const int* rows_live) {
-    if (mt_total > 8) { launch_gemm_many(Wt, wscale, Apk, P, mt_total, N, K, plan, s, rows_live, swiglu_out, st); return; }
+    if (plan.wv == 8) { launch_gemm_many(Wt, wscale, Apk, P, mt_total, N, K, plan, s, rows_live, swiglu_out, st); return; }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64, nt = plan.nt;
     const int m_groups = (mt_total + 3) / 4, mt = block_step_body(mt_total, nt);
     const size_t split_stride = (size_t)mt_total * 32 * N;

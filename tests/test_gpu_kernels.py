@@ -76,23 +76,25 @@ def test_wide_format_gemm_matches_fp64(bb, M, N, K, split):
 
 
 @pytest.mark.parametrize("M,N,K,split,tile_rows", [
-    (257, 32, 64, 0, 128),          # nine m-tiles, one column tile, a single chunk of 64 k: half a unit of the fp8 step
-    (289, 288, 192, 0, 128),        # an odd number of chunks, column tiles that are no multiple of eight
+    (257, 32, 64, 1, 128),          # nine m-tiles, one column tile, a single chunk of 64 k: half a unit of the fp8 step
+    (289, 288, 192, 1, 128),        # an odd number of chunks, column tiles that are no multiple of eight
     (385, 96, 688, 3, 128),         # splits of four chunks, the last one of three with a padded end
     (520, 512, 1088, 3, 128),       # splits of an odd number of chunks
-    (1030, 256, 128, 0, 128),       # one unit; the last row group is one m-tile
-    (390, 2080, 64, 0, 192),        # a single chunk; row groups of 6, 6 and 1 m-tiles; column tiles that are no multiple of eight
+    (1030, 256, 128, 1, 128),       # one unit; the last row group is one m-tile
+    (1190, 4192, 64, 0, 192),       # a single chunk; the last row group has two m-tiles; column tiles that are no multiple of eight
     (1100, 4192, 192, 0, 192),      # three chunks: a unit and a half; the last row group has five m-tiles
-    (1190, 2080, 1088, 0, 192),     # three splits of 6, 6 and 5 chunks; the last row group has two m-tiles
+    (740, 5664, 1344, 0, 192),      # two splits of 12 and 9 chunks; one column tile over a multiple of eight
 ])
 def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split, tile_rows):
     """The eight-wave kernel (more than 256 rows) with both tile heights, where units, k splits, row and column groups end:
-    against fp64, bound as in test_wide_format_gemm_matches_fp64.  (A forced split takes the 128-row tile.)"""
+    against fp64, bound as in test_wide_format_gemm_matches_fp64.  (A forced split takes the 128-row tile.  Without one these
+    small matrices go to the four-wave kernel: test_small_matrices_of_many_rows.)"""
     if split == 0:
         from paper_2605_29233_amd.binding import gemm_plan
         p = gemm_plan(M, N, K, wide=True)
         chunks = (K + 63) // 64
         assert p["mt"] == tile_rows // 32, p
+        assert p["nt"] == 2, "eight waves"
         assert tile_rows == 128 or (chunks - (p["split_k"] - 1) * p["chunks_per_split"]) % 2, "the 192-row cases end in half a unit"
     rng = np.random.default_rng(M * 13 + K)
     A = rng.standard_normal((M, K)).astype(np.float32)
@@ -101,6 +103,29 @@ def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split, tile_rows):
     print(f"many-row gemm case M={M} N={N} K={K} split={split}", flush=True)
     C = bb.debug_gemm(A, Wb, split, wide=True)
     err = np.abs(C - A.astype(np.float64) @ W.T)
+    mag = np.abs(A).astype(np.float64) @ np.abs(W).T
+    assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (257, 32, 64),              # nine m-tiles: three row groups of three; one column tile, one chunk
+    (320, 224, 192),            # ten: 4 + 4 + 2; column tiles that are no multiple of four
+    (385, 256, 688),            # k splits of an odd number of chunks with a padded end
+    (1030, 768, 1088),          # 33 m-tiles: the last row group has one
+    (4096, 96, 256),
+    (272, 128, 4096),           # 16 k splits
+])
+def test_small_matrices_of_many_rows(bb, M, N, K):
+    """More than 256 rows over a matrix so small that the four-wave kernel's 128-column tiles fit one round: against fp64,
+    bound as in test_wide_format_gemm_matches_fp64."""
+    from paper_2605_29233_amd.binding import gemm_plan
+    assert gemm_plan(M, N, K, wide=True)["nt"] == 1, "four waves, 128 columns"
+    rng = np.random.default_rng(M * 17 + K)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    Wb = gen_normal_bf16(3, f"s{N}x{K}", N * K, 0.05).view(torch.int16).numpy().view(np.uint16).reshape(N, K)
+    W = (Wb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    print(f"small matrix M={M} N={N} K={K}", flush=True)
+    err = np.abs(bb.debug_gemm(A, Wb, 0, wide=True) - A.astype(np.float64) @ W.T)
     mag = np.abs(A).astype(np.float64) @ np.abs(W).T
     assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
 

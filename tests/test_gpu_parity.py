@@ -187,24 +187,25 @@ def test_block_step_attention_waves_and_splits(prompt_len, head_dim, splits, wav
     check_report(s)
 
 
-@pytest.mark.parametrize("d_ffn,tile_rows,requests", [
+@pytest.mark.parametrize("heads,d_ffn,tile_rows,requests", [
     # per request: (window, tokens still masked in it) of each branch, None = the branch has finished
-    (688, 128, [(None, ((256, 320), 20), ((0, 160), 150))]),            # 224 rows of 352, 170 of them to the LM head
-    (8192, 192, [(None, ((256, 320), 20), ((0, 160), 150)),             # 448 of 704 and 300 (10 m-tiles: 4 + 3 + 3)
+    (4, 688, 128, [(None, ((256, 320), 20), ((0, 160), 150))]),            # 224 rows of 352, 170 of them to the LM head
+    (32, 8192, 192, [(None, ((256, 320), 20), ((0, 160), 150)),             # 448 of 704 and 300 (10 m-tiles: 4 + 3 + 3)
                  (((0, 64), 30), None, ((160, 320), 100))]),
 ])
-def test_step_with_fewer_live_rows_than_it_is_sized_for(d_ffn, tile_rows, requests):
+def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows, requests):
     """Block steps sized for more than 256 rows in which branches have finished, last windows are clipped and only a part
-    of the rows is masked: whole row groups of the layer GEMMs are skipped (gate/up with tiles of 128 and of 192 rows), and
-    the LM head's live m-tiles are dealt to fewer row groups than are launched.  Logits, tokens, K,V and the commit
+    of the rows is masked: whole row groups of the eight-wave GEMM are skipped (gate/up with tiles of 128 and of 192 rows; with
+    32 heads also the q|k|v projection, which stores partial tiles), and the LM head's live m-tiles are dealt to fewer row groups than are launched.  Logits, tokens, K,V and the commit
     against the oracle in fp64, from a poisoned workspace."""
     from paper_2605_29233_amd import BB_INIT, BB_PERIODIC
     from paper_2605_29233_amd.binding import gemm_plan
-    shape = ModelShape("livetest", 2, 256, 4, 4, 64, d_ffn, 1024)
+    shape = ModelShape("livetest", 2, 256, heads, heads, 64, d_ffn, 1024)
     blocks, G, L_p, n = (64, 128, 160), 320, 20, len(requests)
     decode = DecodeParams(0.9, 0.5, 400, 8, 0)
     bound = n * sum(blocks)
     assert gemm_plan(bound, (d_ffn + 63) // 64 * 128, 256, True, True)["mt"] == tile_rows // 32
+    assert (gemm_plan(bound, 3 * 64 * heads, 256, True)["nt"] == 2) == (heads == 32)
     weights = dict(gen_weights(shape, 23))
     om = OracleModel(shape, weights, np.float64)
     print("live rows, ffn", d_ffn, flush=True)
