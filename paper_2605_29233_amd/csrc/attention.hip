@@ -4,10 +4,10 @@
 // folded into the row dimension, so the K/V tiles a wave reads serve all of them), one kv head,
 // one branch segment.  K and V are found page by page (64 tokens) through the branch's page
 // table: shared or private physical row.  Two kernels:
-//   attention_kernel (block steps: few query rows): one tile per workgroup, the waves take the
+//   attention_kernel (block steps, and full passes with few tiles): one tile per workgroup, the waves take the
 //            row's pages round robin, each keeping a running max / sum / output (online
 //            softmax), and the partial results are combined through LDS in a fixed order;
-//   attention_full_kernel (full-sequence passes: many query rows): four tiles per workgroup, one per
+//   attention_full_kernel (full-sequence passes with many tiles): four tiles per workgroup, one per
 //            wave; the waves walk the pages together, through LDS.
 // Either way the result does not depend on scheduling.
 //
@@ -80,8 +80,8 @@ static __device__ __forceinline__ void softmax_page(f32x16 (&s)[2], bool partial
 }
 
 // WAVES waves per workgroup, two per SIMD either way: eight of one workgroup, or four each of two.  What bounds it: the K,V
-// stream, at the HBM's rate where it is long enough, otherwise at what a CU can have in flight (some 64 KB, so about 50 GB/s)
-// and at each wave's own chain of loads, MFMAs and exponentials, which the second wave of its SIMD fills.  So a wave keeps to
+// stream, which short rows and few tiles leave at the 50-60 KB per us that a CU draws by itself (long ones: 4.5 TB/s of 671 MB
+// over 256 workgroups), and each wave's own chain of loads, MFMAs and exponentials, which the second wave of its SIMD fills.  So a wave keeps to
 // 256 registers: two quarters of a K or V page in flight, and Q in LDS (all waves use the same fragments), in the space
 // that the waves' results take after the last page.
 // Measured, us per launch (heads of 128; before = four waves with 512 registers each, half pages in flight): 768 keys, 320 tiles
@@ -258,8 +258,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attention_kernel(Dev D, const h
 // while K is:
 //   [K landed] barrier | request V | scores | barrier | request next K | softmax | [V landed] barrier | P.V
 // Measured, us per launch (heads of 128; before = every wave fetching for itself, one workgroup per CU): 4 x 5120 rows and
-// keys, 32 heads 5443 -> 4041 (1.27 PFLOP/s in MFMAs; the pipes alone sustain 1.67 with such MFMAs at the power limit), 4 x 768
-// 156 -> 118, 3 x 1402 with 28 query and 4 kv heads 327 -> 240; 768 x 768 (192 workgroups) 47 -> 48.
+// keys, 32 heads 5443 -> 4041 (1.27 PFLOP/s in MFMAs; the pipes alone sustain 1.7 with such MFMAs at the power limit), 4 x 768
+// 156 -> 118, 3 x 1402 with 28 query and 4 kv heads 327 -> 240.  (A workgroup alone on its CU is slower so: attention_plan.)
 // A higher wave priority around the MFMAs was slower (4222).
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attention_full_kernel(Dev D, const half_t* __restrict__ Q, u32x4* __restrict__ Apk,

@@ -12,8 +12,8 @@
 #include <vector>
 
 struct LayerW {
-    u32x4 *wqkv, *wo, *wgu, *wdown;     // tiled bf16 (passes with few rows: two bf16 activation terms)
-    u32x4 *wqkv_w, *wo_w, *wgu_w, *wdown_w;     // the same matrices as row-scaled fp16 (wide format, passes with many rows)
+    u32x4 *wqkv, *wo, *wgu, *wdown;     // tiled bf16 (two bf16 activation terms: bb_debug_wide_format(0))
+    u32x4 *wqkv_w, *wo_w, *wgu_w, *wdown_w;     // the same matrices as row-scaled fp16 (wide format: the layer GEMMs of every pass)
     float *s_qkv, *s_o, *s_gu, *s_down; // 2^-S per weight row of the wide-format copies
     float *g_attn, *g_ffn, *bqkv;       // fp32
 };
@@ -468,8 +468,8 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
     const int d = m.d_model, nq = m.n_q_heads * m.head_dim, f = m.d_ffn, nqkv = D.nqkv, ngu = c->ngu;
     const int mt = (rows_cap + 31) / 32, rows_pad = mt * 32;
     const int gk = rows_cap <= BB_SKINNY_ROWS ? BB_K_GEMM_SKINNY : BB_K_GEMM_WIDE;
-    // many rows: the layer GEMMs are bound by the matrix pipes and run in the wide format (every kernel that writes
-    // a panel for them is told so); the LM head keeps two bf16 terms (its rows are the masked ones only)
+    // the layer GEMMs run in the wide format (every kernel that writes a panel for them is told so); the LM head keeps two
+    // bf16 terms (its rows are the masked ones only)
     const int wide = !c->wide_off;
     const bool defer = rows_cap <= BB_DEFER_ROWS;     // block steps of at most 128 rows: every gate/up GEMM has a k split, its consumer is the SwiGLU kernel
     // kind: 0 LM head, 1 O/down, 2 gate/up, 3 QKV (index of the tuning overrides)

@@ -84,7 +84,7 @@ static inline __host__ __device__ size_t tileW_u4(int n, int k8, int ksteps) {
     return ((size_t)nt * ksteps + kstep) * 64 + lane;
 }
 
-// ---- wide format: fp16 + fp8 operands for the GEMMs of passes with many rows ----------------------------------
+// ---- wide format: fp16 + fp8 operands of the layer GEMMs -------------------------------------------------------
 // Passes over hundreds of rows are not bound by the weight stream but by what the L2 delivers to a CU and by the
 // matrix pipes, and there the second bf16 term costs a whole second pass.  Instead: activation x = hi + lo with
 // hi = fp16(x) (11 bits) and the remainder (|lo| <= 2^-12 |x|) as e5m2(lo * 2^BB_LO_SHIFT), 3 bytes per element
@@ -248,7 +248,7 @@ void launch_pack_rows(const float* A, int M, int K, u32x4* Apk, int mt_total, hi
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out = nullptr, LaunchStamps st = LaunchStamps(),
                       const float* ssq = nullptr, int nblk = 0, float rms_eps = 0.f, const int* rows_live = nullptr);
-// The same for passes with many rows: eight waves per workgroup, tile 32 plan.mt rows x 256 columns (plan.nt == 2, plan.mt 4 or
+// The same for more than 256 rows (plan.wv == 8): eight waves per workgroup, tile 32 plan.mt rows x 256 columns (plan.nt == 2, plan.mt 4 or
 // 6).  rows_live (device, may be null): row count of this pass; row groups past it are skipped.
 void launch_gemm_many(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
                       hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st = LaunchStamps());

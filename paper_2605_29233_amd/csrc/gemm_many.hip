@@ -1,9 +1,9 @@
-// Wide-format MFMA GEMM for passes with many activation rows (full-sequence refresh, initial forward, many requests):
+// Wide-format MFMA GEMM for passes of more than 256 activation rows (full-sequence refresh, initial forward, many requests):
 //     C[m][n] = sum_k A[m][k] * W[n][k]          (operands and precision as in gemm_wide.hip)
 //
-// What bounds it: power.  With random operands the chip sustains 1.67 PFLOP/s of nothing but 32x32x16 fp16 MFMAs (at
-// 1.65 GHz) but 1.90 of 16x16x32 ones, whose fp32 accumulators pass half as often per product; for the mix of four fp16
-// and one fp8 step 1.75 and 1.94 (in bf16 equivalents).  So this kernel computes in 16 x 16 tiles (16x16x32 fp16,
+// What bounds it: power.  With random operands the chip sustains 1.7 PFLOP/s of nothing but 32x32x16 fp16 MFMAs but 1.95
+// of 16x16x32 ones, whose fp32 accumulators pass half as often per product; for the mix of four fp16 and one fp8 step
+// 1.84 and 2.07 (in bf16 equivalents).  So this kernel computes in 16 x 16 tiles (16x16x32 fp16,
 // 16x16x128 fp8), keeps an operand for consecutive MFMAs, and moves as little as it can: a kernel with 32 x 32 tiles
 // that kept the pipes busier than the one before it ran no faster, its clock fell instead.
 // Eight waves per workgroup, two per SIMD: one wave per SIMD left the matrix pipe idle at every wait.  Workgroup tile =
@@ -11,7 +11,9 @@
 // operands reach LDS by direct-to-LDS loads, which pass through no register.
 // Measured (3072 rows; before = four waves, 32 x 32 tiles, weights in registers): gate/up with SwiGLU (24576 x 4096)
 // 775 -> 700 us, down (4096 x 12288) 370 -> 332 us, 1.33 PFLOP/s in bf16 equivalents; 20480 rows of gate/up 5.13 -> 4.61 ms;
-// 4206 rows, 3584 x 18944: 861 -> 665 us.  The matrix pipes are busy 0.81 of the cycles at 1.71 GHz (0.66 at 1.74).
+// 4206 rows, 3584 x 18944: 861 -> 665 us.  The matrix pipes are busy 0.65 of the elapsed cycles at 1.9 GHz (0.60 before;
+// counters, every launch alone), 0.73 of those in which its waves are resident (0.66).
+// Small matrices, whose tiles leave most CUs without work, go to gemm_wide_kernel (gemm_plan_wide has the rule).
 #include "bb_internal.h"
 #include "lds.h"
 #include <hip/hip_ext.h>

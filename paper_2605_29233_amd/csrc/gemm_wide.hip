@@ -10,10 +10,11 @@
 // weights stream L2 -> registers in a ring.  A workgroup walks its (column group, row group) tiles
 // with the grid's stride.
 //
-// What bounds it: the weight stream, through the loads a CU can have in flight.  Some 64 KB per CU whatever the ring's
-// depth, so 45-60 GB/s per CU at the latency of a loaded HBM, of which a 256-column tile of 128 rows spends 24 of every
-// 56 KB on activations; with few rows also the issue of MFMAs and LDS reads.  Hence a body per number of m-tiles: rows
-// that are not there are neither fetched nor multiplied.  Measured, us per launch, body of 4 -> of 1 m-tile at
+// What bounds it: what a CU draws, 30 KB per us of HBM lines with all 256 at it, 60 with 128, 92 with 64, however much more
+// than 32 KB is requested ahead (plain load loops), of which a 256-column tile of 128 rows spends 24 of every
+// 56 KB on activations; with few rows also the issue of MFMAs and LDS reads.  Hence a body per number of m-tiles: m-tiles past
+// the rows the launch is sized for are neither fetched nor multiplied.  (Rows of finished branches and clipped windows inside
+// them are: the kernel does not read the live row count.)  Measured, us per launch, body of 4 -> of 1 m-tile at
 // 32 rows: 12288 x 4096 26.7 -> 19.9, 24576 x 4096 45.0 -> 33.8, 4096 x 12288 27.6 -> 18.7 (5.4 TB/s; reading the weights
 // alone takes 17.6); of 2 at 56 rows: 27.5 -> 22.0, 45.5 -> 39.4, 27.6 -> 20.7; of 3 at 96 rows: 29.2 -> 24.0, 43.4 -> 41.6.
 #include "bb_internal.h"
@@ -357,7 +358,9 @@ static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
 // round: 198 of the CUs have work instead of 148 (37888 x 3584, 56 rows, with SwiGLU: 50.1 against 57.5 us; at 120 rows, where
 // the waves' own work sets the pace, 74.2 against 68.2).
 //
-// 65 to 256 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 and 240 rows:
+// 65 to 256 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 and 240 rows (the
+// bodies of three m-tiles, 65 to 96 and 129 to 192 rows, by one common factor; whole block steps at 72, 96, 160, 176, 192 and 208
+// rows were 1.01 to 1.28 times as fast as under the rule before it, at d 256, 3584 and 4096):
 // time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of everything the L2s
 // deliver, 15 TB/s), 6 us of prologue and store per tile, and the partial tiles, written here and read by the consumer.
 // (12288 x 4096 at 120 rows: four splits on 192 CUs 27.6 us, five on 240 27.5 and a longer consumer; 4096 x 4096 at 240 rows:
