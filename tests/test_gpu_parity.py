@@ -174,6 +174,15 @@ def test_full_pass_attention_tiles(prompt_len, gen_len, head_dim, n_kv_heads):
     check_report(s)
 
 
+def test_full_pass_with_pages_split_over_workgroups():
+    """704 rows against as many keys with two heads: 44 tiles, so a full pass also cuts the 11 pages of the row into ranges of 4, 4
+    and 3 that three workgroups share.  A refresh before every step, against the oracle in fp64."""
+    shape = ModelShape("fullsplit", 2, 256, 2, 2, 128, 688, 1024)
+    s = run_case(shape, DecodeParams(0.9, 0.5, 4, 1, 0), 448, 256, (256,), seed=24, max_steps=2, attention=((704,), (3, 4)))
+    assert s.rep.max_logit_err <= 3e-2
+    check_report(s)
+
+
 @pytest.mark.parametrize("prompt_len,head_dim,splits,waves", [
     (192, 64, 1, 4), (192, 128, 1, 4), (449, 64, 1, 4), (449, 128, 3, 4), (960, 64, 4, 4), (960, 128, 4, 4), (961, 64, 3, 8), (961, 128, 3, 8)])
 def test_block_step_attention_waves_and_splits(prompt_len, head_dim, splits, waves):
