@@ -360,7 +360,7 @@ static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
 //
 // 65 to 256 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 and 240 rows (the
 // bodies of three m-tiles, 65 to 96 and 129 to 192 rows, by one common factor; whole block steps at 72, 96, 160, 176, 192 and 208
-// rows were 1.01 to 1.28 times as fast as under the rule before it, at d 256, 3584 and 4096):
+// rows are 1.01 to 1.30 times as fast as before this rule and the row-tile bodies, at d 256, 3584 and 4096):
 // time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of everything the L2s
 // deliver, 15 TB/s), 6 us of prologue and store per tile, and the partial tiles, written here and read by the consumer.
 // (12288 x 4096 at 120 rows: four splits on 192 CUs 27.6 us, five on 240 27.5 and a longer consumer; 4096 x 4096 at 240 rows:

@@ -5,6 +5,7 @@
 // One 1 KiB fragment (64 lanes x 16 bytes) from src to the LDS byte offset dst without passing through registers; OFF is
 // added on both sides.  Written as assembly because the compiler, where it knows of such loads, lets every LDS read
 // wait for all outstanding ones: the waits for these loads are the explicit ones at the barriers.
+// (The compiler warns that m0 is one of its own registers.  That is why it is told: what it keeps there is overwritten.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <int OFF> static __device__ __forceinline__ void load_to_lds(const char* src, unsigned lane16, unsigned dst) {
