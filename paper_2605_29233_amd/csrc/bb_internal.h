@@ -142,14 +142,6 @@ static inline __host__ __device__ float bf16_to_f32(uint16_t b) {
 }
 
 // ---- fp8 encodings (round to nearest even, finite inputs) ---------------------------------------------------
-// e5m2 is the upper byte of an fp16 value; values beyond its largest finite one (57344) saturate.
-static inline __device__ uint8_t f32_to_e5m2(float x) {
-    const half_t h = (half_t)x;
-    const uint16_t b = *reinterpret_cast<const uint16_t*>(&h);
-    uint16_t r = (uint16_t)((b & 0x7FFFu) + 0x7Fu + ((b >> 8) & 1u)) >> 8;
-    if (r > 0x7Bu) r = 0x7Bu;
-    return (uint8_t)(r | ((b >> 8) & 0x80u));
-}
 // e4m3 (bias 7, no infinities, largest finite value 448, subnormals are multiples of 2^-9); saturates.
 static inline __host__ __device__ uint8_t f32_to_e4m3(float x) {
     union { float f; uint32_t u; } v; v.f = x;
@@ -176,15 +168,26 @@ static __device__ __forceinline__ void store_panel8(u32x4* Apk, int m, int k8, i
         Apk[packA_u4(m, k8, mt_total, 1)] = *reinterpret_cast<u32x4*>(lo);
     } else {
         typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+        typedef short i16x2_t __attribute__((ext_vector_type(2)));
         f16x8_t hi;
-        uint32_t lo0 = 0u, lo1 = 0u;
+        float r[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float x = fminf(fmaxf(y[j], -65504.0f), 65504.0f);
             hi[j] = (half_t)x;
-            const uint32_t b = f32_to_e5m2((x - (float)hi[j]) * (float)(1 << BB_LO_SHIFT));
-            if (j < 4) lo0 |= b << (8 * j); else lo1 |= b << (8 * (j - 4));
+            r[j] = x - (float)hi[j];
         }
+        // |r| <= 2^4, far inside e5m2's range; the hardware divides by its scale operand and rounds to nearest even, once
+        const float sc = 1.0f / (float)(1 << BB_LO_SHIFT);
+        uint32_t lo[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            i16x2_t a = {0, 0};
+            a = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(a, r[4 * q], r[4 * q + 1], sc, false);
+            a = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(a, r[4 * q + 2], r[4 * q + 3], sc, true);
+            lo[q] = __builtin_bit_cast(uint32_t, a);
+        }
+        const uint32_t lo0 = lo[0], lo1 = lo[1];
         Apk[wideA_hi_u4(m, k8, mt_total)] = __builtin_bit_cast(u32x4, hi);
         *reinterpret_cast<uint2*>(reinterpret_cast<char*>(Apk) + wideA_lo_byte(m, k8, mt_total)) = make_uint2(lo0, lo1);
     }
@@ -226,7 +229,7 @@ static __device__ __forceinline__ MSI msi_merge(MSI a, MSI b) {
 }
 
 // ---- kernel launchers (each enqueues on `s`) -----------------------------------------------------
-struct GemmPlan { int split_k; int chunks_per_split; int nt; int mt = 4; int wv = 4; };      // mt: m-tiles of 32 rows per workgroup; wv: its waves (wide format: 3 or 4, 8 = gemm_many_kernel)
+struct GemmPlan { int split_k; int chunks_per_split; int nt; int mt = 4; int wv = 4; bool rounds = false; };      // mt: m-tiles of 32 rows per workgroup; wv: its waves; rounds: (tile, split) items in as many rounds as it takes
 GemmPlan gemm_plan(int m_rows, int N, int K, int forced_split, int forced_nt);
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable = false);     // wide-format kernel: may take mt = 6
 // Epilogue of launch_gemm: partial tiles P[split][m][n] (default); SiLU(gate) * up as the down projection's panel
@@ -248,10 +251,10 @@ void launch_pack_rows(const float* A, int M, int K, u32x4* Apk, int mt_total, hi
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out = nullptr, LaunchStamps st = LaunchStamps(),
                       const float* ssq = nullptr, int nblk = 0, float rms_eps = 0.f, const int* rows_live = nullptr);
-// The same for more than 256 rows (plan.wv == 8): eight waves per workgroup, tile 32 plan.mt rows x 256 columns (plan.nt == 2, plan.mt 4 or
-// 6).  rows_live (device, may be null): row count of this pass; row groups past it are skipped.
-void launch_gemm_many(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
-                      hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st = LaunchStamps());
+// The same for more than 128 rows (plan.mt 3, 4 or 6 m-tiles, plan.nt column tiles per wave).  rows_live (device, may be null): row
+// count of this pass; row groups past it are skipped.
+void launch_gemm_panel(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
+                       hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps);
 void launch_tile_weights_wide(const uint16_t* src, int rows, int K, u32x4* dst, float* scale_out, int dst_row0, int interleave,
                               hipStream_t s);
 void launch_pack_rows_wide(const float* A, int M, int K, u32x4* Apk, int mt_total, hipStream_t s);

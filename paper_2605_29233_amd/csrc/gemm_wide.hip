@@ -1,5 +1,4 @@
-// Wide-format MFMA GEMM for passes of up to 256 rows (block steps), and of more rows over small matrices; gemm_many.hip
-// takes the others:
+// Wide-format MFMA GEMM for passes of up to 128 rows (block steps); gemm_panel.hip takes the others:
 //     C[m][n] = sum_k A[m][k] * W[n][k]          (fp32 accumulate)
 // with the operands in the wide format of bb_internal.h: the activation as fp16 + a scaled e5m2 remainder, the
 // weight as row-scaled fp16, converted in registers to e4m3 for the remainder's product.  Per 64 k and 32x32 tile
@@ -7,8 +6,9 @@
 // accuracy of about 2^-16 per product.  Structure as the two-term
 // kernel: C^T tiles with the weight fragment as the MFMA A-operand, one workgroup per CU, four waves that own
 // 32 * NT weight rows each and share the activation chunk (32 MT rows x 64 k = 6 MT KiB) through LDS stages;
-// weights stream L2 -> registers in a ring.  A workgroup walks its (column group, row group) tiles
-// with the grid's stride.
+// weights stream HBM -> registers in a ring.  A workgroup walks its column groups with the grid's stride.  (The kernel of
+// gemm_panel.hip keeps fewer weights on their way and is slower where the weight stream sets the pace: block steps of 120 rows 5.9 ms
+// with this one, 6.1 with that; of 252 rows 4.9 with this one in two row groups, 4.7 with that.)
 //
 // What bounds it: what a CU draws, 30 KB per us of HBM lines with all 256 at it, 60 with 128, 92 with 64, however much more
 // than 32 KB is requested ahead (plain load loops), of which a 256-column tile of 128 rows spends 24 of every
@@ -23,6 +23,7 @@
 #include <hip/hip_ext.h>
 #include <type_traits>
 #include <algorithm>
+#include <cmath>
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -71,14 +72,14 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
 }
-template <int NT, int EPI, bool STREAM, int MT, int WAVES>
+template <int NT, int EPI, int MT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* __restrict__ Wt, const float* __restrict__ wscale,
                                                            const u32x4* __restrict__ Apk, float* __restrict__ P,
                                                            size_t split_stride, int ldp, int mt_total, int n_tiles,
-                                                           int total_chunks, int chunks_per_split, int tiles_x, int tiles_y,
+                                                           int total_chunks, int chunks_per_split, int tiles_x,
                                                            u32x4* __restrict__ Opk, const float* __restrict__ ssq, int nblk,
                                                            float inv_d, float eps) {
-    static_assert(NT >= 1 && NT <= 3 && NT * MT <= 12, "one to three weight tiles per wave, at most 12 accumulator tiles");
+    static_assert(NT >= 1 && NT <= 2 && MT >= 1 && MT <= 4, "one or two weight tiles per wave, one to four m-tiles");
     constexpr int THREADS = 64 * WAVES;
     constexpr int WCHUNK_U4 = MT * BB_WFRAGS * 64;          // uint4 per staged activation chunk (6 KiB per m-tile)
     constexpr int WA_PER_THREAD = (WCHUNK_U4 + THREADS - 1) / THREADS;  // (an odd MT: the last half piece repeats valid data past the chunk's end)
@@ -90,19 +91,18 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     __shared__ u32x4 lds_raw[STAGES_U4 > SLICES_U4 ? STAGES_U4 : SLICES_U4];
     u32x4 (*lds)[WA_PER_THREAD * THREADS] = reinterpret_cast<u32x4 (*)[WA_PER_THREAD * THREADS]>(lds_raw);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // STREAM (one row group: every weight line is used once): weight loads carry the non-temporal hint, and with a k
-    // split the (column group, split) items are dealt to the 8 XCDs in contiguous runs in split-major order, so that an
-    // XCD's workgroups share one or two k ranges of the activation panel (as in the two-term kernel).
+    // Weight loads carry the non-temporal hint (every line is used once), and with a k split the (column group, split) items
+    // are dealt to the 8 XCDs in contiguous runs in split-major order, so that an XCD's workgroups share one or two k ranges of
+    // the activation panel (as in the two-term kernel).
     int first_tile = blockIdx.x, split_id = blockIdx.z;
-    if (STREAM && gridDim.z > 1 && tiles_y == 1) {
+    if (gridDim.z > 1) {
         const int n = gridDim.x * gridDim.z, lin = blockIdx.x + gridDim.x * blockIdx.z, e = lin & 7;
         const int item = e * (n >> 3) + min(e, n & 7) + (lin >> 3);
         first_tile = item % gridDim.x;
         split_id = item / gridDim.x;
     }
-    for (int tile = first_tile; tile < tiles_x * tiles_y; tile += gridDim.x) {
-    const int bx = tile % tiles_x, by = tile / tiles_x;
-    const int mt0 = by * MT;
+    for (int bx = first_tile; bx < tiles_x; bx += gridDim.x) {
+    constexpr int mt0 = 0;
     const int mt_cnt = min(MT, mt_total - mt0);
     const int c0 = split_id * chunks_per_split;
     const int c1 = min(c0 + chunks_per_split, total_chunks);
@@ -133,8 +133,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
         for (int f = f_lo; f < f_hi; ++f)
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                if constexpr (STREAM) w[f][t] = __builtin_nontemporal_load(wbase[t] + off + f * 64);
-                else w[f][t] = wbase[t][off + f * 64];      // plain loads: the row groups of an XCD share these lines through its L2
+                w[f][t] = __builtin_nontemporal_load(wbase[t] + off + f * 64);
             }
     };
     auto read_bh = [&](u32x4 (&b)[MT], int stage, int k) {
@@ -321,29 +320,53 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     }
 }
 
-// Up to 256 rows: row groups of at most four m-tiles, dealt evenly, each computed by the body for that number (384-column tiles
-// have the body of four only).
+// Up to 256 rows: row groups of at most four m-tiles, dealt evenly (384-column tiles have the body of four only).
 static int block_step_body(int mt_total, int nt) {
     const int groups = (mt_total + 3) / 4;
     return nt == 3 ? 4 : (mt_total + groups - 1) / groups;
 }
 
-static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
-    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, groups = (mt_total + 3) / 4, body = block_step_body(mt_total, 1);
+static GemmPlan plan_one_group(int mt_total, int N, int K, bool fusable) {
+    const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
     double best_t = 1e30;
-    for (int nt = 1; nt <= (groups > 1 ? 3 : 2); ++nt) {
+    for (int nt = 1; nt <= 2; ++nt) {
         if (nt > 1 && n_tiles < 4 * nt) continue;
-        const int base = (n_tiles + 4 * nt - 1) / (4 * nt) * groups;
+        const int base = (n_tiles + 4 * nt - 1) / (4 * nt);
         for (int sp = 1; sp <= BB_MAX_SPLITK && sp <= std::max(1, total_chunks / 4) && (sp == 1 || base * sp <= 256); ++sp) {
             const int cps = (total_chunks + sp - 1) / sp;
             if ((total_chunks + cps - 1) / cps != sp) continue;
-            const double live = std::min(base * sp, 256), weights_kb = 16.4 * nt, acts_kb = 6.1 * body;
-            const double own_us = (nt == 1 ? 0.68 : nt == 2 ? (groups > 1 ? 1.15 : 1.08) : 1.95) * (body == 4 ? 1.0 : 0.88);
-            const double chunk_us = std::max(own_us, live * std::max(weights_kb / groups / 6.0e3, (weights_kb + acts_kb) / 15e3));
+            const double live = std::min(base * sp, 256), weights_kb = 16.4 * nt, acts_kb = 6.1 * mt_total;
+            const double own_us = (nt == 1 ? 0.68 : 1.08) * (mt_total == 4 ? 1.0 : 0.88);
+            const double chunk_us = std::max(own_us, live * std::max(weights_kb / 6.0e3, (weights_kb + acts_kb) / 15e3));
             const bool fused = fusable && sp == 1 && nt == 2;
             const double partial_mb = (double)sp * mt_total * 32 * N * 4e-6;
             const double t = ((base * sp + 255) / 256) * (cps * chunk_us + 6.0) + (fused ? 3.0 : 0.34 * partial_mb + (fusable ? 8.0 : 0.0));
+            if (t < best_t) { best_t = t; best.nt = nt; best.split_k = sp; best.chunks_per_split = cps; }
+        }
+    }
+    return best;
+}
+
+static GemmPlan plan_two_groups(int mt_total, int N, int K, bool fusable) {
+    const int n_tiles = N / 32, total_chunks = (K + 63) / 64, groups = 2;
+    GemmPlan best;
+    double best_t = 1e30;
+    for (int nt = 1; nt <= 3; ++nt) {
+        if (nt > 1 && n_tiles < 4 * nt) continue;
+        const int body = block_step_body(mt_total, nt), base = (n_tiles + 4 * nt - 1) / (4 * nt) * groups;
+        const double own = body == 3 ? (nt == 1 ? 0.535 : 0.80) : nt == 1 ? 0.60 : nt == 2 ? 0.93 : 1.43;
+        for (int sp = 1; sp <= BB_MAX_SPLITK && sp <= std::max(1, total_chunks / 4) && (sp == 1 || base * sp <= 256); ++sp) {
+            const int cps = sp == 1 ? total_chunks : ((total_chunks + sp - 1) / sp + 1) / 2 * 2;
+            if ((total_chunks + cps - 1) / cps != sp) continue;
+            const int items = base * sp;
+            const double live = std::min(items, 256), fill = live / 256, last = (items % 256) / 256.0;
+            const double own_us = own * (nt == 1 ? 1.0 : 1.0 + 0.126 * fill * fill);
+            const double fetch_us = live * (16.4 * nt / groups / 7.46e3 + 6.1 * body / 18.3e3);
+            const double rounds = items <= 256 ? 1.0 : items / 256 + (last > 0 ? 0.62 + 0.38 * last : 0.0);
+            const bool fused = fusable && sp == 1 && nt == 2;
+            const double partial_mb = fused ? 0.0 : (double)sp * mt_total * 32 * N * 4e-6;
+            const double t = rounds * (cps * sqrt(own_us * own_us + fetch_us * fetch_us) + 0.47 * nt * body) + 0.22 * partial_mb + (fusable && !fused ? 8.0 : 0.0);
             if (t < best_t) { best_t = t; best.nt = nt; best.split_k = sp; best.chunks_per_split = cps; }
         }
     }
@@ -358,26 +381,28 @@ static GemmPlan plan_block_step(int mt_total, int N, int K, bool fusable) {
 // round: 198 of the CUs have work instead of 148 (37888 x 3584, 56 rows, with SwiGLU: 50.1 against 57.5 us; at 120 rows, where
 // the waves' own work sets the pace, 74.2 against 68.2).
 //
-// 65 to 256 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 and 240 rows (the
-// bodies of three m-tiles, 65 to 96 and 129 to 192 rows, by one common factor; whole block steps at 72, 96, 160, 176, 192 and 208
-// rows are 1.01 to 1.30 times as fast as before this rule and the row-tile bodies, at d 256, 3584 and 4096):
-// time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of everything the L2s
-// deliver, 15 TB/s), 6 us of prologue and store per tile, and the partial tiles, written here and read by the consumer.
-// (12288 x 4096 at 120 rows: four splits on 192 CUs 27.6 us, five on 240 27.5 and a longer consumer; 4096 x 4096 at 240 rows:
-// 128 columns in four splits 19.4 us, 256 in eight 21.2 and twice the partial tiles; 37888 x 3584 at 240 rows: one round of
-// 384 columns 117 us and a SwiGLU launch, two rounds with SwiGLU in the epilogue 147.)
+// 65 to 128 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 rows (the body of three
+// m-tiles by one common factor): time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of
+// everything the L2s deliver, 15 TB/s), 6 us of prologue and store per tile, and the partial tiles, written here and read by the
+// consumer.  (12288 x 4096 at 120 rows: four splits on 192 CUs 27.6 us, five on 240 27.5 and a longer consumer.)
 //
-// With more rows the candidates of gemm_many_kernel (128 or 192 rows per
-// workgroup, k split) are priced by a model fitted to 800 measured launches (272..4206 rows, N 3584..37888, K
-// 3584..18944; 4.6 % rms): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
+// 129 to 256 rows, two row groups of gemm_panel_kernel: the same by a model of 1486 measured launches (72..256 rows, N 256..37888, K
+// 256..18944; 6 % rms): a chunk takes the root of the squares of the waves' own work and of its share of what HBM (7.5 TB/s, each
+// weight line once) and the L2s (18 TB/s) deliver; partial tiles cost 0.07 us per MB here and 0.15 in the consumer.  Its choice costs 0.6 % more
+// than the best of the measured plans (37888 x 3584 at 240 rows: one round of 384 columns 119 us and a SwiGLU launch, two of 256
+// columns with SwiGLU in the epilogue 148; 24576 x 4096 in one round of 256 columns 84).  Splits take whole units of 128 k.
+//
+// With more rows tiles of 128 or 192 rows x 256 columns and their k splits
+// are priced by a model fitted to 800 measured launches of the kernel before this one (272..4206 rows, N 3584..37888, K
+// 3584..18944; 4.6 % rms; the present one takes 2 to 7 % less at every one of them): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
 // workgroups except that a last round which leaves CUs idle runs at a higher clock (the chip is at its power limit), and
-// the partial tiles, written here and read by the consumer launch once per k split.  Splits take whole units of 128 k.
+// the partial tiles, written here and read by the consumer launch once per k split.
 // Where both tiles price within 5 % the larger one is taken: it fetches a fifth less per product.  fusable: the caller
 // can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
-// Beside them this file's kernel with tiles of 128 columns, where they and their k splits fit one round: small matrices leave
-// most CUs without work either way, and the smaller tile with fewer waves is through sooner.  Its price is fitted to 175
-// shapes (272..4096 rows, N 128..4096, K 64..4096) measured with both; us of eight waves / of four: 768 x 256 at 384 rows 8.3 /
-// 6.5, 256 x 688 9.7 / 7.6, 256 x 2048 8.5 / 6.9, 4096 x 512 at 640 rows 11.7 / 10.6, but 768 x 4096 15.2 / 17.9, 4096 x 4096 37 / 49.
+// Beside them tiles of 128 columns, where they and their k splits fit one round: small matrices leave
+// most CUs without work either way, and the smaller tile is through sooner.  Its price is fitted to 175
+// shapes (272..4096 rows, N 128..4096, K 64..4096); us of 256 / of 128 columns: 768 x 256 at 512 rows 8.8 /
+// 5.9, 256 x 688 at 1024 rows 9.1 / 6.2, 1408 x 256 at 1536 rows 9.9 / 7.2, but 3584 x 3584 at 1024 rows 37 / 46.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
     if (mt_total <= 8) {
@@ -386,18 +411,18 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
         else if (mt_total <= 2) {
             p = gemm_plan(m_rows, N, K, 0, (N / 32 + 3) / 4 <= 256 ? 1 : 0);
             if (p.nt == 2 && p.split_k == 1 && (N / 32 + 5) / 6 <= 256) p.wv = 3;
-        } else p = plan_block_step(mt_total, N, K, fusable);
+        } else p = mt_total <= 4 ? plan_one_group(mt_total, N, K, fusable) : plan_two_groups(mt_total, N, K, fusable);
         p.mt = block_step_body(mt_total, p.nt);
         return p;
     }
     if (forced_split > 0) {
         GemmPlan p = gemm_plan(m_rows, N, K, forced_split, forced_nt);
-        p.wv = 8;
+        p.rounds = true;
         return p;
     }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
-    best.nt = 2; best.wv = 8;
+    best.nt = 2; best.rounds = true;
     double best_t = 1e30;
     for (int mt = 4; mt <= 6; mt += 2) {
         const double chunk_us = mt == 6 ? 1.67 : 1.18, tile_us = 3.8;
@@ -418,7 +443,7 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
         if ((total_chunks + cps - 1) / cps != sp) continue;
         const double fill = base * sp / 256.0, partial = sp * (double)mt_total * 32 * N * 4 * (sp == 1 ? 0.166e-6 : 0.25e-6);
         const double t = 4.0 + cps * 0.585 * (1.0 + 0.8 * fill * fill * fill) + partial + (fusable ? 8.0 : 0.0);
-        if (t < best_t) { best_t = t; best.split_k = sp; best.chunks_per_split = cps; best.nt = 1; best.wv = 4; best.mt = block_step_body(mt_total, 1); }
+        if (t < best_t) { best_t = t; best.split_k = sp; best.chunks_per_split = cps; best.nt = 1; best.rounds = false; best.mt = block_step_body(mt_total, 1); }
     }
     return best;
 }
@@ -426,26 +451,26 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps,
                       const int* rows_live) {
-    if (plan.wv == 8) { launch_gemm_many(Wt, wscale, Apk, P, mt_total, N, K, plan, s, rows_live, swiglu_out, st); return; }
+    if (mt_total > 4 || plan.nt == 3) {
+        launch_gemm_panel(Wt, wscale, Apk, P, mt_total, N, K, plan, s, mt_total > 8 ? rows_live : nullptr, swiglu_out, st, ssq, nblk, rms_eps);
+        return;
+    }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64, nt = plan.nt;
-    const int m_groups = (mt_total + 3) / 4, mt = block_step_body(mt_total, nt);
     const size_t split_stride = (size_t)mt_total * 32 * N;
     const int tiles_x = (n_tiles + plan.wv * nt - 1) / (plan.wv * nt);
-    dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);
-#define WARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, tiles_x, m_groups, swiglu_out, ssq, nblk, 1.0f / (float)K, rms_eps
-#define WLAUNCH(NT_, EPI_, ST_, MT_, WV_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, ST_, MT_, WV_>), grid, dim3(64 * WV_), 0, s, st.start, st.stop, 0, WARGS)
+    dim3 grid(std::min(tiles_x, 256), 1, plan.split_k);
+#define WARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, tiles_x, swiglu_out, ssq, nblk, 1.0f / (float)K, rms_eps
+#define WLAUNCH(NT_, EPI_, MT_, WV_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_wide_kernel<NT_, EPI_, MT_, WV_>), grid, dim3(64 * WV_), 0, s, st.start, st.stop, 0, WARGS)
 #define WLAUNCH_MT(NT_, EPI_) do { \
-        if (m_groups > 1) { if (mt == 3) WLAUNCH(NT_, EPI_, false, 3, 4); else WLAUNCH(NT_, EPI_, false, 4, 4); } \
-        else if (mt == 1) WLAUNCH(NT_, EPI_, true, 1, 4); \
-        else if (mt == 2) WLAUNCH(NT_, EPI_, true, 2, 4); \
-        else if (mt == 3) WLAUNCH(NT_, EPI_, true, 3, 4); \
-        else WLAUNCH(NT_, EPI_, true, 4, 4); \
+        if (mt_total == 1) WLAUNCH(NT_, EPI_, 1, 4); \
+        else if (mt_total == 2) WLAUNCH(NT_, EPI_, 2, 4); \
+        else if (mt_total == 3) WLAUNCH(NT_, EPI_, 3, 4); \
+        else WLAUNCH(NT_, EPI_, 4, 4); \
     } while (0)
     if (plan.wv == 3) {
-        if (swiglu_out) { if (mt == 1) WLAUNCH(2, WEPI_SWIGLU, true, 1, 3); else WLAUNCH(2, WEPI_SWIGLU, true, 2, 3); }
-        else { if (mt == 1) WLAUNCH(2, WEPI_PARTIAL, true, 1, 3); else WLAUNCH(2, WEPI_PARTIAL, true, 2, 3); }
+        if (swiglu_out) { if (mt_total == 1) WLAUNCH(2, WEPI_SWIGLU, 1, 3); else WLAUNCH(2, WEPI_SWIGLU, 2, 3); }
+        else { if (mt_total == 1) WLAUNCH(2, WEPI_PARTIAL, 1, 3); else WLAUNCH(2, WEPI_PARTIAL, 2, 3); }
     } else if (swiglu_out) WLAUNCH_MT(2, WEPI_SWIGLU);
-    else if (nt == 3) { if (m_groups > 1) WLAUNCH(3, WEPI_PARTIAL, false, 4, 4); else WLAUNCH(3, WEPI_PARTIAL, true, 4, 4); }
     else if (nt == 2) WLAUNCH_MT(2, WEPI_PARTIAL);
     else WLAUNCH_MT(1, WEPI_PARTIAL);
 #undef WLAUNCH_MT

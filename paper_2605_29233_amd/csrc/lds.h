@@ -12,10 +12,10 @@ template <int OFF> static __device__ __forceinline__ void load_to_lds(const char
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
                  ::"s"(dst), "v"(lane16), "s"(src), "n"(OFF) : "m0", "memory");
 }
-// The same by the first N waves only (a branch inside the assembly: one in the loop body would split the pipeline's block).
-template <int N> static __device__ __forceinline__ void load_to_lds_first(int wave, const char* src, unsigned lane16, unsigned dst) {
+// The same if i < n only (a branch inside the assembly: one in the loop body would split the pipeline's block).
+static __device__ __forceinline__ void load_to_lds_below(unsigned i, unsigned n, const char* src, unsigned lane16, unsigned dst) {
     asm volatile("s_cmp_ge_u32 %3, %4\n\ts_cbranch_scc1 1f\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n1:"
-                 ::"s"(dst), "v"(lane16), "s"(src), "s"(wave), "n"(N) : "m0", "scc", "memory");
+                 ::"s"(dst), "v"(lane16), "s"(src), "s"(i), "s"(n) : "m0", "scc", "memory");
 }
 #pragma clang diagnostic pop
 // Between the stores and the loads by which the lanes of one wave exchange data through a slice of LDS that is theirs.  The

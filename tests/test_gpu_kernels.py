@@ -130,6 +130,30 @@ def test_small_matrices_of_many_rows(bb, M, N, K):
     assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
 
 
+@pytest.mark.parametrize("M,N,K,nt,mt", [
+    (129, 32, 64, 1, 3),            # five m-tiles: 3 + 2; one column tile, half a unit
+    (160, 96, 688, 1, 3),           # two splits of three units, the last one padded; waves without a column tile
+    (193, 32, 1088, 1, 4),          # seven m-tiles: 4 + 3
+    (129, 16416, 192, 2, 3),        # a unit and a half; a last column group of one tile
+    (256, 16416, 192, 2, 4),
+    (225, 32992, 192, 3, 4),        # 384 columns; eight m-tiles, the last one of one row
+])
+def test_two_row_groups_at_the_edges_of_their_tiles(bb, M, N, K, nt, mt):
+    """129 to 256 rows: every tile the plan can take, where units, k splits, row and column groups end: against fp64,
+    bound as in test_wide_format_gemm_matches_fp64."""
+    from paper_2605_29233_amd.binding import gemm_plan
+    p = gemm_plan(M, N, K, wide=True)
+    assert (p["nt"], p["mt"]) == (nt, mt), p
+    rng = np.random.default_rng(M * 19 + K)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    Wb = gen_normal_bf16(4, f"g{N}x{K}", N * K, 0.05).view(torch.int16).numpy().view(np.uint16).reshape(N, K)
+    W = (Wb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    print(f"two row groups M={M} N={N} K={K}", flush=True)
+    err = np.abs(bb.debug_gemm(A, Wb, 0, wide=True) - A.astype(np.float64) @ W.T)
+    mag = np.abs(A).astype(np.float64) @ np.abs(W).T
+    assert (err <= 2.0 ** -13 * mag / np.sqrt(K) * 4 + 1e-30).all(), float((err / (mag + 1e-300)).max())
+
+
 @pytest.mark.parametrize("hq,hkv,hd,bias", [(4, 2, 64, True), (2, 1, 128, False), (6, 2, 64, True)])
 def test_qkv_projection_gives_the_same_cache_and_logits_under_every_plan(hq, hkv, hd, bias):
     """The q|k|v projection of the block forward with tiles of 128, 256 or 384 columns and with k whole or split in
