@@ -168,23 +168,22 @@ static __device__ __forceinline__ void store_panel8(u32x4* Apk, int m, int k8, i
         Apk[packA_u4(m, k8, mt_total, 1)] = *reinterpret_cast<u32x4*>(lo);
     } else {
         typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+        typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
         typedef short i16x2_t __attribute__((ext_vector_type(2)));
-        f16x8_t hi;
-        float r[8];
+        f16x8_t hi, r;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float x = fminf(fmaxf(y[j], -65504.0f), 65504.0f);
             hi[j] = (half_t)x;
-            r[j] = x - (float)hi[j];
+            r[j] = (half_t)((x - (float)hi[j]) * (float)(1 << BB_LO_SHIFT));
         }
-        // |r| <= 2^4, far inside e5m2's range; the hardware divides by its scale operand and rounds to nearest even, once
-        const float sc = 1.0f / (float)(1 << BB_LO_SHIFT);
+        // (|r| <= 2^12, far inside e5m2's range; the hardware divides by its scale operand and rounds to nearest even)
         uint32_t lo[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             i16x2_t a = {0, 0};
-            a = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(a, r[4 * q], r[4 * q + 1], sc, false);
-            a = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(a, r[4 * q + 2], r[4 * q + 3], sc, true);
+            a = __builtin_amdgcn_cvt_scalef32_pk_bf8_f16(a, f16x2_t{r[4 * q], r[4 * q + 1]}, 1.0f, false);
+            a = __builtin_amdgcn_cvt_scalef32_pk_bf8_f16(a, f16x2_t{r[4 * q + 2], r[4 * q + 3]}, 1.0f, true);
             lo[q] = __builtin_bit_cast(uint32_t, a);
         }
         const uint32_t lo0 = lo[0], lo1 = lo[1];
