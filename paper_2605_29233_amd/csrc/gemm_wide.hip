@@ -33,6 +33,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define KC 4                                    // fp16 k-steps (of 16) per chunk = weight fragments per (tile, chunk)
 
+#define IC(v) std::integral_constant<int, (v)>{}
 #define WEPI_PARTIAL 0
 #define WEPI_SWIGLU 1
 
@@ -62,11 +63,15 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 // same features; NT == 2, k not split): writes SiLU(gate) * up as the wide-format panel Opk of the down projection.
 //
 // Chunk pipeline (one wave per SIMD, nothing else hides a stall), five phases per 64 k:
-//   fp16 k-step 0: MFMAs | LDS reads of step 1 | LDS writes of chunk c+1's activations (loaded during c-AD)
-//   fp16 k-step 1: MFMAs | LDS reads of step 2 | global loads of chunk c+1+AD's activations       -> barrier
-//   fp16 k-step 2: MFMAs | LDS reads of step 3 | global loads of chunk c+DW-1's weight fragments 0, 1
-//   fp16 k-step 3: MFMAs | LDS reads of the fp8 fragments | weight fragments 2, 3 | this chunk's weights -> e4m3
-//   fp8 step:      MFMAs | LDS reads of step 0 of chunk c+1
+//   fp16 k-step 0: MFMAs | LDS reads of step 1 | LDS writes of chunk c+1's activations (loaded during c-AD), first half
+//   fp16 k-step 1: MFMAs | LDS reads of step 2 | second half | global loads of chunk c+1+AD's activations, first half     -> barrier
+//   fp16 k-step 2: MFMAs | LDS reads of step 3 | second half | chunk c+DW-1's weight fragment 0
+//   fp16 k-step 3: MFMAs | LDS reads of the fp8 fragments | weight fragment 1 | this chunk's weights -> e4m3
+//   fp8 step:      MFMAs | LDS reads of step 0 of chunk c+1 | weight fragments 2, 3
+// With three or four m-tiles so; with fewer the activations are written in the first phase and requested in the second, and the weights
+// in the third and fourth, two fragments each.  (All that in so few phases left four m-tiles waiting for the LDS in the first, 24 KB written and 16 read
+// in 256 cycles, and for the load path in the next three: block steps of 56 columns per CU, 37888 x 3584 at 112 rows, 5642 -> 5496 us for
+// 28 layers; with one m-tile the even spread is 1 % slower, its weights come later.)
 // With few accumulator tiles the registers hold a ring of four weight chunks, and activations that are requested two
 // chunks ahead instead of one (64-row body, 37888 x 3584: 62.5 -> 57.4 us; with more tiles the deeper ring gains nothing).
 template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     constexpr int THREADS = 64 * WAVES;
     constexpr int WCHUNK_U4 = MT * BB_WFRAGS * 64;          // uint4 per staged activation chunk (6 KiB per m-tile)
     constexpr int WA_PER_THREAD = (WCHUNK_U4 + THREADS - 1) / THREADS;  // (an odd MT: the last half piece repeats valid data past the chunk's end)
-    constexpr bool DEEP = NT * MT <= 4 && MT < 4;
+    constexpr bool DEEP = NT * MT <= 4 && MT < 4, SPREAD = MT >= 3;
     constexpr int DW = DEEP ? 4 : 3, AD = DEEP ? 2 : 1;     // chunks in the weight ring and LDS; activation chunks in registers
     constexpr int COLS = 32 * NT, LDT = COLS + 4;           // store slices: row stride in floats (16-byte aligned, conflict-free)
     constexpr int MPP = NT <= 2 && MT % 2 == 0 ? 2 : 1;     // m-tiles per store pass
@@ -122,10 +127,10 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     }
     const u32x4* abase = Apk + (size_t)mt0 * (BB_WFRAGS * 64);
     const size_t a_chunk = (size_t)mt_total * (BB_WFRAGS * 64);
-    auto load_a = [&](u32x4 (&a)[WA_PER_THREAD], int c) {
+    auto load_a = [&](u32x4 (&a)[WA_PER_THREAD], int c, int lo, int hi) {
         const u32x4* p = abase + (size_t)min(c, c1 - 1) * a_chunk;
 #pragma unroll
-        for (int i = 0; i < WA_PER_THREAD; ++i) a[i] = p[aoff[i]];
+        for (int i = lo; i < hi; ++i) a[i] = p[aoff[i]];
     };
     auto load_w = [&](u32x4 (&w)[KC][NT], int c, int f_lo, int f_hi) {
         const size_t off = (size_t)min(c, c1 - 1) * (KC * 64);
@@ -189,44 +194,51 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     // prologue: chunk c0 staged, AD chunks of activations in registers, weights of DW - 1 chunks in flight; loads in the
     // order the loop issues them (activations of a chunk, then its weights), so that the wait counts at the loop head, the
     // more cautious of the two ways in, are those of the steady state
-    unroll<AD>([&](auto I) { load_a(a[I], c0 + I); load_w(w[I], c0 + I, 0, KC); });
+    unroll<AD>([&](auto I) { load_a(a[I], c0 + I, 0, WA_PER_THREAD); load_w(w[I], c0 + I, 0, KC); });
 #pragma unroll
     for (int i = 0; i < WA_PER_THREAD; ++i) lds[0][i * THREADS + threadIdx.x] = a[0][i];
-    load_a(a[0], c0 + AD);
+    load_a(a[0], c0 + AD, 0, WA_PER_THREAD);
     unroll<DW - 1 - AD>([&](auto I) { load_w(w[AD + I], c0 + AD + I, 0, KC); });
     __syncthreads();
     read_bh(bh[0], 0, 0);
 
+    constexpr int WA1 = SPREAD ? (WA_PER_THREAD + 1) / 2 : WA_PER_THREAD, W1 = SPREAD ? 1 : 2, W2 = SPREAD ? 2 : KC;     // activation pieces and weight fragments up to a phase
+    auto write_a = [&](auto Stage, auto As, auto Lo, auto Hi) {
+#pragma unroll
+        for (int i = decltype(Lo)::value; i < decltype(Hi)::value; ++i) lds[decltype(Stage)::value][i * THREADS + threadIdx.x] = a[decltype(As)::value][i];
+    };
     auto chunk = [&](auto U, int c) {
         constexpr int u = decltype(U)::value, st = u, st1 = (u + 1) % DW, slot2 = (u + DW - 1) % DW, as = (u + 1) % AD;
         __builtin_amdgcn_sched_barrier(0);  // (a conversion moved up from a later chunk would wait for that chunk's loads)
         // fp16 k-step 0
         read_bh(bh[1], st, 1);
-#pragma unroll
-        for (int i = 0; i < WA_PER_THREAD; ++i) lds[st1][i * THREADS + threadIdx.x] = a[as][i];
+        write_a(IC(st1), IC(as), IC(0), IC(WA1));
         mfma_hi(w[u][0], bh[0]);
-        sched_groups<MT, NT, MT, WA_PER_THREAD, 0>();
+        sched_groups<MT, NT, MT, WA1, 0>();
         // fp16 k-step 1
         read_bh(bh[0], st, 2);
-        load_a(a[as], c + 1 + AD);
+        write_a(IC(st1), IC(as), IC(WA1), IC(WA_PER_THREAD));
+        load_a(a[as], c + 1 + AD, 0, WA1);
         mfma_hi(w[u][1], bh[1]);
-        sched_groups<MT, NT, MT, 0, WA_PER_THREAD>();
+        sched_groups<MT, NT, MT, WA_PER_THREAD - WA1, WA1>();
         __syncthreads();                    // chunk c+1 is staged; the stage of chunk c-1 is free again
         // fp16 k-step 2
         read_bh(bh[1], st, 3);
-        load_w(w[slot2], c + DW - 1, 0, 2);
+        load_a(a[as], c + 1 + AD, WA1, WA_PER_THREAD);
+        load_w(w[slot2], c + DW - 1, 0, W1);
         mfma_hi(w[u][2], bh[0]);
-        sched_groups<MT, NT, MT, 0, 2 * NT>();
+        sched_groups<MT, NT, MT, 0, WA_PER_THREAD - WA1 + W1 * NT>();
         // fp16 k-step 3 (and the conversion of this chunk's weights for the fp8 step)
         read_bl(bl, st);
-        load_w(w[slot2], c + DW - 1, 2, 4);
+        load_w(w[slot2], c + DW - 1, W1, W2);
         convert_w(w8, w[u]);
         mfma_hi(w[u][3], bh[1]);
-        sched_groups<MT, NT, 2 * MT, 0, 2 * NT>();
+        sched_groups<MT, NT, 2 * MT, 0, (W2 - W1) * NT>();
         // fp8 step (reads the first fp16 fragments of the next chunk)
         read_bh(bh[0], st1, 0);
+        load_w(w[slot2], c + DW - 1, W2, KC);
         mfma_lo(w8, bl);
-        sched_groups<MT, NT, MT, 0, 0>();
+        sched_groups<MT, NT, MT, 0, (KC - W2) * NT>();
     };
     int c = c0;
     for (; c + DW <= c1; c += DW) unroll<DW>([&](auto U) { chunk(U, c + U); });
