@@ -21,6 +21,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define KC 4        // k-steps (of 16) per staged chunk
 #define MT_MAX 4    // m-tiles (of 32 rows) per workgroup
+#define VOCAB_MT 5  // ... of the LM head with 256-column tiles: four chunks of activations fill the 160 KiB
 #define DW 3        // weight chunks per wave in the register ring (two in flight ahead of the MFMAs)
 #define CHUNK_U4(mt) (KC * (mt) * BB_SPLIT * 64)        // uint4 per staged activation chunk of mt m-tiles (four: 2048 = 32 KiB)
 
@@ -56,12 +57,11 @@ static __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
 //
 // The LM head's row list is filled on the device (masked positions only), so the launch is sized for its upper bound and
 // the kernel reads the count: row groups past it are skipped, and the live m-tiles are dealt evenly to the groups, each
-// computed by the body for its own number of m-tiles (a group of one m-tile issues a quarter of the MFMAs and LDS reads of
-// a full one and is bound by the weight stream alone).  Row groups of a column group are neighbours in the item order
-// and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
-// Measured (vocabulary 126464, d 4096; before = every row of the bound, row groups of 128, running sums in the epilogue):
-// 1152 live of 1920 rows 3573 -> 1916 us, 144 of 240 480 -> 414 us, 19 of 32 rows 180 us = 5.7 TB/s; vocabulary 1024, d 256,
-// 34 of 56 rows: 24 -> 12 us, most of it the serial chain of exponentials that the epilogue no longer has.
+// computed by the body for its own number of m-tiles.  With one or two m-tiles that is the tile below, which keeps two chunks of weights
+// on their way and is bound by their stream; with three to five vocab_tile, bound by the matrix pipes (two passes per weight).  Row groups of
+// a column group are neighbours in the item order and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
+// Measured (vocabulary 126464, d 4096): 19 of 32 rows 180 us = 5.7 TB/s; 144-152 of 240-252 rows (five m-tiles in one group; before, two
+// groups of the tile below, 32 x 32 MFMAs) 405 -> 271; 256 rows (4 + 4) 424 -> 415; 72 of 120 rows (three) 212 -> 205.
 struct GemmArgs {
     const u32x4* Wt; const u32x4* Apk; float* P;
     size_t split_stride;
@@ -237,7 +237,8 @@ static __device__ __forceinline__ void gemm_tile(const GemmArgs& g, u32x4* lds_r
         static_assert(EPI != EPI_VOCAB || NT <= 2, "vocabulary epilogue is written for one or two tiles per wave");
         // Lane l holds, for activation row l % 32 of every m-tile, 16 columns of each of its weight tiles, in
         // ascending column order (register r <-> column 8 (r/4) + 4 (l/32) + r%4): a strict '>' keeps the lowest id.
-        __shared__ MSI sV[4][MT_MAX * 32];
+        MSI (*sV)[MT_MAX * 32] = reinterpret_cast<MSI (*)[MT_MAX * 32]>(lds_raw);
+        __syncthreads();                                    // all waves are done with the staged activations
         const int mask_id = g.mask_id;
         const int x0v = (bx * 4 + wave) * NT, gv = lane >> 5;
 #pragma unroll
@@ -313,13 +314,199 @@ static __device__ __forceinline__ void gemm_tile(const GemmArgs& g, u32x4* lds_r
     __syncthreads();                                        // the next tile's prologue overwrites the LDS slices
 }
 
+template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
+    if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
+}
+#define IC(v) std::integral_constant<int, (v)>{}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// The LM head's workgroup tile for MT m-tiles from mt0 x the 256 columns of group bx (k whole): 16 x 16 MFMAs, weights global -> registers
+// a half chunk (32 k) four ahead, activations by direct-to-LDS loads into a ring of four chunks, one barrier per chunk, each half cut into
+// slots of eight MFMAs (two terms x four column tiles) with an even share of the LDS reads and loads.
+template <int MT>
+static __device__ __forceinline__ void vocab_tile(const GemmArgs& ga, char* lds, int bx, int mt0) {
+    constexpr int T = 4, R = 2 * MT, STAGE = MT * 8192, D = R > 6 ? R / 2 : R;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    const int n_chunks = ga.ksteps / KC, x0 = (bx * 4 + wave) * 2;
+    const unsigned lane16 = lane * 16, lds0 = lds_offset(lds), frag_lane = (g >> 1) * 1024 + (c16 + 32 * (g & 1)) * 16;
+    const size_t a_chunk = (size_t)KC * ga.mt_total * 2048;
+    // wave w fetches k-step w of a chunk: both terms of every m-tile.  Past the end all lanes read one address of the last chunk.
+    const char* a_src = (const char*)ga.Apk + ((size_t)wave * ga.mt_total + mt0) * 2048;
+    unsigned a_lane = lane16, a_dst = lds0 + wave * 1024;
+    int a_c = 0;
+    auto a_next = [&]() {
+        ++a_c;
+        const bool in = a_c < n_chunks;
+        a_src += in ? a_chunk : 0;
+        a_lane = in ? lane16 : 0u;
+        a_dst = (a_c & 3) == 0 ? a_dst - 3 * STAGE : a_dst + STAGE;
+    };
+    auto fetch_a = [&](auto I) { load_to_lds<0>(a_src + decltype(I)::value * 1024, a_lane, a_dst + decltype(I)::value * 4096); };
+    typedef const __attribute__((address_space(1))) char* gchar;
+    typedef const __attribute__((address_space(1))) u32x4* gvec;
+    // (through assembly, so that the compiler takes the weight loads for reads of memory that the direct-to-LDS loads may write and
+    // keeps their order, which the waits count on)
+    gchar wsrc[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        wsrc[t] = (gchar)ga.Wt + (size_t)min(x0 + t, ga.n_tiles - 1) * n_chunks * 4096;        // clamped loads; stores are guarded
+        asm volatile("" : "+s"(wsrc[t]));
+    }
+    unsigned w_lane = frag_lane;
+    int w_c = 0;
+    auto w_next = [&]() {
+        ++w_c;
+        const bool in = w_c < n_chunks;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) { wsrc[t] += in ? 4096 : 0; asm volatile("" : "+s"(wsrc[t])); }
+        w_lane = in ? frag_lane : 0u;
+    };
+    u32x4 w[4][T], b[D][2];
+    auto fetch_w = [&](auto S) {
+        constexpr int s = decltype(S)::value;
+#pragma unroll
+        for (int t = 0; t < T; ++t) w[s][t] = __builtin_nontemporal_load((gvec)(wsrc[t >> 1] + (size_t)w_lane + (s & 1) * 2048 + (t & 1) * 256));
+    };
+    f32x4 acc[T][R];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+            asm("" : "+v"(acc[t][m]));                      // (as constants the compiler carries them through the loop element by element, and copies)
+        }
+    unroll<2 * MT>([&](auto I) { fetch_a(I); });
+    a_next();
+    fetch_w(IC(0)); fetch_w(IC(1));
+    w_next();
+    unroll<2 * MT>([&](auto I) { fetch_a(I); });
+    a_next();
+    fetch_w(IC(2)); fetch_w(IC(3));
+    unroll<MT>([&](auto I) { fetch_a(I); });
+    // all but the latest `Later` loads of this wave have landed; after the barrier so have the others'
+    auto landed = [&](auto Later) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(Later)::value) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    landed(IC(4 * T + 3 * MT));
+    const char* cur = lds + frag_lane;
+    unsigned stage = 0;
+    auto read_b = [&](int m, const char* at, int h) {
+#pragma unroll
+        for (int term = 0; term < 2; ++term) b[m % D][term] = *reinterpret_cast<const u32x4*>(at + ((m >> 1) * 2 + term) * 4096 + h * 2048 + (m & 1) * 256);
+    };
+#pragma unroll
+    for (int m = 0; m < D; ++m) read_b(m, cur, 0);
+    // half S of two chunks; the next half's first fragments are at nxt
+    auto half = [&](auto S, const char* here, const char* nxt, auto First, auto Last) {
+        constexpr int s = decltype(S)::value, first = decltype(First)::value;
+        unroll<R>([&](auto M) {
+            constexpr int m = decltype(M)::value;
+#pragma unroll
+            for (int term = 0; term < 2; ++term)
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w[s][t]), as_bf16x8(b[m % D][term]), acc[t][m], 0, 0, 0);
+            if constexpr (m + D < R) read_b(m + D, here, s & 1);
+            else read_b(m + D - R, nxt, 1 - (s & 1));
+            if constexpr (!decltype(Last)::value) {
+                unroll<MT * (m + 1) / R - MT * m / R>([&](auto I) { fetch_a(IC(first + MT * m / R + decltype(I)::value)); });
+                if constexpr (m == R - 1) fetch_w(S);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto chunk = [&](auto S, auto Last) {
+        constexpr int s = decltype(S)::value;
+        constexpr bool last = decltype(Last)::value;
+        if constexpr (!last) w_next();
+        half(IC(s), cur, cur, IC(MT), Last);
+        landed(IC(last ? 0 : 3 * T + 2 * MT));              // (those issued after the next chunk's pieces may still be on their way)
+        if constexpr (!last) a_next();
+        stage = stage == 3 * STAGE ? 0u : stage + STAGE;
+        const char* nxt = lds + frag_lane + stage;
+        half(IC(s + 1), cur, nxt, IC(0), Last);
+        cur = nxt;
+    };
+    int c = 0;
+    for (; c + 2 <= n_chunks; c += 2) { chunk(IC(0), std::false_type{}); chunk(IC(2), std::false_type{}); }
+    // every load that the waits count was made: none of them may go because nothing reads it
+#pragma unroll
+    for (int i = 0; i < 4 * T; ++i) asm volatile("" ::"v"(w[i / T][i % T]));
+    if (c < n_chunks) chunk(IC(0), std::true_type{});
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                        // all waves are done with the staged activations
+
+    // Register r of lane (c16, g) holds column 16 t + 4 g + r of activation row c16: in ascending order, so a strict '>' keeps the
+    // lowest id.  Maximum and its column first, then the exponentials: 16 independent ones.
+    MSI (*sV)[MT * 32] = reinterpret_cast<MSI (*)[MT * 32]>(lds);
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+        MSI a = {-INFINITY, 0.f, 0x7fffffff};
+        float x[T][4];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int v = x0 * 32 + 16 * t + 4 * g + r;
+                x[t][r] = x0 + (t >> 1) < ga.n_tiles && v != ga.mask_id ? acc[t][m][r] : -INFINITY;
+                if (x[t][r] > a.m) { a.m = x[t][r]; a.i = v; }
+            }
+        const float top = a.m == -INFINITY ? 0.f : a.m;
+        float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[r] += expf(x[t][r] - top);
+        a.s = (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+        for (int o = 16; o <= 32; o <<= 1) {
+            const MSI q = {__shfl_xor(a.m, o, 64), __shfl_xor(a.s, o, 64), __shfl_xor(a.i, o, 64)};
+            a = (lane & o) ? msi_merge(q, a) : msi_merge(a, q);        // both partners form the same merge
+        }
+        if (g == 0) sV[wave][m * 16 + c16] = a;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < MT * 32) {
+        MSI t4 = sV[0][threadIdx.x];
+#pragma unroll
+        for (int w4 = 1; w4 < 4; ++w4) t4 = msi_merge(t4, sV[w4][threadIdx.x]);
+        ga.Vp[(size_t)(mt0 * 32 + threadIdx.x) * ga.tiles_x + bx] = make_float4(t4.m, t4.s, __int_as_float(t4.i), 0.f);
+    }
+    __syncthreads();
+    if (!ga.keep_logits) return;
+    // The logits go out through LDS (each wave its own slice, one m-tile at a time) as whole 128-byte lines.
+    constexpr int LDT = 64 + 4;
+    float* tl = reinterpret_cast<float*>(lds) + wave * (32 * LDT);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                *reinterpret_cast<float4*>(&tl[(s * 16 + c16) * LDT + t * 16 + 4 * g]) =
+                    make_float4(acc[t][2 * mt + s][0], acc[t][2 * mt + s][1], acc[t][2 * mt + s][2], acc[t][2 * mt + s][3]);
+        wave_lds_order();                                   // (the same wave wrote and reads: no barrier needed)
+#pragma unroll
+        for (int it = 0; it < 8; ++it) {
+            const int r = it * 4 + g, c4 = c16 * 4;
+            const float4 v = *reinterpret_cast<const float4*>(&tl[r * LDT + c4]);
+            if (x0 * 32 + c4 < ga.n_tiles * 32) *reinterpret_cast<float4*>(&ga.P[(size_t)((mt0 + mt) * 32 + r) * ga.ldp + x0 * 32 + c4]) = v;
+        }
+        wave_lds_order();                                   // (the next m-tile overwrites the slice)
+    }
+    __syncthreads();                                        // the next tile's loads overwrite the LDS slices
+}
+
 template <int NT, int EPI>
 __global__ __launch_bounds__(256, 1) void gemm_kernel(GemmArgs g) {
-    __shared__ u32x4 lds[3 * CHUNK_U4(MT_MAX)];
+    __shared__ u32x4 lds[EPI == EPI_VOCAB && NT == 2 ? 4 * VOCAB_MT * 512 : 3 * CHUNK_U4(MT_MAX)];
     // a workgroup walks the (column group, row group) tiles with the grid's stride: at most one round of
     // workgroups is ever launched, the rest of the tiles are taken by the same workgroups
     if constexpr (EPI == EPI_VOCAB) {       // (k is not split)
-        const int live_mt = min(g.mt_total, (*g.rows_live + 31) >> 5), groups = (live_mt + MT_MAX - 1) / MT_MAX;
+        constexpr int MOST = NT == 2 ? VOCAB_MT : MT_MAX;
+        const int live_mt = min(g.mt_total, (*g.rows_live + 31) >> 5), groups = (live_mt + MOST - 1) / MOST;
         const int per = live_mt / max(groups, 1), more = live_mt % max(groups, 1);         // the first `more` groups take one m-tile more
         const int items = g.tiles_x * groups;
         for (int base = 0; base < items; base += gridDim.x) {
@@ -327,11 +514,15 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(GemmArgs g) {
             if (lin >= n) break;
             const int e = lin & 7, item = base + e * (n >> 3) + min(e, n & 7) + (lin >> 3);
             const int bx = item / groups, by = item % groups, mt0 = by * per + min(by, more), cnt = per + (by < more);
-            switch (cnt) {
-                case 1: gemm_tile<NT, EPI, 1>(g, lds, bx, mt0, 1, 0); break;
-                case 2: gemm_tile<NT, EPI, 2>(g, lds, bx, mt0, 2, 0); break;
-                case 3: gemm_tile<NT, EPI, 3>(g, lds, bx, mt0, 3, 0); break;
-                default: gemm_tile<NT, EPI, 4>(g, lds, bx, mt0, 4, 0);
+            if (cnt == 1) gemm_tile<NT, EPI, 1>(g, lds, bx, mt0, 1, 0);
+            else if (cnt == 2) gemm_tile<NT, EPI, 2>(g, lds, bx, mt0, 2, 0);
+            else if constexpr (NT == 1) {
+                if (cnt == 3) gemm_tile<NT, EPI, 3>(g, lds, bx, mt0, 3, 0);
+                else gemm_tile<NT, EPI, 4>(g, lds, bx, mt0, 4, 0);
+            } else {
+                if (cnt == 3) vocab_tile<3>(g, reinterpret_cast<char*>(lds), bx, mt0);
+                else if (cnt == 4) vocab_tile<4>(g, reinterpret_cast<char*>(lds), bx, mt0);
+                else vocab_tile<5>(g, reinterpret_cast<char*>(lds), bx, mt0);
             }
         }
         return;

@@ -255,6 +255,30 @@ def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows,
         bb.close()
 
 
+@pytest.mark.parametrize("d_model,vocab,gen_len", [
+    (256, 1024, 96),        # three m-tiles
+    (256, 1056, 97),        # four, the last one of one row; a last column group of one tile
+    (192, 992, 160),        # five m-tiles; an odd number of chunks; a last column group of seven tiles
+    (320, 1024, 161),       # six: 3 + 3; five chunks
+    (64, 288, 300),         # ten: 5 + 5; a single chunk
+])
+def test_lm_head_tiles(d_model, vocab, gen_len):
+    """The initial forward's logits, argmax, confidence and log-sum-exp where the LM head's row groups, column groups and chunks end:
+    against the oracle in fp64."""
+    shape = ModelShape("lmtest", 1, d_model, 2, 2, 64, 64, vocab)
+    decode = DecodeParams(0.9, 0.5, 400, 8, 0)
+    weights = dict(gen_weights(shape, 31))
+    print("lm head", d_model, vocab, gen_len, flush=True)
+    bb = make_bb(shape, decode, weights, 1, 20 + gen_len, gen_len, 32, poison=True)
+    try:
+        s = SideBySide(bb, OracleModel(shape, weights, np.float64), gen_prompt(shape, 31, 0, 20), gen_len, (32,), decode, conf_tol=5e-4)
+        s.init()
+        s.commit()
+        assert s.rep.max_logit_err <= 1e-3          # one layer (two terms per operand: 2^-16 of logits of about 10)
+    finally:
+        bb.close()
+
+
 def test_long_row_with_empty_attention_splits():
     """A row of L = 64 * 64 + 1 = 4097 keys (65 pages) beside one of 100 (2 pages) in the same block steps: the pages of every row
     are cut into nine ranges.  The long row's last range is one page that holds one key, so seven of its eight waves get
