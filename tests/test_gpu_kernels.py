@@ -86,15 +86,15 @@ def test_wide_format_gemm_matches_fp64(bb, M, N, K, split):
     (740, 5664, 1344, 0, 192),      # two splits of 12 and 9 chunks; one column tile over a multiple of eight
 ])
 def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split, tile_rows):
-    """The eight-wave kernel (more than 256 rows) with both tile heights, where units, k splits, row and column groups end:
+    """Tiles of 256 columns (more than 256 rows) with both tile heights, where units, k splits, row and column groups end:
     against fp64, bound as in test_wide_format_gemm_matches_fp64.  (A forced split takes the 128-row tile.  Without one these
-    small matrices go to the four-wave kernel: test_small_matrices_of_many_rows.)"""
+    small matrices take tiles of 128 columns: test_small_matrices_of_many_rows.)"""
     if split == 0:
         from paper_2605_29233_amd.binding import gemm_plan
         p = gemm_plan(M, N, K, wide=True)
         chunks = (K + 63) // 64
         assert p["mt"] == tile_rows // 32, p
-        assert p["nt"] == 2, "eight waves"
+        assert p["nt"] == 2, "256 columns"
         assert tile_rows == 128 or (chunks - (p["split_k"] - 1) * p["chunks_per_split"]) % 2, "the 192-row cases end in half a unit"
     rng = np.random.default_rng(M * 13 + K)
     A = rng.standard_normal((M, K)).astype(np.float32)
@@ -116,10 +116,10 @@ def test_many_row_gemm_at_the_edges_of_its_tiles(bb, M, N, K, split, tile_rows):
     (272, 128, 4096),           # 16 k splits
 ])
 def test_small_matrices_of_many_rows(bb, M, N, K):
-    """More than 256 rows over a matrix so small that the four-wave kernel's 128-column tiles fit one round: against fp64,
+    """More than 256 rows over a matrix so small that tiles of 128 columns fit one round: against fp64,
     bound as in test_wide_format_gemm_matches_fp64."""
     from paper_2605_29233_amd.binding import gemm_plan
-    assert gemm_plan(M, N, K, wide=True)["nt"] == 1, "four waves, 128 columns"
+    assert gemm_plan(M, N, K, wide=True)["nt"] == 1, "128 columns"
     rng = np.random.default_rng(M * 17 + K)
     A = rng.standard_normal((M, K)).astype(np.float32)
     Wb = gen_normal_bf16(3, f"s{N}x{K}", N * K, 0.05).view(torch.int16).numpy().view(np.uint16).reshape(N, K)

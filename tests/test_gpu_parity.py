@@ -204,7 +204,7 @@ def test_block_step_attention_waves_and_splits(prompt_len, head_dim, splits, wav
 ])
 def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows, requests):
     """Block steps sized for more than 256 rows in which branches have finished, last windows are clipped and only a part
-    of the rows is masked: whole row groups of the eight-wave GEMM are skipped (gate/up with tiles of 128 and of 192 rows; with
+    of the rows is masked: whole row groups of the layer GEMMs are skipped (gate/up with tiles of 128 and of 192 rows; with
     32 heads also the q|k|v projection, which stores partial tiles), and the LM head's live m-tiles are dealt to fewer row groups than are launched.  Logits, tokens, K,V and the commit
     against the oracle in fp64, from a poisoned workspace."""
     from paper_2605_29233_amd import BB_INIT, BB_PERIODIC
