@@ -56,12 +56,15 @@ static __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
 // are stored only when keep_logits is set (tests).
 //
 // The LM head's row list is filled on the device (masked positions only), so the launch is sized for its upper bound and
-// the kernel reads the count: row groups past it are skipped, and the live m-tiles are dealt evenly to the groups, each
+// the kernel reads the count: row groups past it are skipped, and the live m-tiles are dealt evenly to the groups, as many as one round of
+// workgroups holds (a small vocabulary leaves CUs idle otherwise) but at least what the largest body needs, each
 // computed by the body for its own number of m-tiles.  With one or two m-tiles that is the tile below, which keeps two chunks of weights
 // on their way and is bound by their stream; with three to five vocab_tile, bound by the matrix pipes (two passes per weight).  Row groups of
 // a column group are neighbours in the item order and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
 // Measured (vocabulary 126464, d 4096): 19 of 32 rows 180 us = 5.7 TB/s; 144-152 of 240-252 rows (five m-tiles in one group; before, two
 // groups of the tile below, 32 x 32 MFMAs) 405 -> 271; 256 rows (4 + 4) 424 -> 415; 72 of 120 rows (three) 212 -> 205.
+// Vocabulary 1024, d 256 (4 column groups; before, as few row groups as the bodies allow), whole steps of two layers: 134 of 228 rows 147.5 -> 128.5 us,
+// 60 of 100 rows 128.3 -> 124, 538 of 896 rows 208.9 -> 189.4.
 struct GemmArgs {
     const u32x4* Wt; const u32x4* Apk; float* P;
     size_t split_stride;
@@ -506,7 +509,8 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(GemmArgs g) {
     // workgroups is ever launched, the rest of the tiles are taken by the same workgroups
     if constexpr (EPI == EPI_VOCAB) {       // (k is not split)
         constexpr int MOST = NT == 2 ? VOCAB_MT : MT_MAX;
-        const int live_mt = min(g.mt_total, (*g.rows_live + 31) >> 5), groups = (live_mt + MOST - 1) / MOST;
+        const int live_mt = min(g.mt_total, (*g.rows_live + 31) >> 5);
+        const int groups = max((live_mt + MOST - 1) / MOST, min(live_mt, (int)gridDim.x / g.tiles_x));
         const int per = live_mt / max(groups, 1), more = live_mt % max(groups, 1);         // the first `more` groups take one m-tile more
         const int items = g.tiles_x * groups;
         for (int base = 0; base < items; base += gridDim.x) {
@@ -586,7 +590,7 @@ void launch_gemm(const u32x4* Wt, const u32x4* Apk, float* P, int mt_total, int 
     const int n_tiles = N / 32, ksteps = (K + 63) / 64 * 4, m_groups = (mt_total + MT_MAX - 1) / MT_MAX;     // K padded to whole chunks
     const size_t split_stride = (size_t)mt_total * 32 * N;
     const int tiles_x = (n_tiles + 4 * plan.nt - 1) / (4 * plan.nt);
-    dim3 grid(std::min(tiles_x * m_groups, 256), 1, plan.split_k);
+    dim3 grid(std::min(tiles_x * (epi.vocab_part ? mt_total : m_groups), 256), 1, plan.split_k);
     const GemmArgs g = {Wt, Apk, P, split_stride, N, mt_total, n_tiles, ksteps, plan.chunks_per_split, tiles_x, m_groups, epi.swiglu_out, epi.vocab_part, epi.mask_id, epi.keep_logits, epi.rows_live};
     if (epi.swiglu_out)
         hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_kernel<2, EPI_SWIGLU>), grid, dim3(256), 0, s, st.start, st.stop, 0, g);

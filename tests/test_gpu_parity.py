@@ -256,11 +256,19 @@ def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows,
 
 
 @pytest.mark.parametrize("d_model,vocab,gen_len", [
-    (256, 1024, 96),        # three m-tiles
-    (256, 1056, 97),        # four, the last one of one row; a last column group of one tile
-    (192, 992, 160),        # five m-tiles; an odd number of chunks; a last column group of seven tiles
-    (320, 1024, 161),       # six: 3 + 3; five chunks
-    (64, 288, 300),         # ten: 5 + 5; a single chunk
+    # a small vocabulary: an m-tile per row group
+    (256, 1024, 96),
+    (256, 1056, 97),        # the last m-tile of one row; a last column group of one tile
+    (192, 992, 160),        # an odd number of chunks; a last column group of seven tiles
+    (320, 1024, 161),       # five chunks
+    (64, 288, 300),         # a single chunk
+    (128, 16416, 161),      # 65 column groups, three row groups of two m-tiles
+    # more than 128 column groups: as few row groups as the bodies allow
+    (256, 33024, 96),       # three m-tiles
+    (256, 33056, 97),       # four, the last one of one row; a last column group of one tile
+    (192, 33248, 160),      # five m-tiles; an odd number of chunks; a last column group of seven tiles
+    (320, 33024, 161),      # six: 3 + 3; five chunks
+    (64, 33056, 300),       # ten: 5 + 5; a single chunk
 ])
 def test_lm_head_tiles(d_model, vocab, gen_len):
     """The initial forward's logits, argmax, confidence and log-sum-exp where the LM head's row groups, column groups and chunks end:
