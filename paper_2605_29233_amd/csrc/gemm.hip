@@ -58,10 +58,13 @@ static __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
 // The LM head's row list is filled on the device (masked positions only), so the launch is sized for its upper bound and
 // the kernel reads the count: row groups past it are skipped, and the live m-tiles are dealt evenly to the groups, as many as one round of
 // workgroups holds (a small vocabulary leaves CUs idle otherwise) but at least what the largest body needs, each
-// computed by the body for its own number of m-tiles.  With one or two m-tiles that is the tile below, which keeps two chunks of weights
-// on their way and is bound by their stream; with three to five vocab_tile, bound by the matrix pipes (two passes per weight).  Row groups of
-// a column group are neighbours in the item order and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
-// Measured (vocabulary 126464, d 4096): 19 of 32 rows 180 us = 5.7 TB/s; 144-152 of 240-252 rows (five m-tiles in one group; before, two
+// computed by the body for its own number of m-tiles.  The count of live rows depends on every request of the step, so all bodies of a tile
+// width add the same products in the same order: a row's bits depend neither on its place nor on the rows beside it.  With 256-column
+// tiles (vocabularies of 256 and more) that is vocab_tile, bound by the weight stream with one or two m-tiles and by the matrix pipes (two
+// passes per weight) with more; with 128-column tiles the tile below.  Row groups of a column group are neighbours in
+// the item order and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
+// Measured (us; vocabulary 126464, d 4096): 19 live rows 173 (6.0 TB/s), the same with the tile below; 64 rows 184, 181 with the tile below
+// (152064 x 3584: 226, 217), which is no reason for a second order of the sums; 144-152 of 240-252 rows (five m-tiles in one group; before, two
 // groups of the tile below, 32 x 32 MFMAs) 405 -> 271; 256 rows (4 + 4) 424 -> 415; 72 of 120 rows (three) 212 -> 205.
 // Vocabulary 1024, d 256 (4 column groups; before, as few row groups as the bodies allow), whole steps of two layers: 134 of 228 rows 147.5 -> 128.5 us,
 // 60 of 100 rows 128.3 -> 124, 538 of 896 rows 208.9 -> 189.4.
@@ -518,15 +521,18 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel(GemmArgs g) {
             if (lin >= n) break;
             const int e = lin & 7, item = base + e * (n >> 3) + min(e, n & 7) + (lin >> 3);
             const int bx = item / groups, by = item % groups, mt0 = by * per + min(by, more), cnt = per + (by < more);
-            if (cnt == 1) gemm_tile<NT, EPI, 1>(g, lds, bx, mt0, 1, 0);
-            else if (cnt == 2) gemm_tile<NT, EPI, 2>(g, lds, bx, mt0, 2, 0);
-            else if constexpr (NT == 1) {
-                if (cnt == 3) gemm_tile<NT, EPI, 3>(g, lds, bx, mt0, 3, 0);
+            if constexpr (NT == 1) {
+                if (cnt == 1) gemm_tile<NT, EPI, 1>(g, lds, bx, mt0, 1, 0);
+                else if (cnt == 2) gemm_tile<NT, EPI, 2>(g, lds, bx, mt0, 2, 0);
+                else if (cnt == 3) gemm_tile<NT, EPI, 3>(g, lds, bx, mt0, 3, 0);
                 else gemm_tile<NT, EPI, 4>(g, lds, bx, mt0, 4, 0);
             } else {
-                if (cnt == 3) vocab_tile<3>(g, reinterpret_cast<char*>(lds), bx, mt0);
-                else if (cnt == 4) vocab_tile<4>(g, reinterpret_cast<char*>(lds), bx, mt0);
-                else vocab_tile<5>(g, reinterpret_cast<char*>(lds), bx, mt0);
+                char* raw = reinterpret_cast<char*>(lds);
+                if (cnt == 1) vocab_tile<1>(g, raw, bx, mt0);
+                else if (cnt == 2) vocab_tile<2>(g, raw, bx, mt0);
+                else if (cnt == 3) vocab_tile<3>(g, raw, bx, mt0);
+                else if (cnt == 4) vocab_tile<4>(g, raw, bx, mt0);
+                else vocab_tile<5>(g, raw, bx, mt0);
             }
         }
         return;

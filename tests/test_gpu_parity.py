@@ -407,6 +407,68 @@ def test_equal_rows_give_bit_identical_logits_wherever_they_are_placed():
         bb.close()
 
 
+@pytest.mark.parametrize("vocab,requests", [
+    (16416, 7),         # 65 column groups, three row groups of 3 + 2 + 2 m-tiles
+    (32000, 5),         # 125 column groups, 3 + 2
+    (33056, 11),        # more than 128 column groups: 4 + 4 + 3
+])
+def test_equal_rows_in_row_groups_of_different_heights(vocab, requests):
+    """Requests with the same prompt in one initial forward, 32 logit rows each: the LM head deals their m-tiles unevenly to its
+    row groups, and every request must come out with the same bits, whichever body computed its m-tile."""
+    from paper_2605_29233_amd import BB_INIT
+    shape = ModelShape("dealtest", 1, 192, 2, 2, 64, 64, vocab)
+    L_p, G = 9, 32
+    bb = make_bb(shape, DecodeParams(0.9, 0.5, 400, 8, 0), dict(gen_weights(shape, 5)), 1, L_p + G, G, requests * (L_p + G), max_requests=requests)
+    try:
+        print("uneven deal", vocab, requests, flush=True)
+        prompt = gen_prompt(shape, 5, 0, L_p)
+        ids = [bb.request_open(prompt, G, (G,)) for _ in range(requests)]
+        bb.refresh(ids, BB_INIT)
+        v = bb.latest_view()
+        assert v.m_lm == requests * G
+        for x in (v.logits()[:, :-1], v.argmax(), v.conf(), v.lse()):
+            for b in range(1, requests):
+                assert np.array_equal(x[b * G:(b + 1) * G], x[:G]), f"request {b} differs"
+    finally:
+        bb.close()
+
+
+@pytest.mark.parametrize("vocab", [1024, 16416, 33056])
+def test_a_row_does_not_depend_on_how_many_rows_are_masked_beside_it(vocab):
+    """Block steps of two requests in which the second one has more and more masked positions (1, 2, 3, 4, 5 and 3 + 3 m-tiles
+    where the vocabulary leaves one row group per round of workgroups): the first request's rows keep their bits."""
+    from types import SimpleNamespace
+    from paper_2605_29233_amd import BB_INIT
+    shape = ModelShape("besidetest", 1, 192, 2, 2, 64, 64, vocab)
+    L_p, G = 20, 160
+    rng = np.random.default_rng(6)
+    bb = make_bb(shape, DecodeParams(0.9, 0.5, 400, 8, 0), dict(gen_weights(shape, 6)), 1, L_p + G, G, 2 * G, max_requests=2)
+    try:
+        prompts = [gen_prompt(shape, 6, i, L_p) for i in range(2)]
+        ids = [bb.request_open(p, G, (G,)) for p in prompts]
+        for r in ids:
+            bb.refresh([r], BB_INIT)
+        truth = rng.integers(0, shape.vocab - 1, (2, G), dtype=np.int32)
+        first = None
+        for live in (21, 60, 80, 120, 150, 180):
+            print("masked rows", vocab, live, flush=True)
+            for i, n in enumerate((20, live - 20)):
+                X = np.concatenate([prompts[i], truth[i]]).astype(np.int32)[None]
+                X[0, L_p:L_p + n] = shape.mask_id
+                bb.set_state(ids[i], X, [SimpleNamespace(start=L_p, end=L_p + G, done=0, mean_conf=0.5)])
+            v = bb.denoise_step(ids)
+            assert (v.m_q, v.m_lm) == (2 * G, live)
+            gbr, pos = v.rows()
+            lm = v.lm_rows()
+            mine = gbr[lm] == gbr[0]
+            assert mine.sum() == 20 and np.array_equal(pos[lm][mine], L_p + np.arange(20))
+            got = v.logits()[mine, :-1], v.argmax()[mine], v.conf()[mine], v.lse()[mine]
+            first = first or got
+            assert all(np.array_equal(a, b) for a, b in zip(got, first)), live
+    finally:
+        bb.close()
+
+
 def test_two_requests_initialised_and_refreshed_by_single_calls():
     """Two requests of different lengths and branch sets share every forward: one bb_refresh(BB_INIT) call packs
     both initial forwards, one bb_denoise_step both windows sets, one bb_refresh(BB_PERIODIC) both refreshes; each
