@@ -306,8 +306,8 @@ def test_wide_format_gemm_for_every_number_of_row_tiles(bb, M, N, K):
 
 @pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 97, 129, 161, 225, 257])
 def test_lm_head_row_groups(n):
-    """n rows receive logits: 1, 2, 3 or 4 m-tiles in one row group, then two and three groups with the m-tiles dealt evenly
-    (129 rows = 3 + 2, 225 = 4 + 4, 257 = 3 + 3 + 3).  The launch is sized for the same n rows (fewer live ones than it is
+    """n rows receive logits: one to nine m-tiles, each a row group of its own (four column groups; taller row groups: test_lm_head_tiles,
+    test_vocabulary_ties_in_every_body_of_the_lm_head).  The launch is sized for the same n rows (fewer live ones than it is
     sized for: test_step_with_fewer_live_rows_than_it_is_sized_for).  Logits against the oracle (fp64);
     token, confidence and log-sum-exp against a reduction of the returned logits in fp64: 1 / c and exp(lse - max) are
     sums of up to 1024 exponentials in fp32, each good to 2 ulp of an argument below 2^7."""

@@ -196,20 +196,24 @@ def test_block_step_attention_waves_and_splits(prompt_len, head_dim, splits, wav
     check_report(s)
 
 
-@pytest.mark.parametrize("heads,d_ffn,tile_rows,requests", [
+@pytest.mark.parametrize("heads,d_ffn,tile_rows,requests,vocab", [
     # per request: (window, tokens still masked in it) of each branch, None = the branch has finished
-    (4, 688, 128, [(None, ((256, 320), 20), ((0, 160), 150))]),            # 224 rows of 352, 170 of them to the LM head
-    (32, 8192, 192, [(None, ((256, 320), 20), ((0, 160), 150)),             # 448 of 704 and 300 (10 m-tiles: 4 + 3 + 3)
-                 (((0, 64), 30), None, ((160, 320), 100))]),
+    (4, 688, 128, [(None, ((256, 320), 20), ((0, 160), 150))], 1024),      # 224 rows of 352, 170 of them to the LM head (6 m-tiles, one per row group)
+    (32, 8192, 192, [(None, ((256, 320), 20), ((0, 160), 150)),             # 448 of 704 and 300 (10 m-tiles, one per row group)
+                     (((0, 64), 30), None, ((160, 320), 100))], 1024),
+    (4, 688, 128, [(None, ((256, 320), 50), ((0, 160), 150))], 16416),     # 7 of 11 m-tiles: 3 + 2 + 2
+    (4, 688, 128, [(None, ((256, 320), 50), ((0, 160), 150))], 33056),     # 4 + 3
+    (32, 8192, 192, [(None, ((256, 320), 20), ((0, 160), 150)),             # 11 of 22: 4 + 4 + 3
+                     (((0, 64), 30), None, ((160, 320), 140))], 33056),
 ])
-def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows, requests):
+def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows, requests, vocab):
     """Block steps sized for more than 256 rows in which branches have finished, last windows are clipped and only a part
     of the rows is masked: whole row groups of the layer GEMMs are skipped (gate/up with tiles of 128 and of 192 rows; with
     32 heads also the q|k|v projection, which stores partial tiles), and the LM head's live m-tiles are dealt to fewer row groups than are launched.  Logits, tokens, K,V and the commit
     against the oracle in fp64, from a poisoned workspace."""
     from paper_2605_29233_amd import BB_INIT, BB_PERIODIC
     from paper_2605_29233_amd.binding import gemm_plan
-    shape = ModelShape("livetest", 2, 256, heads, heads, 64, d_ffn, 1024)
+    shape = ModelShape("livetest", 2, 256, heads, heads, 64, d_ffn, vocab)
     blocks, G, L_p, n = (64, 128, 160), 320, 20, len(requests)
     decode = DecodeParams(0.9, 0.5, 400, 8, 0)
     bound = n * sum(blocks)
@@ -217,7 +221,7 @@ def test_step_with_fewer_live_rows_than_it_is_sized_for(heads, d_ffn, tile_rows,
     assert (gemm_plan(bound, 3 * 64 * heads, 256, True)["nt"] == 2) == (heads == 32)
     weights = dict(gen_weights(shape, 23))
     om = OracleModel(shape, weights, np.float64)
-    print("live rows, ffn", d_ffn, flush=True)
+    print("live rows, ffn", d_ffn, "vocabulary", vocab, flush=True)
     bb = make_bb(shape, decode, weights, 3, L_p + G, G, bound, max_requests=n, poison=True)
     try:
         rng = np.random.default_rng(23)
@@ -368,6 +372,57 @@ def test_vocabulary_reduction_ties_take_the_lowest_token_id():
         finally:
             bb.close()
     assert checked >= 8 * 8
+
+
+@pytest.mark.parametrize("gen_len", [31, 33, 65, 97, 160])
+def test_vocabulary_ties_in_every_body_of_the_lm_head(gen_len):
+    """More than 128 column groups and 1, 2, 3, 4 and 5 m-tiles, which are then one row group.  The LM-head row of the token that wins a row is
+    copied to another token: beside it, in another lane group (4 columns on), column tile (16, 32), wave (64) or column group, below and above.
+    The two logits are equal, the argmax is the lower id, the confidence counts both; and without stored logits (as in
+    production) token, confidence and log-sum-exp have the same bits."""
+    from paper_2605_29233_amd import BB_INIT
+    shape = ModelShape("tietest", 1, 128, 2, 2, 64, 64, 33056)
+    decode = DecodeParams(0.9, 0.5, 400, 8, 0)
+    base = dict(gen_weights(shape, 37))
+    prompt = gen_prompt(shape, 37, 0, 20)
+    offsets = (1, -1, 4, -4, 16, -16, 32, -32, 64, -64, 200, -200, 1024, -1024)
+
+    def init(weights, keep):
+        bb = make_bb(shape, decode, weights, 1, 20 + gen_len, gen_len, 32, poison=True)
+        try:
+            bb.keep_logits(keep)
+            bb.refresh([bb.request_open(prompt, gen_len, (32,))], BB_INIT)
+            v = bb.latest_view()
+            assert v.m_lm == gen_len
+            return (v.argmax(), v.conf(), v.lse()) + ((v.logits(),) if keep else ())
+        finally:
+            bb.close()
+
+    print("vocabulary ties", gen_len, flush=True)
+    pred = init(base, True)[0]
+    tokens = [int(t) for t in dict.fromkeys(pred.tolist())]
+    checked = 0
+    for shift in range(len(offsets)):
+        lm, pairs, used = base["lm_head"].clone(), {}, set(tokens)
+        for i, t in enumerate(tokens):
+            u = t + offsets[(i + shift) % len(offsets)]
+            if 0 <= u < shape.vocab and u != shape.mask_id and u not in used:
+                lm[u] = lm[t]
+                pairs[t] = u
+                used.add(u)
+        weights = dict(base, lm_head=lm)
+        am, conf, lse, lg = init(weights, True)
+        for got, want in zip(init(weights, False), (am, conf, lse)):
+            assert np.array_equal(got, want)
+        x = lg.astype(np.float64)
+        x[:, shape.mask_id] = -np.inf
+        total = np.exp(x - x.max(1, keepdims=True)).sum(1)
+        assert np.abs(conf - 1.0 / total).max() <= 1e-5
+        for j, t in enumerate(pred.tolist()):
+            if t in pairs:
+                assert lg[j, t] == lg[j, pairs[t]] and am[j] == min(t, pairs[t]), (shift, j, t, pairs[t], am[j])
+                checked += 1
+    assert checked >= gen_len * len(offsets) // 2
 
 
 def test_equal_rows_give_bit_identical_logits_wherever_they_are_placed():
