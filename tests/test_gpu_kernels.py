@@ -137,6 +137,15 @@ def test_small_matrices_of_many_rows(bb, M, N, K):
     (129, 16416, 192, 2, 3),        # a unit and a half; a last column group of one tile
     (256, 16416, 192, 2, 4),
     (225, 32992, 192, 3, 4),        # 384 columns; eight m-tiles, the last one of one row
+    # long k ranges: the ring of four chunks goes round more than twice, remainders are fetched nine times into one buffer
+    (129, 12288, 1216, 1, 3),       # nine units and a half
+    (193, 12288, 1088, 1, 4),       # eight and a half
+    (160, 16416, 1216, 2, 3),
+    (225, 16416, 1088, 2, 4),
+    (192, 32992, 1216, 3, 4),
+    (256, 32992, 1088, 3, 4),
+    (144, 16416, 1152, 2, 3),       # nine whole units
+    (224, 32992, 1024, 3, 4),       # eight
 ])
 def test_two_row_groups_at_the_edges_of_their_tiles(bb, M, N, K, nt, mt):
     """129 to 256 rows: every tile the plan can take, where units, k splits, row and column groups end: against fp64,

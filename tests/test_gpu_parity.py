@@ -425,6 +425,19 @@ def test_vocabulary_ties_in_every_body_of_the_lm_head(gen_len):
     assert checked >= gen_len * len(offsets) // 2
 
 
+@pytest.mark.parametrize("rows,tile_rows", [(160, 96), (225, 128)])
+def test_swiglu_in_the_epilogue_of_two_row_groups(rows, tile_rows):
+    """Initial forwards of 129 to 256 rows whose gate/up projection has tiles of 256 columns with k whole, so that its epilogue writes the down
+    projection's panel (a last row group of two m-tiles, and one whose last m-tile holds one row), and a refresh and two steps behind it."""
+    from paper_2605_29233_amd.binding import gemm_plan
+    shape = ModelShape("gutest", 1, 256, 4, 4, 64, 8224, 1024)
+    p = gemm_plan(rows, 2 * 8224, 256, True, True)
+    assert (p["nt"], p["mt"], p["split_k"]) == (2, tile_rows // 32, 1), p
+    s = run_case(shape, DecodeParams(0.9, 0.5, 1, 8, 0), rows - 64, 64, (32,), seed=27, max_steps=2)
+    assert s.rep.max_logit_err <= 3e-2
+    check_report(s)
+
+
 def test_equal_rows_give_bit_identical_logits_wherever_they_are_placed():
     """Three branches of one block size in each of two request slots with the same prompt: all six rows see the same
     tokens, so every row of a position must carry the same logit bits, whichever packed row, m-tile or request
