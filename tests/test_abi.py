@@ -109,7 +109,7 @@ def test_gemm_plans_cover_k_fit_the_chip_and_the_register_file(lib):
                     m_tiles, columns = (M + 31) // 32, 128 * p["nt"]
                     if not wide:
                         assert p["mt"] == 4, (M, N, K, p)
-                    elif M > 256 and p["nt"] == 2:          # eight waves
+                    elif M > 256 and p["nt"] == 2:          # tiles of 128 or 192 rows x 256 columns
                         assert p["mt"] in (4, 6), (M, N, K, p)
                     else:           # a body per number of m-tiles, two groups of them above 128 rows; 384 columns: the body of four
                         groups = (m_tiles + 3) // 4
@@ -119,7 +119,7 @@ def test_gemm_plans_cover_k_fit_the_chip_and_the_register_file(lib):
                     tiles = -(-N // columns) * -(-m_tiles // p["mt"])
                     want = min(tiles * p["split_k"], 256) if wide and M > 256 and p["nt"] == 2 else min(tiles, 256) * p["split_k"]
                     assert p["workgroups"] == want, (M, N, K, p, want)
-    # more than 256 rows: tiles of 128 columns and four waves (nt == 1) where a small matrix leaves most CUs without work
+    # more than 256 rows: tiles of 128 columns (nt == 1) where a small matrix leaves most CUs without work
     for M, N, K, small in ((384, 768, 256, True), (384, 256, 256, True), (384, 256, 688, True), (1400, 768, 256, True), (640, 4096, 512, True),
                            (272, 128, 4096, True), (640, 768, 4096, False), (768, 4096, 4096, False), (1400, 4096, 512, False), (3072, 12288, 4096, False)):
         p = binding.gemm_plan(M, N, K, True)
