@@ -1079,7 +1079,7 @@ extern "C" int bb_debug_gemm_plan(int M, int N, int K, int wide, int fusable, in
     const GemmPlan p = wide ? gemm_plan_wide(M, N, K, 0, 0, fusable != 0) : gemm_plan(M, N, K, 0, 0);
     const int mt_total = (M + 31) / 32, n_groups = (N / 32 + p.wv * p.nt - 1) / (p.wv * p.nt), m_groups = (mt_total + p.mt - 1) / p.mt;
     out[0] = p.split_k; out[1] = p.chunks_per_split; out[2] = p.nt; out[3] = p.mt;
-    out[4] = p.rounds ? std::min(n_groups * m_groups * p.split_k, 256) : std::min(n_groups * m_groups, 256) * p.split_k;
+    out[4] = wide && M > 128 ? std::min(n_groups * m_groups * p.split_k, 256) : std::min(n_groups * m_groups, 256) * p.split_k;
     return BB_OK;
 }
 

@@ -141,19 +141,6 @@ static inline __host__ __device__ float bf16_to_f32(uint16_t b) {
     union { float f; uint32_t u; } v; v.u = ((uint32_t)b) << 16; return v.f;
 }
 
-// ---- fp8 encodings (round to nearest even, finite inputs) ---------------------------------------------------
-// e4m3 (bias 7, no infinities, largest finite value 448, subnormals are multiples of 2^-9); saturates.
-static inline __host__ __device__ uint8_t f32_to_e4m3(float x) {
-    union { float f; uint32_t u; } v; v.f = x;
-    const uint8_t sign = (uint8_t)((v.u >> 24) & 0x80u);
-    v.u &= 0x7FFFFFFFu;
-    if (!(v.f < 448.0f)) return sign | 0x7E;
-    if (v.f < 0.015625f) return sign | (uint8_t)(int)rintf(v.f * 512.0f);       // 0..8: the subnormals, 8 = 2^-6 itself
-    const uint32_t u = v.u + 0x7FFFFu + ((v.u >> 20) & 1u);                     // round the mantissa to 3 bits
-    const uint32_t code = (((u >> 23) - 120u) << 3) | ((u >> 20) & 7u);         // exponent rebased from 127 to 7
-    return sign | (uint8_t)(code > 0x7Eu ? 0x7Eu : code);
-}
-
 #ifdef __HIPCC__
 // Eight consecutive k of one activation row into a packed panel: two bf16 terms, or (wide) fp16 + e5m2.
 static __device__ __forceinline__ void store_panel8(u32x4* Apk, int m, int k8, int mt_total, const float (&y)[8], int wide) {
@@ -199,19 +186,6 @@ static __device__ __forceinline__ void zero_panel8(u32x4* Apk, int m, int k8, in
         *reinterpret_cast<uint2*>(reinterpret_cast<char*>(Apk) + wideA_lo_byte(m, k8, mt_total)) = make_uint2(0u, 0u);
     }
 }
-// Four fp16 weights (two dwords, already scaled by 2^S) -> four e4m3 values of w 2^(S - BB_LO_SHIFT): the hardware
-// conversion divides by its scale operand and rounds to nearest even; |w 2^S| < 2^15 keeps the result below e4m3's 448.
-// Each conversion writes one half of its destination and keeps the other, which the second one overwrites: `old` may be
-// anything, best what the destination register holds.
-static __device__ __forceinline__ int fp16x4_to_e4m3x4(unsigned int d0, unsigned int d1, int old) {
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    typedef short i16x2 __attribute__((ext_vector_type(2)));
-    const float sc = (float)(1 << BB_LO_SHIFT);
-    i16x2 a = __builtin_bit_cast(i16x2, old);
-    a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(a, __builtin_bit_cast(f16x2, d0), sc, false);
-    a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(a, __builtin_bit_cast(f16x2, d1), sc, true);
-    return __builtin_bit_cast(int, a);
-}
 #endif
 
 // ---- running (max, rescaled sum of exponentials, argmax) of a row of logits ------------------------------
@@ -228,7 +202,7 @@ static __device__ __forceinline__ MSI msi_merge(MSI a, MSI b) {
 }
 
 // ---- kernel launchers (each enqueues on `s`) -----------------------------------------------------
-struct GemmPlan { int split_k; int chunks_per_split; int nt; int mt = 4; int wv = 4; bool rounds = false; };      // mt: m-tiles of 32 rows per workgroup; wv: its waves; rounds: (tile, split) items in as many rounds as it takes
+struct GemmPlan { int split_k; int chunks_per_split; int nt; int mt = 4; int wv = 4; };      // mt: m-tiles of 32 rows per workgroup; wv: its waves
 GemmPlan gemm_plan(int m_rows, int N, int K, int forced_split, int forced_nt);
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable = false);     // wide-format kernel: may take mt = 6
 // Epilogue of launch_gemm: partial tiles P[split][m][n] (default); SiLU(gate) * up as the down projection's panel
@@ -253,7 +227,7 @@ void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, fl
 // The same for more than 128 rows (plan.mt 3, 4 or 6 m-tiles, plan.nt column tiles per wave).  rows_live (device, may be null): row
 // count of this pass; row groups past it are skipped.
 void launch_gemm_panel(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
-                       hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps);
+                       hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st);
 void launch_tile_weights_wide(const uint16_t* src, int rows, int K, u32x4* dst, float* scale_out, int dst_row0, int interleave,
                               hipStream_t s);
 void launch_pack_rows_wide(const float* A, int M, int K, u32x4* Apk, int mt_total, hipStream_t s);

@@ -44,8 +44,7 @@ __global__ __launch_bounds__(256, 1) void gemm_panel_kernel(const u32x4* __restr
                                                             const u32x4* __restrict__ Apk, float* __restrict__ P,
                                                             size_t split_stride, int ldp, int mt_total, int n_tiles,
                                                             int total_chunks, int chunks_per_split, int n_split, int tiles_x,
-                                                            const int* __restrict__ rows_live, u32x4* __restrict__ Opk,
-                                                            const float* __restrict__ ssq, int nblk, float inv_d, float eps) {
+                                                            const int* __restrict__ rows_live, u32x4* __restrict__ Opk) {
     constexpr int T = 2 * NT, R = 2 * MT;                   // 16 x 16 accumulator tiles per wave: T of columns, R of rows
     constexpr int STAGE = MT * 4096, LO = 4 * STAGE, LO_CHUNK = MT * 2048;      // LDS: fp16 fragments of four chunks, remainders of a unit
     constexpr int LDT = 16 * T + 4;                         // store slices: row stride in floats
@@ -255,19 +254,12 @@ __global__ __launch_bounds__(256, 1) void gemm_panel_kernel(const u32x4* __restr
             for (int m = 0; m < R; ++m) {
                 if (m / 2 >= mt_cnt) break;
                 const int row = (mt0 + m / 2) * 32 + (m & 1) * 16 + c16;
-                // ssq: the activation rows were packed without their RMSNorm scale (sums of squares per block of columns instead)
-                float inv = 1.0f;
-                if (ssq) {
-                    float t = 0.f;
-                    for (int b = 0; b < nblk; ++b) t += ssq[row * nblk + b];
-                    inv = 1.0f / sqrtf(t * inv_d + eps);
-                }
                 float act[2][4], y[8];
 #pragma unroll
                 for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float gt = acc[tt][m][r] * inv, up = acc[T - 2 + tt][m][r] * inv;
+                        const float gt = acc[tt][m][r], up = acc[T - 2 + tt][m][r];
                         act[tt][r] = gt / (1.0f + expf(-gt)) * up;
                     }
 #pragma unroll
@@ -308,11 +300,11 @@ __global__ __launch_bounds__(256, 1) void gemm_panel_kernel(const u32x4* __restr
 }
 
 void launch_gemm_panel(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
-                       hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps) {
+                       hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st) {
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64, tiles_x = (n_tiles + 4 * plan.nt - 1) / (4 * plan.nt), tiles_y = (mt_total + plan.mt - 1) / plan.mt;
     const size_t split_stride = (size_t)mt_total * 32 * N;
     dim3 grid(std::min(tiles_x * tiles_y * plan.split_k, 256));
-#define PARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, plan.split_k, tiles_x, rows_live, swiglu_out, ssq, nblk, 1.0f / (float)K, rms_eps
+#define PARGS Wt, wscale, Apk, P, split_stride, N, mt_total, n_tiles, total_chunks, plan.chunks_per_split, plan.split_k, tiles_x, rows_live, swiglu_out
 #define PLAUNCH(MT_, NT_, EPI_) hipExtLaunchKernelGGL(HIP_KERNEL_NAME(gemm_panel_kernel<MT_, NT_, EPI_>), grid, dim3(256), 0, s, st.start, st.stop, 0, PARGS)
 #define PLAUNCH_MT(NT_, EPI_) do { if (plan.mt == 3) PLAUNCH(3, NT_, EPI_); else PLAUNCH(4, NT_, EPI_); } while (0)
     if (plan.mt == 6) { if (swiglu_out) PLAUNCH(6, 2, PEPI_SWIGLU); else PLAUNCH(6, 2, PEPI_PARTIAL); }

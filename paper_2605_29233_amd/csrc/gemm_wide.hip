@@ -44,8 +44,9 @@ static __device__ __forceinline__ i32x8 as_i32x8(const u32x4& a, const u32x4& b)
     r[4] = (int)b[0]; r[5] = (int)b[1]; r[6] = (int)b[2]; r[7] = (int)b[3];
     return r;
 }
-// Eight fp16 weights -> eight e4m3 values (fp16x4_to_e4m3x4 twice, starting from the sources themselves, which saves
-// clearing a register).
+// Eight fp16 weights (scaled by 2^S) -> eight e4m3 values of w 2^(S - BB_LO_SHIFT): the hardware conversion divides by its scale
+// operand and rounds to nearest even; |w 2^S| < 2^15 keeps the result below e4m3's 448.  Each conversion writes one half of its
+// destination and keeps the other, which the second one overwrites: starting from the sources saves clearing a register.
 static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo, int& hi) {
     // (the dwords are copied out first: a bit cast applied directly to a vector element picked element 0 every time)
     const unsigned int d0 = w[0], d1 = w[1], d2 = w[2], d3 = w[3];
@@ -427,14 +428,10 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
         p.mt = block_step_body(mt_total, p.nt);
         return p;
     }
-    if (forced_split > 0) {
-        GemmPlan p = gemm_plan(m_rows, N, K, forced_split, forced_nt);
-        p.rounds = true;
-        return p;
-    }
+    if (forced_split > 0) return gemm_plan(m_rows, N, K, forced_split, forced_nt);
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;
-    best.nt = 2; best.rounds = true;
+    best.nt = 2;
     double best_t = 1e30;
     for (int mt = 4; mt <= 6; mt += 2) {
         const double chunk_us = mt == 6 ? 1.67 : 1.18, tile_us = 3.8;
@@ -455,7 +452,7 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
         if ((total_chunks + cps - 1) / cps != sp) continue;
         const double fill = base * sp / 256.0, partial = sp * (double)mt_total * 32 * N * 4 * (sp == 1 ? 0.166e-6 : 0.25e-6);
         const double t = 4.0 + cps * 0.585 * (1.0 + 0.8 * fill * fill * fill) + partial + (fusable ? 8.0 : 0.0);
-        if (t < best_t) { best_t = t; best.split_k = sp; best.chunks_per_split = cps; best.nt = 1; best.rounds = false; best.mt = block_step_body(mt_total, 1); }
+        if (t < best_t) { best_t = t; best.split_k = sp; best.chunks_per_split = cps; best.nt = 1; best.mt = block_step_body(mt_total, 1); }
     }
     return best;
 }
@@ -464,7 +461,7 @@ void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, fl
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps,
                       const int* rows_live) {
     if (mt_total > 4 || plan.nt == 3) {
-        launch_gemm_panel(Wt, wscale, Apk, P, mt_total, N, K, plan, s, mt_total > 8 ? rows_live : nullptr, swiglu_out, st, ssq, nblk, rms_eps);
+        launch_gemm_panel(Wt, wscale, Apk, P, mt_total, N, K, plan, s, mt_total > 8 ? rows_live : nullptr, swiglu_out, st);
         return;
     }
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64, nt = plan.nt;
