@@ -471,7 +471,7 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
     // the layer GEMMs run in the wide format (every kernel that writes a panel for them is told so); the LM head keeps two
     // bf16 terms (its rows are the masked ones only)
     const int wide = !c->wide_off;
-    const bool defer = rows_cap <= BB_DEFER_ROWS;     // block steps of at most 128 rows: every gate/up GEMM has a k split, its consumer is the SwiGLU kernel
+    const bool defer = rows_cap <= BB_DEFER_ROWS;     // block steps of at most 128 rows: the consumers of the projections apply the norm's scale
     // kind: 0 LM head, 1 O/down, 2 gate/up, 3 QKV (index of the tuning overrides)
     // swiglu_out: where the gate/up projection may put SiLU(gate) * up itself; it does when its k range
     // is not split (then 0 is returned and no partial sums exist)

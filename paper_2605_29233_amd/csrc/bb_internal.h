@@ -224,8 +224,8 @@ void launch_pack_rows(const float* A, int M, int K, u32x4* Apk, int mt_total, hi
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out = nullptr, LaunchStamps st = LaunchStamps(),
                       const float* ssq = nullptr, int nblk = 0, float rms_eps = 0.f, const int* rows_live = nullptr);
-// The same for more than 128 rows (plan.mt 3, 4 or 6 m-tiles, plan.nt column tiles per wave).  rows_live (device, may be null): row
-// count of this pass; row groups past it are skipped.
+// The same for more than 128 rows (plan.mt 3, 4 or 6 m-tiles, plan.nt column tiles per wave).  rows_live (device; null: all of
+// mt_total): row count of this pass; row groups past it are skipped.
 void launch_gemm_panel(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K, GemmPlan plan,
                        hipStream_t s, const int* rows_live, u32x4* swiglu_out, LaunchStamps st);
 void launch_tile_weights_wide(const uint16_t* src, int rows, int K, u32x4* dst, float* scale_out, int dst_row0, int interleave,

@@ -60,8 +60,8 @@ static __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
 // workgroups holds (a small vocabulary leaves CUs idle otherwise) but at least what the largest body needs, each
 // computed by the body for its own number of m-tiles.  The count of live rows depends on every request of the step, so all bodies of a tile
 // width add the same products in the same order: a row's bits depend neither on its place nor on the rows beside it.  With 256-column
-// tiles (vocabularies of 256 and more) that is vocab_tile, bound by the weight stream with one or two m-tiles and by the matrix pipes (two
-// passes per weight) with more; with 128-column tiles the tile below.  Row groups of a column group are neighbours in
+// tiles (vocabularies of 256 and more) that is vocab_tile, bound by the weight stream with one or two m-tiles; with more the matrix work
+// (two passes per weight) weighs as much, pipes busy 0.61 to 0.69 of the resident cycles; with 128-column tiles the tile below.  Row groups of a column group are neighbours in
 // the item order and an XCD takes a contiguous run of items, so the weights are fetched from HBM once.
 // Measured (us; vocabulary 126464, d 4096): 19 live rows 173 (6.0 TB/s), the same with the tile below; 64 rows 184, 181 with the tile below
 // (152064 x 3584: 226, 217), which is no reason for a second order of the sums; 144-152 of 240-252 rows (five m-tiles in one group; before, two

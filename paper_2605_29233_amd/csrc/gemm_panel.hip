@@ -1,22 +1,25 @@
 // Wide-format MFMA GEMM for passes of more than 128 activation rows (wide block steps, refreshes, initial forwards, many requests):
 //     C[m][n] = sum_k A[m][k] * W[n][k]          (operands and precision as in gemm_wide.hip)
 //
-// What bounds it: the matrix pipes, at the clock that the chip's power allows (1.9-2.1 GHz with all CUs at it): nothing but its
-// MFMAs take 0.79 us per 64 k of a 128 x 256 tile, LDS reads add 0.04, the conversions to e4m3 0.1, the loads from
-// the L2s 0.1, weights that come from HBM another 0.1.  Hence 16 x 16 MFMAs (16x16x32 fp16, 16x16x128 fp8), whose accumulators pass half as
-// often per product as those of 32 x 32 (2.07 PFLOP/s of the mix against 1.84), and operands that move as little as they can: four
-// waves, one per SIMD, each with 32 NT columns of weights in registers and the activation panel in LDS for all of them.  (Eight
+// What bounds it: first the matrix pipes, but not they alone: they are busy 0.63 of the time at 2.05 GHz (0.70 of the cycles in which
+// the waves are resident).  Nothing but its MFMAs take 0.79 us per 64 k of a 128 x 256 tile at the clock that the chip's power allows
+// with all CUs at it, LDS reads add 0.04, the conversions to e4m3 0.1, the loads from the L2s 0.1, weights that come from HBM another 0.1.
+// A chunk of 192 x 256 takes 1.6 us with all CUs at work (1.2 of MFMAs alone) and 1.2 with half of them, and about 9 us per tile of prologue,
+// drain and epilogue leave the pipes idle (1536 tiles of 24576 x 3072 rows over k = 512 to 8192).  Hence 16 x 16 MFMAs (16x16x32 fp16, 16x16x128
+// fp8), whose accumulators pass half as often per product as those of 32 x 32 (2.07 PFLOP/s of the mix against 1.84), and operands that
+// move as little as they can: four waves, one per SIMD, each with 32 NT columns of weights in registers and the activation panel in LDS for all of them.  (Eight
 // waves in a grid of 2 x 4, both operands through LDS, read 1.3 to 1.6 times as much LDS per product and convert each weight twice.)
 // A wave owns 2 NT x 2 MT accumulator tiles: 128 x 256 and 192 x 256 per workgroup, 96 or 128 rows x 128 or 384 columns where that
-// fills the chip better.  256 x 256 leaves no register for the operands.
+// fills the chip better.
 //
 // Pipeline, in units of 128 k (two chunks, four halves).  Weights: global -> registers, a half four ahead.  Activations: direct-to-LDS
 // loads, the fp16 terms into a ring of four chunks, the remainders of a unit into one buffer.  One wave per SIMD has nothing to hide a stall,
 // so each half is cut into slots of 2 NT MFMAs with an even share of the LDS reads, conversions and loads.
 //     half 0 | barrier | half 1 (requests this unit's remainders) | half 2 | barrier | half 3 | barrier | fp8 MFMAs of the unit
-// Measured, us per launch, before = the eight-wave kernel (more than 256 rows) and four waves with 32 x 32 MFMAs (up to 256): 240 rows,
-// 12288 x 4096 49 -> 45, 4096 x 12288 43 -> 39, 3584 x 18944 65 -> 55; 768 rows, 12288 x 4096 111 -> 107, 4096 x 12288 97 -> 92; 1536
-// rows, 4096 x 12288 177 -> 170; 3072 rows, gate/up with SwiGLU (24576 x 4096) 732 -> 722.
+// Measured, us per launch, before = the eight-wave kernel (more than 256 rows) and four waves with 32 x 32 MFMAs (up to 256), in turn on one
+// box: 240 rows, 12288 x 4096 44.0 -> 42.5, 4096 x 12288 42.7 -> 39.7, 3584 x 18944 60.2 -> 51.6, gate/up with SwiGLU (24576 x 4096) 84.2 ->
+// 79.7; 768 rows, 12288 x 4096 101.6 -> 98.3, gate/up 209.7 -> 203.5, 4096 x 12288 90.9 -> 90.4; 1536 rows, 4096 x 12288 167.2 -> 164.4; 3072 rows,
+// gate/up 686 -> 671 (the 192-row tile holds 450 of 512 registers: with an applied norm scale in its epilogue it took 511 and 695 us).
 #include "bb_internal.h"
 #include "lds.h"
 #include <hip/hip_ext.h>

@@ -71,8 +71,10 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 //   fp8 step:      MFMAs | LDS reads of step 0 of chunk c+1 | weight fragments 2, 3
 // With three or four m-tiles so; with fewer the activations are written in the first phase and requested in the second, and the weights
 // in the third and fourth, two fragments each.  (All that in so few phases left four m-tiles waiting for the LDS in the first, 24 KB written and 16 read
-// in 256 cycles, and for the load path in the next three: block steps of 56 columns per CU, 37888 x 3584 at 112 rows, 5642 -> 5496 us for
-// 28 layers; with one m-tile the even spread is 1 % slower, its weights come later.)
+// in 256 cycles, and for the load path in the next three.  us per launch at 112 rows, bunched -> spread, in turn: 24576 x 4096 49.6 -> 48.4,
+// 37888 x 3584 72.4 -> 69.1, 3584 x 18944 36.3 -> 35.6, 4096 x 12288 28.4 -> 28.0, but 4096 x 4096, eight chunks per split, 14.7 -> 15.9; of three
+// m-tiles within 1 %.  Whole steps: 37888 x 3584, 28 layers, 5642 -> 5496, 5729 -> 5647 on a second box, none on a third; 24576 x 4096 none.
+// With one m-tile the even spread is 1 % slower, its weights come later.)
 // With few accumulator tiles the registers hold a ring of four weight chunks, and activations that are requested two
 // chunks ahead instead of one (64-row body, 37888 x 3584: 62.5 -> 57.4 us; with more tiles the deeper ring gains nothing).
 template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
@@ -394,8 +396,8 @@ static GemmPlan plan_two_groups(int mt_total, int N, int K, bool fusable) {
 // round: 198 of the CUs have work instead of 148 (37888 x 3584, 56 rows, with SwiGLU: 50.1 against 57.5 us; at 120 rows, where
 // the waves' own work sets the pace, 74.2 against 68.2).
 //
-// 65 to 128 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 rows (the body of three
-// m-tiles by one common factor): time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of
+// 65 to 128 rows: the candidates (tile width, k split) are priced by a model of 150 measured launches at 120 and 240 rows (those of 240
+// with the two row groups that this kernel had then; the body of three m-tiles by one common factor): time of one 64-k chunk of a workgroup, at least what its share of the weight stream takes (6 TB/s; of
 // everything the L2s deliver, 15 TB/s), 6 us of prologue and store per tile, and the partial tiles, written here and read by the
 // consumer.  (12288 x 4096 at 120 rows: four splits on 192 CUs 27.6 us, five on 240 27.5 and a longer consumer.)
 //
@@ -406,16 +408,18 @@ static GemmPlan plan_two_groups(int mt_total, int N, int K, bool fusable) {
 // columns with SwiGLU in the epilogue 148; 24576 x 4096 in one round of 256 columns 84).  Splits take whole units of 128 k.
 //
 // With more rows tiles of 128 or 192 rows x 256 columns and their k splits
-// are priced by a model fitted to 800 measured launches of the kernel before this one (272..4206 rows, N 3584..37888, K
-// 3584..18944; 4.6 % rms; the present one takes 2 to 7 % less at every one of them): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
-// workgroups except that a last round which leaves CUs idle runs at a higher clock (the chip is at its power limit), and
-// the partial tiles, written here and read by the consumer launch once per k split.
+// are priced by a model fitted to 800 measured launches of the eight-wave kernel that these passes had before (272..4206 rows, N 3584..37888, K
+// 3584..18944; 4.6 % rms): time of one 64-k chunk of a workgroup tile, a fixed cost per tile, whole rounds of 256
+// workgroups except that a last round which leaves CUs idle runs at a higher clock, and
+// the partial tiles, written here and read by the consumer launch once per k split.  The constants are not those of gemm_panel_kernel (a chunk of 192
+// rows takes it 1.6 us, a tile 9 us more); its choices were measured on it, 68 shapes of 273..4120 rows with every tile and up to eight splits: 0.3 % more than
+// the best on average, 5 % at 931 x 3584 x 3584, and just above 256 rows, where tiles of 96 rows x 128 columns would be better, 6 to 9 % and once 27 % (273 x 3584 x 3584).
 // Where both tiles price within 5 % the larger one is taken: it fetches a fifth less per product.  fusable: the caller
 // can take SiLU(gate) * up from the epilogue when k is not split; then there are no partial tiles and no launch for it.
 // Beside them tiles of 128 columns, where they and their k splits fit one round: small matrices leave
 // most CUs without work either way, and the smaller tile is through sooner.  Its price is fitted to 175
-// shapes (272..4096 rows, N 128..4096, K 64..4096); us of 256 / of 128 columns: 768 x 256 at 512 rows 8.8 /
-// 5.9, 256 x 688 at 1024 rows 9.1 / 6.2, 1408 x 256 at 1536 rows 9.9 / 7.2, but 3584 x 3584 at 1024 rows 37 / 46.
+// shapes (272..4096 rows, N 128..4096, K 64..4096) of the kernels before; on the present one, us of 256 / of 128 columns: 768 x 256 at 512 rows 8.8 /
+// 5.9, 256 x 688 at 1024 rows 10.5 / 6.9, 1408 x 256 at 1536 rows 9.8 / 7.1, but 3584 x 3584 at 1024 rows 38 / 43.
 GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_nt, bool fusable) {
     const int mt_total = (m_rows + 31) / 32;
     if (mt_total <= 8) {
@@ -460,7 +464,7 @@ GemmPlan gemm_plan_wide(int m_rows, int N, int K, int forced_split, int forced_n
 void launch_gemm_wide(const u32x4* Wt, const float* wscale, const u32x4* Apk, float* P, int mt_total, int N, int K,
                       GemmPlan plan, hipStream_t s, u32x4* swiglu_out, LaunchStamps st, const float* ssq, int nblk, float rms_eps,
                       const int* rows_live) {
-    if (mt_total > 4 || plan.nt == 3) {
+    if (mt_total > 4 || plan.nt == 3) {         // (up to 256 rows both row groups are computed whatever the live row count: only the passes of more rows look at it)
         launch_gemm_panel(Wt, wscale, Apk, P, mt_total, N, K, plan, s, mt_total > 8 ? rows_live : nullptr, swiglu_out, st);
         return;
     }
