@@ -123,7 +123,7 @@ def steady_state(bb, w, ids, steps, warmup, profile_steps, torch):
     tfl = g["flops"] / 1e12 / (raw_ms / 1e3)
     roof = {"bound": "hbm" if hbm_bound else "mfma",
             "kernel": "%s and the LM head's gemm_kernel (MFMA GEMM launches of the block forward: %s)"
-                      % (("gemm_wide_kernel", "weight streaming") if hbm_bound else ("gemm_panel_kernel", "many rows")),
+                      % ("gemm_wide_kernel" if sized <= 128 else "gemm_panel_kernel", "weight streaming" if hbm_bound else "many rows"),
             "achieved": gbs if hbm_bound else tfl, "peak": HBM_PEAK_GBS if hbm_bound else MFMA_BF16_PEAK_TFLOPS,
             "unit": "GB/s" if hbm_bound else "TFLOP/s",
             "frac": gbs / HBM_PEAK_GBS if hbm_bound else tfl / MFMA_BF16_PEAK_TFLOPS,
