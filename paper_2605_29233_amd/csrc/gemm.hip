@@ -320,10 +320,6 @@ static __device__ __forceinline__ void gemm_tile(const GemmArgs& g, u32x4* lds_r
     __syncthreads();                                        // the next tile's prologue overwrites the LDS slices
 }
 
-template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
-    if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
-}
-#define IC(v) std::integral_constant<int, (v)>{}
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The LM head's workgroup tile for MT m-tiles from mt0 x the 256 columns of group bx (k whole): 16 x 16 MFMAs, weights global -> registers

@@ -22,6 +22,7 @@
 // gate/up 686 -> 671 (the 192-row tile holds 450 of 512 registers: with an applied norm scale in its epilogue it took 511 and 695 us).
 #include "bb_internal.h"
 #include "lds.h"
+#include "sched.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <type_traits>
@@ -33,11 +34,6 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 static __device__ __forceinline__ f16x8 as_f16x8(const u32x4& v) { return __builtin_bit_cast(f16x8, v); }
-
-template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
-    if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
-}
-#define IC(v) std::integral_constant<int, (v)>{}
 
 #define PEPI_PARTIAL 0
 #define PEPI_SWIGLU 1

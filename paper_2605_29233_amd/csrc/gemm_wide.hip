@@ -33,7 +33,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define KC 4                                    // fp16 k-steps (of 16) per chunk = weight fragments per (tile, chunk)
 
-#define IC(v) std::integral_constant<int, (v)>{}
 #define WEPI_PARTIAL 0
 #define WEPI_SWIGLU 1
 
@@ -77,9 +76,6 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 // With one m-tile the even spread is 1 % slower, its weights come later.)
 // With few accumulator tiles the registers hold a ring of four weight chunks, and activations that are requested two
 // chunks ahead instead of one (64-row body, 37888 x 3584: 62.5 -> 57.4 us; with more tiles the deeper ring gains nothing).
-template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
-    if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
-}
 template <int NT, int EPI, int MT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* __restrict__ Wt, const float* __restrict__ wscale,
                                                            const u32x4* __restrict__ Apk, float* __restrict__ P,

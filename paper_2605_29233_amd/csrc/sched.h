@@ -1,6 +1,13 @@
-// Schedule groups of the software-pipelined GEMM loops.
+// Unrolling and schedule groups of the software-pipelined GEMM loops.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <type_traits>
+
+// f(0), ..., f(N - 1) with the index as a constant of its own type
+#define IC(v) std::integral_constant<int, (v)>{}
+template <int N, int I = 0, class F> static __device__ __forceinline__ void unroll(F&& f) {
+    if constexpr (I < N) { f(std::integral_constant<int, I>{}); unroll<N, I + 1>(f); }
+}
 
 // sched_group_barrier masks
 #define SG_MFMA 0x008
