@@ -479,14 +479,14 @@ static int forward(bb_ctx* c, int rows_cap, int lm_cap, int mode, int seg_base, 
                     int rows, int mtt, int klass, u32x4* swiglu_out = nullptr, const float* ssq = nullptr, int nblk = 0) {
         // tile width: the two-term kernel's fused SwiGLU epilogue pairs two tiles per wave (passes with more than 128 rows);
         // otherwise the plan picks it.  With at most 128 rows the norm's scale is deferred: the wide-format kernel's SwiGLU epilogue
-        // applies it (ssq) where the plan comes out with two tiles per wave and k whole (many columns: the Dream
-        // shape), the two-term kernel leaves it to the separate SwiGLU kernel.
+        // applies it (ssq) where the plan leaves k whole (many columns: the Dream shape; few rows; small models), the two-term kernel
+        // leaves it to the separate SwiGLU kernel.
         // The overrides hold up to 128 rows: the buffers have room for any of their splits only there (buf_elems).
         const bool tuned = rows <= 128;
         const int nt = tuned && c->force_nt[kind] > 0 ? c->force_nt[kind] : (swiglu_out && !defer && !wide ? 2 : 0);
         GemmPlan p = wide ? gemm_plan_wide(rows, N, K, 0, nt, swiglu_out && !defer) : gemm_plan(rows, N, K, 0, nt);
         if (tuned && c->force_split[kind] > 0) p = gemm_plan(rows, N, K, c->force_split[kind], c->force_nt[kind]);
-        const bool fused = swiglu_out && (wide || !defer) && p.split_k == 1 && p.nt == 2;
+        const bool fused = swiglu_out && (wide || !defer) && p.split_k == 1 && (p.nt == 2 || (wide && p.nt == 1 && mtt <= 4));
         PROF_STAMPED(klass, 2.0 * N * K, 2.0 * rows * (double)N * K);
         if (wide) launch_gemm_wide(Ww, wscale, A, P, mtt, N, K, p, s, fused ? swiglu_out : nullptr, prof_scope_.stamps(),
                                    fused ? ssq : nullptr, nblk, m.rms_eps, D.counts);

@@ -297,6 +297,39 @@ def test_swiglu_in_the_gemm_epilogue_with_the_deferred_norm_scale():
         assert np.abs(V - Vr).max() <= 1e-3 * max(1.0, np.abs(Vr).max())
 
 
+@pytest.mark.parametrize("blocks,d_ffn", [
+    ((8,), 64),                     # one m-tile; a single workgroup
+    ((32, 24), 688),                # two, the second with padding rows; padded columns of the fused matrix
+    ((64, 32), 1376 + 16),          # three
+    ((64, 48, 16), 33024 + 16),     # four; more column groups than workgroups (one each of 256): the halves' place is used again
+])
+def test_swiglu_across_two_waves_is_the_one_within_a_wave(blocks, d_ffn):
+    """The gate/up projection with one column tile per wave and k whole finishes SiLU(gate) * up with halves that two waves swap through
+    LDS; with two tiles per wave both factors are in one wave's registers.  Same sums, same expressions: logits and caches equal bit for bit."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("swaptest", 2, 256, 4, 4, 64, d_ffn, 1024, qkv_bias=False)
+    weights = dict(gen_weights(shape, 11))
+    prompt = gen_prompt(shape, 11, 0, 40)
+    G, res = 64, {}
+    for nt in (1, 2):
+        b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 8), Limits(1, len(blocks), 40 + G, G, sum(blocks)), poison_workspace=True)
+        try:
+            b.load_weights(weights.items())
+            b.keep_logits(True)
+            b.set_gemm_plan(2, nt, 1)
+            rid = b.request_open(prompt, G, blocks)
+            b.refresh([rid], BB_INIT)
+            b.merge_commit([rid])
+            print(f"swiglu swap blocks={blocks} d_ffn={d_ffn} nt={nt}", flush=True)
+            v = b.denoise_step([rid])
+            res[nt] = [v.logits().copy()] + [x for k in range(len(blocks)) for l in range(2) for x in b.get_kv(rid, k, l)]
+        finally:
+            b.close()
+    for a, r in zip(res[1], res[2]):
+        assert np.isfinite(a[..., :-1]).all() and np.array_equal(a, r)
+
+
 @pytest.mark.parametrize("M", [1, 31, 33, 63, 65, 95, 97, 128, 129, 160, 191, 193, 256])
 @pytest.mark.parametrize("N,K", [(224, 64), (160, 208), (4640, 320), (608, 1040), (33280, 128)])
 def test_wide_format_gemm_for_every_number_of_row_tiles(bb, M, N, K):
