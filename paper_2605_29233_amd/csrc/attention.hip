@@ -387,29 +387,40 @@ template <int HD>
 __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const float* __restrict__ part, u32x4* __restrict__ Apk,
                                                                 int mt_total, int seg_base, int n_splits, int wide) {
     const int gbr = seg_base + blockIdx.z;
-    const int seg_rows = D.seg_rows[gbr];
-    if (seg_rows == 0) return;
-    const int group = D.hq / D.hkv, nflat = seg_rows * group, wg_base = blockIdx.y * 32;
-    if (wg_base >= nflat) return;
-    const int kvh = blockIdx.x, seg_off = D.seg_off[gbr];
+    const int seg_rows = D.seg_rows[gbr], seg_off = D.seg_off[gbr], group = D.hq / D.hkv, nflat = seg_rows * group, wg_base = blockIdx.y * 32, kvh = blockIdx.x;
     const float* src = part + (((size_t)blockIdx.z * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * n_splits * (64 + 32 * HD);
+    // (The loads of four splits are on their way together, and ask for their places before the segment's size is known: a tile past its end has a place and is not
+    // stored.  us per launch: 32 tiles in three splits 6.4 -> 4.8, 100 in two 5.6 -> 5.0.)
     for (int item = threadIdx.x; item < 32 * (HD / 8); item += 256) {
         const int q = item / (HD / 8), d8 = item % (HD / 8);
-        const int f = wg_base + q;
-        if (f >= nflat) continue;
-        float M = -INFINITY;
-        for (int s = 0; s < n_splits; ++s) M = fmaxf(M, src[s * (64 + 32 * HD) + q]);
-        float lsum = 0.f, y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < n_splits; ++s) {
-            const float* ps = src + s * (64 + 32 * HD);
-            const float ms = ps[q], wgt = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);
-            lsum += wgt * ps[32 + q];
-            const float4 a = *reinterpret_cast<const float4*>(ps + 64 + q * HD + d8 * 8);
-            const float4 b = *reinterpret_cast<const float4*>(ps + 64 + q * HD + d8 * 8 + 4);
-            y[0] += wgt * a.x; y[1] += wgt * a.y; y[2] += wgt * a.z; y[3] += wgt * a.w;
-            y[4] += wgt * b.x; y[5] += wgt * b.y; y[6] += wgt * b.z; y[7] += wgt * b.w;
+        float M = -INFINITY, lsum = 0.f, y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < n_splits; s0 += 4) {
+            float m[4], l[4];
+            float4 a[4], b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float* ps = src + min(s0 + u, n_splits - 1) * (64 + 32 * HD);
+                m[u] = ps[q]; l[u] = ps[32 + q];
+                a[u] = *reinterpret_cast<const float4*>(ps + 64 + q * HD + d8 * 8);
+                b[u] = *reinterpret_cast<const float4*>(ps + 64 + q * HD + d8 * 8 + 4);
+            }
+            if (s0 == 0) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) M = fmaxf(M, m[u]);
+                for (int s = 4; s < n_splits; ++s) M = fmaxf(M, src[s * (64 + 32 * HD) + q]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (s0 + u >= n_splits) break;
+                const float wgt = m[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[u] - M);
+                lsum += wgt * l[u];
+                y[0] += wgt * a[u].x; y[1] += wgt * a[u].y; y[2] += wgt * a[u].z; y[3] += wgt * a[u].w;
+                y[4] += wgt * b[u].x; y[5] += wgt * b[u].y; y[6] += wgt * b[u].z; y[7] += wgt * b[u].w;
+            }
         }
         const float inv = 1.0f / lsum;
+        const int f = wg_base + q;
+        if (f >= nflat) continue;
         const int hig = f / seg_rows, r = f % seg_rows;
         const int m = seg_off + r, k8 = ((kvh * group + hig) * HD) / 8 + d8;
 #pragma unroll
