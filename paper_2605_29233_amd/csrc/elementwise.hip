@@ -85,6 +85,14 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
     const int count = gather ? D.counts[1] : D.counts[0];
     if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
     const int r = gather ? D.lm_row[j] : j;
+    int gbr = 0, nb = 1; size_t mrow = 0;
+    if (gather) {                       // (dependent loads, on their way beside the row's)
+        gbr = D.row_gbr[r];
+        const int slot = gbr / D.max_br;
+        const int gi = D.row_pos[r] - D.hdr[slot].L_p;
+        if (bcast) { gbr = slot * D.max_br; nb = D.hdr[slot].N; }
+        mrow = (size_t)gbr * D.gmax + gi;
+    }
     float* hr = h + (size_t)r * d;
     // the row stays in registers between the two passes: thread t owns the 8-column groups t, t + 256, ...
     constexpr int MAXG = 4;             // d <= 8192
@@ -113,14 +121,6 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
     }
     ss = wg_sum(ss, sh);
     const float inv = 1.0f / sqrtf(ss / (float)d + D.rms_eps);
-    int gbr = 0, nb = 1; size_t mrow = 0;
-    if (gather) {
-        gbr = D.row_gbr[r];
-        const int slot = gbr / D.max_br;
-        const int gi = D.row_pos[r] - D.hdr[slot].L_p;
-        if (bcast) { gbr = slot * D.max_br; nb = D.hdr[slot].N; }
-        mrow = (size_t)gbr * D.gmax + gi;
-    }
 #pragma unroll
     for (int i = 0; i < MAXG; ++i) {
         const int k8 = threadIdx.x + 256 * i;
@@ -489,14 +489,27 @@ void launch_swiglu_epilogue(const Dev& D, const float* gu, int n_partial, size_t
 // Writes confidence, token and lse, also into the probability map of the row's branch (of every branch of the
 // request after the initial forward).
 __global__ __launch_bounds__(256) void vocab_finish_kernel(Dev D, int bcast) {
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int j = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (j >= D.counts[1]) return;
+    // The row's place in the probability map takes three dependent loads: they are on their way beside the tiles, of which eight per lane are asked
+    // for together (494 tiles, 240 rows: 9.0 -> 7.6 us).
+    const int r = D.lm_row[j];
+    int gbr = D.row_gbr[r], nb = 1;
+    const int slot = gbr / D.max_br;
+    int gi = D.row_pos[r] - D.hdr[slot].L_p;
+    const int n_br = D.hdr[slot].N;
     const float4* row = D.vr_part + (size_t)j * D.vr_tiles;
     MSI t = {-INFINITY, 0.f, 0x7fffffff};
-    for (int b = lane; b < D.vr_tiles; b += 64) {
-        const float4 p = row[b];
-        const MSI o = {p.x, p.y, __float_as_int(p.z)};
-        t = msi_merge(t, o);
+    for (int b0 = 0; b0 < D.vr_tiles; b0 += 512) {
+        float4 p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = row[min(b0 + 64 * u + lane, D.vr_tiles - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (b0 + 64 * u + lane >= D.vr_tiles) break;
+            const MSI o = {p[u].x, p[u].y, __float_as_int(p[u].z)};
+            t = msi_merge(t, o);
+        }
     }
     for (int o = 32; o > 0; o >>= 1) {
         const MSI b = {__shfl_xor(t.m, o, 64), __shfl_xor(t.s, o, 64), __shfl_xor(t.i, o, 64)};
@@ -505,11 +518,7 @@ __global__ __launch_bounds__(256) void vocab_finish_kernel(Dev D, int bcast) {
     if (lane != 0) return;
     const float conf = 1.0f / t.s, lse = t.m + logf(t.s);
     D.out_pred[j] = t.i; D.out_conf[j] = conf; D.out_lse[j] = lse;
-    const int r = D.lm_row[j];
-    int gbr = D.row_gbr[r], nb = 1;
-    const int slot = gbr / D.max_br;
-    const int gi = D.row_pos[r] - D.hdr[slot].L_p;
-    if (bcast) { gbr = slot * D.max_br; nb = D.hdr[slot].N; }
+    if (bcast) { gbr = slot * D.max_br; nb = n_br; }
     for (int b = 0; b < nb; ++b) {
         const size_t m = (size_t)(gbr + b) * D.gmax + gi;
         D.map_pred[m] = t.i; D.map_conf[m] = conf; D.map_lse[m] = lse;

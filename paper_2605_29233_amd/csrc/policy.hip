@@ -4,6 +4,7 @@
 // All branch and request state lives in device memory, so a decode loop never has to read
 // anything back.
 #include "bb_internal.h"
+#include <algorithm>
 
 // ---- small workgroup reductions (blockDim.x == 256) ----------------------------------------
 static __device__ __forceinline__ int wg_sum_i(int v, int* sh) {
@@ -32,42 +33,55 @@ static __device__ __forceinline__ float wg_sum_f(float v, float* sh) {
 // Block step: every unfinished branch of the listed requests contributes the rows of its
 // window; rows still masked are additionally listed for the LM head.  Pages under a window
 // that the branch does not own yet are queued for copy-on-write and re-pointed.
-__global__ __launch_bounds__(256) void pack_step_kernel(Dev D, int n_req) {
-    __shared__ int s_rows[256], s_lm[256], s_off[257], s_lmoff[257];
-    const int nb_all = D.max_req * D.max_br, nb = n_req * D.max_br, t = threadIdx.x;
-    const int wave = t >> 6, lane = t & 63;
-    for (int i = t; i < nb_all; i += 256) D.seg_rows[i] = 0;
+//
+// One workgroup, a wave per branch (round robin).  A chain of dependent loads; what the second walk over a branch needs of the first is kept in LDS.
+// Up to sixteen waves and a parallel prefix sum, before four and a serial one: us per launch with 64 branches 46.2 -> 15.2, with six 8.2 -> 6.1.
+__global__ __launch_bounds__(1024) void pack_step_kernel(Dev D, int n_req) {
+    __shared__ int s_rows[256], s_lm[256], s_off[256], s_lmoff[256], s_slot[256], s_start[256], s_tot[8];
+    const int nb_all = D.max_req * D.max_br, nb = n_req * D.max_br, t = threadIdx.x, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    for (int i = t; i < nb_all; i += blockDim.x) D.seg_rows[i] = 0;
     if (t == 0) D.counts[2] = 0;
-    for (int i = t; i < 256; i += 256) { s_rows[i] = 0; s_lm[i] = 0; }
-    __syncthreads();
-    // one wave per branch (round robin): window length and number of masked positions
-    for (int b = wave; b < nb; b += 4) {
+    for (int i = nb + t; i < 256; i += blockDim.x) { s_rows[i] = 0; s_lm[i] = 0; }
+    // window length and number of masked positions
+    for (int b = wave; b < nb; b += waves) {
         const int slot = D.req_list[b / D.max_br], k = b % D.max_br;
         const ReqHeader& H = D.hdr[slot];
         const bb_branch_state& B = D.br[slot * D.max_br + k];
+        const int N = H.N, done = B.done, start = B.start, end = B.end;
         int rows = 0, nlm = 0;
-        if (k < H.N && !B.done) {
-            const int start = B.start, end = B.end;
+        if (k < N && !done) {
             rows = end - start;
             const int* Xr = D.X + ((size_t)slot * D.max_br + k) * D.lpad;
             for (int i = start + lane; i < end; i += 64) nlm += Xr[i] == D.mask_id;
             for (int o = 32; o > 0; o >>= 1) nlm += __shfl_xor(nlm, o, 64);
         }
-        if (lane == 0) { s_rows[b] = rows; s_lm[b] = nlm; D.hdr[slot].pending[k] = rows > 0; }
+        if (lane == 0) { s_rows[b] = rows; s_lm[b] = nlm; s_slot[b] = slot; s_start[b] = start; D.hdr[slot].pending[k] = rows > 0; }
     }
     __syncthreads();
-    if (t == 0) {
-        int a = 0, c = 0;
-        for (int i = 0; i < nb; ++i) { s_off[i] = a; s_lmoff[i] = c; a += s_rows[i]; c += s_lm[i]; }
-        D.counts[0] = a; D.counts[1] = c;
+    // exclusive prefix sums over the at most 256 branches: the first four waves, then over these
+    int rows_sum = 0, lm_sum = 0;
+    if (t < 256) {
+        const int rows = s_rows[t], lm = s_lm[t];
+        rows_sum = rows; lm_sum = lm;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int a = __shfl_up(rows_sum, o, 64), c = __shfl_up(lm_sum, o, 64);
+            if (lane >= o) { rows_sum += a; lm_sum += c; }
+        }
+        if (lane == 63) { s_tot[wave] = rows_sum; s_tot[4 + wave] = lm_sum; }
+        rows_sum -= rows; lm_sum -= lm;
     }
     __syncthreads();
-    for (int b = wave; b < nb; b += 4) {
+    if (t < 256) {
+        for (int w = 0; w < wave; ++w) { rows_sum += s_tot[w]; lm_sum += s_tot[4 + w]; }
+        s_off[t] = rows_sum; s_lmoff[t] = lm_sum;
+    }
+    if (t == 0) { D.counts[0] = s_tot[0] + s_tot[1] + s_tot[2] + s_tot[3]; D.counts[1] = s_tot[4] + s_tot[5] + s_tot[6] + s_tot[7]; }
+    __syncthreads();
+    for (int b = wave; b < nb; b += waves) {
         const int rows = s_rows[b];
         if (rows == 0) continue;
-        const int slot = D.req_list[b / D.max_br], k = b % D.max_br;
-        const bb_branch_state& B = D.br[slot * D.max_br + k];
-        const int start = B.start, end = B.end;
+        const int slot = s_slot[b], k = b % D.max_br, start = s_start[b], end = start + rows;
         const int gbr = slot * D.max_br + k, own = slot * D.phys_per_req + k;
         const int* Xr = D.X + (size_t)gbr * D.lpad;
         if (lane == 0) { D.seg_off[gbr] = s_off[b]; D.seg_rows[gbr] = rows; }
@@ -101,7 +115,10 @@ __global__ __launch_bounds__(256) void pack_step_kernel(Dev D, int n_req) {
     }
 }
 
-void launch_pack_step(const Dev& D, int n_req, hipStream_t s) { pack_step_kernel<<<1, 256, 0, s>>>(D, n_req); }
+void launch_pack_step(const Dev& D, int n_req, hipStream_t s) {
+    const int waves = std::min(16, std::max(4, n_req * D.max_br));
+    pack_step_kernel<<<1, 64 * waves, 0, s>>>(D, n_req);
+}
 
 // Full-sequence forwards of the listed requests, packed into one row list.  mode BB_INIT: the common row of each
 // request (all its branches are still identical), written to the request's shared physical row that every branch's

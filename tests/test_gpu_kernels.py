@@ -1,6 +1,8 @@
 """Kernel-level GPU checks through the C ABI: the MFMA GEMM path (tile edges, split-K, K = 688)
 the q|k|v projection under every tile width and k split, and the bit-equality of the input generator on the
 two devices."""
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -442,5 +444,50 @@ def test_plan_overrides_leave_larger_panels_alone():
             assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]), (kind, nt, split)
             if kind:
                 b.set_gemm_plan(kind, 0, 0)
+    finally:
+        b.close()
+
+
+@pytest.mark.parametrize("requests,blocks", [
+    (7, (4, 8, 16)),                # 21 branches: more than the packing kernel has waves
+    (32, (4, 4, 8, 8, 16, 16, 4, 8)),       # 256: the most there can be
+    (1, (16,)),
+])
+def test_packed_rows_of_many_branches(requests, blocks):
+    """The block step's row list, for every number of branches per wave of the packing kernel: rows in branch order, every position of
+    every unfinished window, the masked ones listed for the LM head in the same order; from the windows and tokens set before."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("packtest", 1, 128, 2, 2, 64, 128, 512, qkv_bias=False)
+    G, Lp, N = 32, 20, len(blocks)
+    rng = np.random.default_rng(requests)
+    b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 8), Limits(requests, N, Lp + G, G, requests * sum(blocks)), poison_workspace=True)
+    try:
+        b.load_weights(gen_weights(shape, 3))
+        b.keep_logits(True)
+        ids = [b.request_open(gen_prompt(shape, 3, i, Lp), G, blocks) for i in range(requests)]
+        rows, lm = [], []
+        for i, rid in enumerate(ids):
+            b.refresh([rid], BB_INIT)
+            X = rng.integers(0, shape.vocab - 1, (N, Lp + G), dtype=np.int32)
+            windows = []
+            for k, blk in enumerate(blocks):
+                start = Lp + blk * int(rng.integers(0, G // blk))
+                done = N > 1 and rng.random() < 0.2
+                w = types.SimpleNamespace(start=start, end=start + blk, done=int(done), mean_conf=0.5)
+                masked = rng.random(blk) < 0.6
+                masked[int(rng.integers(0, blk))] = True
+                X[k, start:start + blk][masked] = shape.mask_id
+                windows.append(w)
+                if not done:
+                    lm += [len(rows) + j for j in range(blk) if masked[j]]
+                    rows += [(rid * N + k, start + j) for j in range(blk)]
+            b.set_state(rid, X, windows)
+        print(f"packed rows requests={requests} branches={N}", flush=True)
+        v = b.denoise_step(ids)
+        gbr, pos = v.rows()
+        assert list(zip(gbr.tolist(), pos.tolist())) == rows
+        assert v.lm_rows().tolist() == lm
+        assert np.isfinite(v.conf()).all()
     finally:
         b.close()
