@@ -97,7 +97,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     constexpr int STAGES_U4 = DW * WA_PER_THREAD * THREADS, SLICES_U4 = WAVES * 32 * MPP * LDT / 4;
     __shared__ u32x4 lds_raw[STAGES_U4 > SLICES_U4 ? STAGES_U4 : SLICES_U4];
     u32x4 (*lds)[WA_PER_THREAD * THREADS] = reinterpret_cast<u32x4 (*)[WA_PER_THREAD * THREADS]>(lds_raw);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     // Weight loads carry the non-temporal hint (every line is used once), and with a k split the (column group, split) items
     // are dealt to the 8 XCDs in contiguous runs in split-major order, so that an XCD's workgroups share one or two k ranges of
     // the activation panel (as in the two-term kernel).
@@ -119,9 +119,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int x = min((bx * WAVES + wave) * NT + t, n_tiles - 1);      // clamped loads; stores are guarded
-        wbase[t] = Wt + (size_t)x * total_chunks * (KC * 64) + lane;
+        wbase[t] = Wt + (size_t)x * total_chunks * (KC * 64);
     }
-    int aoff[WA_PER_THREAD];
+    unsigned aoff[WA_PER_THREAD];
 #pragma unroll
     for (int i = 0; i < WA_PER_THREAD; ++i) {
         const int idx = i * THREADS + threadIdx.x, mt = idx / (BB_WFRAGS * 64), rem = idx % (BB_WFRAGS * 64);
@@ -129,18 +129,23 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     }
     const u32x4* abase = Apk + (size_t)mt0 * (BB_WFRAGS * 64);
     const size_t a_chunk = (size_t)mt_total * (BB_WFRAGS * 64);
+    // Past the end of the k range the loads are issued for the wait counts only: all lanes then read one address (a mask, not a choice, which
+    // would cut the pipeline's block in two).  Before, they fetched the last chunk again two or three times, which the epilogue then waited for: us per launch
+    // at 32 rows, 12288 x 4096 in two splits 20.7 -> 19.0, 24576 x 4096 37.5 -> 35.7, 4096 x 4096 and 4096 x 12288 in eight 14.9 -> 14.2 on average; at 120 rows within 1 %.
+    auto inside = [&](int c) { return (unsigned)((c - c1) >> 31); };
     auto load_a = [&](u32x4 (&a)[WA_PER_THREAD], int c, int lo, int hi) {
         const u32x4* p = abase + (size_t)min(c, c1 - 1) * a_chunk;
 #pragma unroll
-        for (int i = lo; i < hi; ++i) a[i] = p[aoff[i]];
+        for (int i = lo; i < hi; ++i) a[i] = p[aoff[i] & inside(c)];
     };
     auto load_w = [&](u32x4 (&w)[KC][NT], int c, int f_lo, int f_hi) {
         const size_t off = (size_t)min(c, c1 - 1) * (KC * 64);
+        const unsigned l = lane & inside(c);
 #pragma unroll
         for (int f = f_lo; f < f_hi; ++f)
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                w[f][t] = __builtin_nontemporal_load(wbase[t] + off + f * 64);
+                w[f][t] = __builtin_nontemporal_load(wbase[t] + off + f * 64 + l);
             }
     };
     auto read_bh = [&](u32x4 (&b)[MT], int stage, int k) {
@@ -196,11 +201,13 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     // prologue: chunk c0 staged, AD chunks of activations in registers, weights of DW - 1 chunks in flight; loads in the
     // order the loop issues them (activations of a chunk, then its weights), so that the wait counts at the loop head, the
     // more cautious of the two ways in, are those of the steady state
-    unroll<AD>([&](auto I) { load_a(a[I], c0 + I, 0, WA_PER_THREAD); load_w(w[I], c0 + I, 0, KC); });
+    auto first_a = [&](u32x4 (&a)[WA_PER_THREAD], int c) { load_a(a, c, 0, WA_PER_THREAD); __builtin_amdgcn_sched_barrier(0); };
+    auto first_w = [&](u32x4 (&w)[KC][NT], int c) { unroll<KC>([&](auto F) { load_w(w, c, F, F + 1); __builtin_amdgcn_sched_barrier(0); }); };
+    unroll<AD>([&](auto I) { first_a(a[I], c0 + I); first_w(w[I], c0 + I); });
 #pragma unroll
     for (int i = 0; i < WA_PER_THREAD; ++i) lds[0][i * THREADS + threadIdx.x] = a[0][i];
-    load_a(a[0], c0 + AD, 0, WA_PER_THREAD);
-    unroll<DW - 1 - AD>([&](auto I) { load_w(w[AD + I], c0 + AD + I, 0, KC); });
+    first_a(a[0], c0 + AD);
+    unroll<DW - 1 - AD>([&](auto I) { first_w(w[AD + I], c0 + AD + I); });
     __syncthreads();
     read_bh(bh[0], 0, 0);
 
