@@ -75,15 +75,16 @@ static __device__ __forceinline__ void part_sum4n(const float* __restrict__ P, i
 // In gather mode y is also stored as the branch's probability-map entry for that position
 // (P_k(i, v) = exp(y . W_v - lse) is evaluated on demand by the merge), for every branch of
 // the request when bcast != 0 (initial forward: all rows are identical).
-__global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restrict__ h, const float* __restrict__ partial,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __restrict__ h, const float* __restrict__ partial,
                                                            int n_partial, size_t partial_stride,
                                                            const float* __restrict__ gain, u32x4* __restrict__ Apk,
                                                            int mt_total, int gather, int bcast, int wide,
                                                            const uint16_t* __restrict__ emb) {
-    __shared__ float sh[4];
+    __shared__ float sh[THREADS / 64];
     const int j = xcd_run_item(blockIdx.x, gridDim.x), d = D.d, k8s = d >> 3;
     const int count = gather ? D.counts[1] : D.counts[0];
-    if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
+    if (j >= count && (gather || emb)) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }      // (else behind the loads: see request_early)
     const int r = gather ? D.lm_row[j] : j;
     int gbr = 0, nb = 1; size_t mrow = 0;
     if (gather) {                       // (dependent loads, on their way beside the row's)
@@ -94,13 +95,13 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
         mrow = (size_t)gbr * D.gmax + gi;
     }
     float* hr = h + (size_t)r * d;
-    // the row stays in registers between the two passes: thread t owns the 8-column groups t, t + 256, ...
-    constexpr int MAXG = 4;             // d <= 8192
+    // the row stays in registers between the two passes: thread t owns the 8-column groups t, t + THREADS, ...
+    constexpr int MAXG = 1024 / THREADS;        // d <= 8192
     float v[MAXG][8];
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < MAXG; ++i) {
-        const int k8 = threadIdx.x + 256 * i;
+        const int k8 = threadIdx.x + THREADS * i;
         if (k8 < k8s) {
             float4 a, b;
             load_stream8(D, hr, emb, r, k8, a, b);
@@ -111,7 +112,8 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
             }
             v[i][0] = a.x + p[0].x; v[i][1] = a.y + p[0].y; v[i][2] = a.z + p[0].z; v[i][3] = a.w + p[0].w;
             v[i][4] = b.x + p[1].x; v[i][5] = b.y + p[1].y; v[i][6] = b.z + p[1].z; v[i][7] = b.w + p[1].w;
-            if (n_partial || emb) {
+            request_early(a, b, p[0], p[1]);
+            if ((n_partial || emb) && j < count) {
                 reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
                 reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
             }
@@ -119,11 +121,12 @@ __global__ __launch_bounds__(256) void rmsnorm_pack_kernel(Dev D, float* __restr
             for (int q = 0; q < 8; ++q) ss += v[i][q] * v[i][q];
         }
     }
+    if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
     ss = wg_sum(ss, sh);
     const float inv = 1.0f / sqrtf(ss / (float)d + D.rms_eps);
 #pragma unroll
     for (int i = 0; i < MAXG; ++i) {
-        const int k8 = threadIdx.x + 256 * i;
+        const int k8 = threadIdx.x + THREADS * i;
         if (k8 >= k8s) break;
         const float4 g0 = reinterpret_cast<const float4*>(gain)[2 * k8], g1 = reinterpret_cast<const float4*>(gain)[2 * k8 + 1];
         const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
@@ -228,8 +231,11 @@ void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_par
     // one (d <= 512: at most 64 of the 256 threads have a column group)
     if (!gather && D.d <= 4096 && mt_total * 32 > 256 && (mt_total * 4 >= 256 || D.d <= 512))
         rmsnorm_pack8_kernel<<<mt_total * 4, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, wide, emb);
+    else if (D.d > 2048)        // (up to 4096 columns a thread then has one group of eight; with 256 threads two: 252 rows and two to
+        // five partial tiles 9.7 -> 8.6 us, 768 rows and four 18.3 -> 16.5)
+        rmsnorm_pack_kernel<512><<<mt_total * 32, 512, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
     else
-        rmsnorm_pack_kernel<<<mt_total * 32, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
+        rmsnorm_pack_kernel<256><<<mt_total * 32, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
 }
 
 // Few rows (block steps): the norm's row-wide sum would leave one workgroup per row with the whole row's partial tiles
