@@ -443,7 +443,7 @@ AttentionPlan attention_plan(const Dev& D, int max_seg_rows, int n_segs, int max
     // workgroups: 27.5 against 19.8), with few pages eight have too little each (12 pages, 320 tiles: 44.9 us against 43.3).
     // Where the tiles leave CUs idle the pages of a row are split over several workgroups and a second kernel merges the
     // partial results: worth it once the share of a CU's own stream that it saves (about 50 KB per us) exceeds that launch
-    // (100 tiles, 24 pages: 31.0 us unsplit, 19.8 + 5.7 in two).
+    // (100 tiles, 24 pages: 31.0 us unsplit, 20.1 + 5.0 in two).
     const int qtiles = (nflat + 31) / 32, tiles = qtiles * D.hkv * n_segs, wgs = std::max(1, seg_tiles * D.hkv), waves = max_pages > 16 ? 8 : 4;
     const double stream_us = max_pages * (D.hd * 512.0) / 50e3, combine_us = 7.0;
     int n_splits = std::min(std::min(256 / wgs, (max_pages + waves - 1) / waves), 16);
