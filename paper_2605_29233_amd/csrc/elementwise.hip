@@ -81,7 +81,7 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
                                                            const float* __restrict__ gain, u32x4* __restrict__ Apk,
                                                            int mt_total, int gather, int bcast, int wide,
                                                            const uint16_t* __restrict__ emb) {
-    __shared__ float sh[THREADS / 64];
+    __shared__ float sh[4];
     const int j = xcd_run_item(blockIdx.x, gridDim.x), d = D.d, k8s = d >> 3;
     const int count = gather ? D.counts[1] : D.counts[0];
     if (j >= count && (gather || emb)) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }      // (else behind the loads: see request_early)
@@ -95,14 +95,17 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
         mrow = (size_t)gbr * D.gmax + gi;
     }
     float* hr = h + (size_t)r * d;
-    // the row stays in registers between the two passes: thread t owns the 8-column groups t, t + THREADS, ...
-    constexpr int MAXG = 1024 / THREADS;        // d <= 8192
+    // The row stays in registers between the two passes.  256 threads: one 8-column group each (d <= 2048).  512: thread t of the first half
+    // owns the groups t (and t + 256 of a row of more than 4096 columns), thread t of the second half the one or two that follow 256 apart.
+    constexpr int MAXG = THREADS / 256;         // d <= 8192
+    const int t = threadIdx.x & 255, half = threadIdx.x >> 8, groups = THREADS == 512 && k8s > 512 ? 2 : 1;
+    auto group = [&](int i) { return (half * groups + i) * 256 + t; };
+    auto mine = [&](int i) { return i < groups && group(i) < k8s; };
     float v[MAXG][8];
-    float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < MAXG; ++i) {
-        const int k8 = threadIdx.x + THREADS * i;
-        if (k8 < k8s) {
+        const int k8 = group(i);
+        if (mine(i)) {
             float4 a, b;
             load_stream8(D, hr, emb, r, k8, a, b);
             float4 p[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
@@ -117,17 +120,34 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
                 reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
                 reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) ss += v[i][q] * v[i][q];
         }
     }
     if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
-    ss = wg_sum(ss, sh);
-    const float inv = 1.0f / sqrtf(ss / (float)d + D.rms_eps);
+    // The squares are added as by 256 threads that own the groups t, t + 256, ...: the second half goes on from the first's sums.  A row so has
+    // the same scale here and in rmsnorm_pack8_kernel, whichever of them a pass's row count takes.
+    float ss = 0.f;
+    auto squares = [&]() {
+#pragma unroll
+        for (int i = 0; i < MAXG; ++i)
+            if (mine(i)) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) ss += v[i][q] * v[i][q];
+            }
+    };
+    if constexpr (THREADS == 512) {
+        __shared__ float first[256];
+        if (half == 0) { squares(); first[t] = ss; }
+        __syncthreads();
+        if (half == 1) { ss = first[t]; squares(); }
+    } else squares();
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    if (half == THREADS / 256 - 1 && (t & 63) == 0) sh[t >> 6] = ss;
+    __syncthreads();
+    const float inv = 1.0f / sqrtf((sh[0] + sh[1] + sh[2] + sh[3]) / (float)d + D.rms_eps);
 #pragma unroll
     for (int i = 0; i < MAXG; ++i) {
-        const int k8 = threadIdx.x + THREADS * i;
-        if (k8 >= k8s) break;
+        const int k8 = group(i);
+        if (!mine(i)) break;
         const float4 g0 = reinterpret_cast<const float4*>(gain)[2 * k8], g1 = reinterpret_cast<const float4*>(gain)[2 * k8 + 1];
         const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
         float y[8];

@@ -491,3 +491,30 @@ def test_packed_rows_of_many_branches(requests, blocks):
         assert np.isfinite(v.conf()).all()
     finally:
         b.close()
+
+
+def test_a_rows_norm_does_not_depend_on_the_pass_it_runs_in():
+    """The first layer's keys and values of a row, from an initial forward of 1024 rows (a workgroup per row in the norm kernel) and from a
+    refresh of 2048 (eight rows per workgroup): same tokens, same sums in the projection, and the squares of a row of more than 2048
+    columns are added in one order by both norm kernels, so the caches are equal bit for bit."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT, BB_PERIODIC
+    from paper_2605_29233_amd.binding import gemm_plan
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("normtest", 1, 2112, 4, 4, 128, 64, 512, qkv_bias=False)
+    L, G, blocks = 1024, 64, (16, 32)
+    few, many = (gemm_plan(rows, 3 * 512, shape.d_model) for rows in (L, 2 * L))
+    assert (few["split_k"], few["chunks_per_split"]) == (many["split_k"], many["chunks_per_split"]), (few, many)
+    b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 8), Limits(1, 2, L, G, sum(blocks)), poison_workspace=True)
+    try:
+        b.load_weights(gen_weights(shape, 13))
+        rid = b.request_open(gen_prompt(shape, 13, 0, L - G), G, blocks)
+        b.refresh([rid], BB_INIT)
+        first = [b.get_kv(rid, k, 0) for k in range(2)]
+        print("norm of a row in passes of 1024 and 2048 rows", flush=True)
+        b.refresh([rid], BB_PERIODIC)
+        again = [b.get_kv(rid, k, 0) for k in range(2)]
+    finally:
+        b.close()
+    for kv, kv2 in zip(first, again):
+        for x, y in zip(kv, kv2):
+            assert np.isfinite(x).all() and np.array_equal(x, y), np.abs(x - y).max()
