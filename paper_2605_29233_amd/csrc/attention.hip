@@ -387,12 +387,16 @@ template <int HD>
 __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const float* __restrict__ part, u32x4* __restrict__ Apk,
                                                                 int mt_total, int seg_base, int n_splits, int wide) {
     const int gbr = seg_base + blockIdx.z;
-    const int seg_rows = D.seg_rows[gbr], seg_off = D.seg_off[gbr], group = D.hq / D.hkv, nflat = seg_rows * group, wg_base = blockIdx.y * 32, kvh = blockIdx.x;
+    const int seg_rows = D.seg_rows[gbr], seg_off = D.seg_off[gbr];
+    const int group = D.hq / D.hkv, nflat = seg_rows * group, wg_base = blockIdx.y * 32, kvh = blockIdx.x;
+    if (wg_base >= nflat) return;
     const float* src = part + (((size_t)blockIdx.z * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * n_splits * (64 + 32 * HD);
-    // (The loads of four splits are on their way together, and ask for their places before the segment's size is known: a tile past its end has a place and is not
-    // stored.  us per launch: 32 tiles in three splits 6.4 -> 4.8, 100 in two 5.6 -> 5.0.)
+    // The loads of four splits are on their way together.  us per launch: 32 tiles in three splits 6.4 -> 4.8, 100 in two 5.6 -> 5.0.  (None before
+    // the segment's size is known: the grid has a place for every tile of every slot of the context, and reading those of 255 empty
+    // segments, 32 tiles in three splits each, took 64 us.)
     for (int item = threadIdx.x; item < 32 * (HD / 8); item += 256) {
-        const int q = item / (HD / 8), d8 = item % (HD / 8);
+        const int q = item / (HD / 8), d8 = item % (HD / 8), f = wg_base + q;
+        if (f >= nflat) break;          // (items go through the tile's rows in order)
         float M = -INFINITY, lsum = 0.f, y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (int s0 = 0; s0 < n_splits; s0 += 4) {
             float m[4], l[4];
@@ -419,8 +423,6 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const flo
             }
         }
         const float inv = 1.0f / lsum;
-        const int f = wg_base + q;
-        if (f >= nflat) continue;
         const int hig = f / seg_rows, r = f % seg_rows;
         const int m = seg_off + r, k8 = ((kvh * group + hig) * HD) / 8 + d8;
 #pragma unroll

@@ -518,3 +518,45 @@ def test_a_rows_norm_does_not_depend_on_the_pass_it_runs_in():
     for kv, kv2 in zip(first, again):
         for x, y in zip(kv, kv2):
             assert np.isfinite(x).all() and np.array_equal(x, y), np.abs(x - y).max()
+
+
+def _class_us(b, ids, klass, steps=20):
+    """Shortest of three runs: microseconds per block step in the launches of one profile class."""
+    best = float("inf")
+    b.profile_enable()
+    for _ in range(3):
+        b.synchronize()
+        b.profile_read()
+        for _ in range(steps):
+            b.denoise_step(ids, want_view=False)
+        best = min(best, b.profile_read()[klass]["total_ms"] * 1e3 / steps)
+    b.profile_enable(False)
+    return best
+
+
+def test_empty_slots_cost_split_attention_nothing():
+    """One request whose attention tiles are split over three workgroups each, in a context of its own and in one of 64 requests x 4
+    branches: same plan, same logits bit for bit, and no time for the partial results of the 255 empty segments (3 x 255 x 32 tiles of 16.6 KB,
+    406 MB: at the 8 TB/s of the memory 51 us, where the launches themselves take about 20)."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("slottest", 1, 256, 32, 32, 128, 256, 1024, qkv_bias=False)
+    weights = dict(gen_weights(shape, 5, device="cuda:0"))
+    prompt = gen_prompt(shape, 5, 0, 704)
+    out, us = [], []
+    for requests, branches in ((1, 1), (64, 4)):
+        b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 8), Limits(requests, branches, 768, 64, 32), poison_workspace=True)
+        try:
+            assert b.attention_plan([32], 768) == (3, 4)
+            b.load_weights(weights.items())
+            b.keep_logits(True)
+            rid = b.request_open(prompt, 64, (32,))
+            b.refresh([rid], BB_INIT)
+            print(f"empty slots: {requests} x {branches}", flush=True)
+            out.append(b.denoise_step([rid]).logits().copy())
+            us.append(_class_us(b, [rid], "attention"))
+        finally:
+            b.close()
+    print("attention us per step:", us, flush=True)
+    assert np.isfinite(out[0][:, :-1]).all() and np.array_equal(out[0], out[1])
+    assert us[1] < 2 * us[0], us
