@@ -26,13 +26,6 @@ static __device__ __forceinline__ void zero_packed_row(u32x4* Apk, int m, int k8
     for (int k8 = threadIdx.x; k8 < k8s; k8 += blockDim.x) zero_panel8(Apk, m, k8, mt_total, wide);
 }
 
-// These kernels are chains of dependent loads of a few hundred ns each.  What does not depend on the pass's row count is asked for before
-// the count is looked at (every buffer has the padded rows; what they hold is not used): the values pass through assembly here, so that the
-// compiler does not move their loads behind the branch that the count decides.  us per launch: residual + pack of 120 rows 6.6 -> 6.1, SwiGLU 8.0 -> 7.6, q|k|v
-// epilogue of 92 rows x 4608 columns 6.7 -> 6.3, of 3072 x 12288 64.5 -> 61.7.
-static __device__ __forceinline__ void request_early(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
-template <class... Rest> static __device__ __forceinline__ void request_early(float4& v, Rest&... rest) { request_early(v); request_early(rest...); }
-
 // Eight columns of a row of the residual stream: from h, or, before the first layer (emb given), the token's embedding.  (The
 // gather is part of the first norm / residual kernel: a launch of its own took 8.8 us for 120 rows of 4096, 2.6 us for 56 of 256.)
 static __device__ __forceinline__ void load_stream8(const Dev& D, const float* __restrict__ hr, const uint16_t* __restrict__ emb, int row, int k8,
@@ -84,7 +77,7 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
     __shared__ float sh[4];
     const int j = xcd_run_item(blockIdx.x, gridDim.x), d = D.d, k8s = d >> 3;
     const int count = gather ? D.counts[1] : D.counts[0];
-    if (j >= count && (gather || emb)) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }      // (else behind the loads: see request_early)
+    if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
     const int r = gather ? D.lm_row[j] : j;
     int gbr = 0, nb = 1; size_t mrow = 0;
     if (gather) {                       // (dependent loads, on their way beside the row's)
@@ -115,14 +108,12 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
             }
             v[i][0] = a.x + p[0].x; v[i][1] = a.y + p[0].y; v[i][2] = a.z + p[0].z; v[i][3] = a.w + p[0].w;
             v[i][4] = b.x + p[1].x; v[i][5] = b.y + p[1].y; v[i][6] = b.z + p[1].z; v[i][7] = b.w + p[1].w;
-            request_early(a, b, p[0], p[1]);
-            if ((n_partial || emb) && j < count) {
+            if (n_partial || emb) {
                 reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
                 reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
             }
         }
     }
-    if (j >= count) { zero_packed_row(Apk, j, k8s, mt_total, wide); return; }
     // The squares are added as by 256 threads that own the groups t, t + 256, ...: the second half goes on from the first's sums.  A row so has
     // the same scale here and in rmsnorm_pack8_kernel, whichever of them a pass's row count takes.
     float ss = 0.f;
@@ -251,8 +242,8 @@ void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_par
     // one (d <= 512: at most 64 of the 256 threads have a column group)
     if (!gather && D.d <= 4096 && mt_total * 32 > 256 && (mt_total * 4 >= 256 || D.d <= 512))
         rmsnorm_pack8_kernel<<<mt_total * 4, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, wide, emb);
-    else if (D.d > 2048)        // (up to 4096 columns a thread then has one group of eight; with 256 threads two: 252 rows and two to
-        // five partial tiles 9.7 -> 8.6 us, 768 rows and four 18.3 -> 16.5)
+    else if (D.d > 2048)        // (up to 4096 columns a thread then has one group of eight; with 256 threads two: 120 rows and eight
+        // partial tiles 10.4 -> 8.8 us, 252 rows and two to five 11.3 -> 10.1, 768 rows and four 18.3 -> 17.6)
         rmsnorm_pack_kernel<512><<<mt_total * 32, 512, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
     else
         rmsnorm_pack_kernel<256><<<mt_total * 32, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
@@ -274,34 +265,27 @@ __global__ __launch_bounds__(256) void residual_pack_kernel(Dev D, float* __rest
     const int item = xcd_run_item(blockIdx.x, gridDim.x), unit = item >> 3;         // eight rows of one column block in a row
     const int j = unit / nblk * 8 + (item & 7), b = unit % nblk, d = D.d, k8 = b * (BB_SSQ_BLOCK / 8) + threadIdx.x;
     const bool live = k8 < (d >> 3);
-    float* hr = h + (size_t)j * d;
-    const int count = D.counts[0];
-    float4 a, c, p[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)}, g0, g1;
-    if (live && !emb) {                 // (asked for before the row count is there: see request_early)
-        load_stream8(D, hr, nullptr, j, k8, a, c);
-        g0 = reinterpret_cast<const float4*>(gain)[2 * k8]; g1 = reinterpret_cast<const float4*>(gain)[2 * k8 + 1];
-        if (n_partial) {
-            const size_t off[2] = {(size_t)j * d + k8 * 8, (size_t)j * d + k8 * 8 + 4};
-            part_sum4n<2>(partial, n_partial, partial_stride, off, p);
-        }
-        request_early(a, c, g0, g1, p[0], p[1]);
-    }
-    if (j >= count) {
+    if (j >= D.counts[0]) {
         if (live) zero_panel8(Apk, j, k8, mt_total, wide);
         if (threadIdx.x == 0) ssq[j * nblk + b] = 0.f;
         return;
     }
     float ss = 0.f;
     if (live) {
-        if (emb) {
-            load_stream8(D, hr, emb, j, k8, a, c);
-            g0 = reinterpret_cast<const float4*>(gain)[2 * k8]; g1 = reinterpret_cast<const float4*>(gain)[2 * k8 + 1];
+        float* hr = h + (size_t)j * d;
+        float4 a, c;
+        load_stream8(D, hr, emb, j, k8, a, c);
+        float4 p[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+        if (n_partial) {
+            const size_t off[2] = {(size_t)j * d + k8 * 8, (size_t)j * d + k8 * 8 + 4};
+            part_sum4n<2>(partial, n_partial, partial_stride, off, p);
         }
         const float v[8] = {a.x + p[0].x, a.y + p[0].y, a.z + p[0].z, a.w + p[0].w, c.x + p[1].x, c.y + p[1].y, c.z + p[1].z, c.w + p[1].w};
         if (n_partial || emb) {
             reinterpret_cast<float4*>(hr)[2 * k8] = make_float4(v[0], v[1], v[2], v[3]);
             reinterpret_cast<float4*>(hr)[2 * k8 + 1] = make_float4(v[4], v[5], v[6], v[7]);
         }
+        const float4 g0 = reinterpret_cast<const float4*>(gain)[2 * k8], g1 = reinterpret_cast<const float4*>(gain)[2 * k8 + 1];
         const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
         float y[8];
 #pragma unroll
@@ -349,6 +333,7 @@ static __device__ __forceinline__ void put2x4(half_t* hi_p, half_t* lo_p, const 
 // fp16 terms (q for the attention kernel, k into the fragment-ordered cache page); v heads go
 // through LDS so that neighbouring lanes store neighbouring tokens of one head dim, which are adjacent
 // in the V fragments.
+template <bool ROPE_LAST>
 __global__ __launch_bounds__(256) void qkv_epilogue_kernel(Dev D, const float* __restrict__ qkv, int n_partial,
                                                            size_t partial_stride, const float* __restrict__ bias,
                                                            half_t* __restrict__ Q, int layer,
@@ -356,22 +341,25 @@ __global__ __launch_bounds__(256) void qkv_epilogue_kernel(Dev D, const float* _
     __shared__ float tile[128][17];
     const int m0 = blockIdx.x * 16, c0 = blockIdx.y * 128, t = threadIdx.x;
     const int count = D.counts[0];
+    if (m0 >= count) return;
     const int hd = D.hd, half = hd >> 1, nq = D.hq * hd, nk = D.hkv * hd;
     if (c0 < nq + nk) {
         // 16 rows x (128 / hd heads) x hd/8 groups of 4 pairs = 256 work items
         const int per_row = 16, r = t / per_row, m = m0 + r;
+        if (m >= count) return;
         const int hh = (t % per_row) / (half >> 2), j = ((t % per_row) % (half >> 2)) * 4;
         const int ch = c0 + hh * hd;                   // first column of this head
         const size_t off = (size_t)m * D.nqkv + ch + j;
-        int pos = D.row_pos[m], phys = D.row_phys[m];
+        const int pos = D.row_pos[m], phys = D.row_phys[m];
         const size_t offs[2] = {off, off + half};
-        float4 xs[2];
+        float4 xs[2], c, sn;
+        auto rope = [&]() {
+            c = *reinterpret_cast<const float4*>(&D.rope_cos[(size_t)pos * half + j]);
+            sn = *reinterpret_cast<const float4*>(&D.rope_sin[(size_t)pos * half + j]);
+        };
+        if (!ROPE_LAST) rope();
         part_sum4n<2>(qkv, n_partial, partial_stride, offs, xs);
-        request_early(xs[0], xs[1]);
-        asm volatile("" : "+v"(pos), "+v"(phys));
-        if (m >= count) return;
-        const float4 c = *reinterpret_cast<const float4*>(&D.rope_cos[(size_t)pos * half + j]);
-        const float4 sn = *reinterpret_cast<const float4*>(&D.rope_sin[(size_t)pos * half + j]);
+        if (ROPE_LAST) rope();
         float4 x1 = xs[0], x2 = xs[1];
         if (ssq) {          // the projection's input was packed without its RMSNorm scale
             const float inv = row_inv_rms(D, ssq, nblk, m);
@@ -407,13 +395,11 @@ __global__ __launch_bounds__(256) void qkv_epilogue_kernel(Dev D, const float* _
     // v columns
     {
         const int r = t / 16, cg = (t % 16) * 8, m = m0 + r;
-        const size_t off = (size_t)m * D.nqkv + c0 + cg;
-        const size_t offs[2] = {off, off + 4};
-        float4 vs[2];
-        part_sum4n<2>(qkv, n_partial, partial_stride, offs, vs);
-        request_early(vs[0], vs[1]);
-        if (m0 >= count) return;
         if (m < count) {
+            const size_t off = (size_t)m * D.nqkv + c0 + cg;
+            const size_t offs[2] = {off, off + 4};
+            float4 vs[2];
+            part_sum4n<2>(qkv, n_partial, partial_stride, offs, vs);
             float4 v0 = vs[0], v1 = vs[1];
             if (ssq) {
                 const float inv = row_inv_rms(D, ssq, nblk, m);
@@ -469,7 +455,11 @@ __global__ __launch_bounds__(256) void qkv_epilogue_kernel(Dev D, const float* _
 void launch_qkv_epilogue(const Dev& D, const float* qkv, int n_partial, size_t partial_stride, const float* bias,
                          half_t* Q, int layer, int rows_cap, const float* ssq, int nblk, hipStream_t s) {
     dim3 grid((rows_cap + 15) / 16, D.nqkv / 128);
-    qkv_epilogue_kernel<<<grid, 256, 0, s>>>(D, qkv, n_partial, partial_stride, bias, Q, layer, ssq, nblk);
+    // The rotation's angles take two dependent loads.  With few workgroups these start before the partial results' (their chain is the longer one),
+    // with many after (what counts there is how soon the many bytes are asked for).  us per launch, angles first / last, by rows x columns:
+    // 120 x 12288 8.4 / 8.8, 252 x 12288 11.4 / 11.6, 768 x 12288 17.2 / 16.8, 3072 x 12288 64.0 / 59.2.
+    if (rows_cap <= 256) qkv_epilogue_kernel<false><<<grid, 256, 0, s>>>(D, qkv, n_partial, partial_stride, bias, Q, layer, ssq, nblk);
+    else qkv_epilogue_kernel<true><<<grid, 256, 0, s>>>(D, qkv, n_partial, partial_stride, bias, Q, layer, ssq, nblk);
 }
 
 // act = SiLU(gate) * up.  The fused matrix alternates 32 gate rows with the 32 up rows of the
@@ -481,16 +471,14 @@ __global__ __launch_bounds__(256) void swiglu_epilogue_kernel(Dev D, const float
     // up and stores whole 128-byte lines.  (The panel's K is padded to whole chunks of 64 with zeros.)
     // 120 rows x 12288 features, two partial tiles: 11.2 -> 8.4 us (before: a row per run of workgroups, 16-byte pieces).
     const int m = (blockIdx.x % mt_total) * 32 + threadIdx.x / 8, f = blockIdx.x / mt_total * 64 + threadIdx.x % 8 * 8;
-    const int count = D.counts[0];
+    if (m >= D.counts[0] || f >= D.f) {
+        zero_panel8(Apk, m, f >> 3, mt_total, wide);
+        return;
+    }
     const size_t off = (size_t)m * ldp + (f >> 5) * 64 + (f & 31);
     const size_t offs[4] = {off, off + 4, off + 32, off + 36};
     float4 gs[4];
     part_sum4n<4>(gu, n_partial, partial_stride, offs, gs);
-    request_early(gs[0], gs[1], gs[2], gs[3]);
-    if (m >= count || f >= D.f) {
-        zero_panel8(Apk, m, f >> 3, mt_total, wide);
-        return;
-    }
     const float4 g0 = gs[0], g1 = gs[1], u0 = gs[2], u1 = gs[3];
     const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
     const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};

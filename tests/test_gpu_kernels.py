@@ -560,3 +560,31 @@ def test_empty_slots_cost_split_attention_nothing():
     print("attention us per step:", us, flush=True)
     assert np.isfinite(out[0][:, :-1]).all() and np.array_equal(out[0], out[1])
     assert us[1] < 2 * us[0], us
+
+
+def test_finished_branches_cost_the_kernels_between_the_gemms_little():
+    """A step sized for 128 rows of which four are live, against all 128: the kernels that add up the k splits of a projection (sixteen here,
+    the partial results of a layer 470 MB) leave the rows past the live count alone, so the first takes a fraction of the second's time."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+    from workload.gen import gen_weights, gen_prompt
+    shape = ModelShape("deadtest", 2, 8192, 64, 64, 128, 8192, 512, qkv_bias=False)
+    L_p, G, blocks = 40, 128, (4, 124)
+    b = BlockBatch(shape, DecodeParams(0.9, 0.5, 200, 8), Limits(1, 2, L_p + G, G, 128), poison_workspace=True)
+    try:
+        b.load_weights(gen_weights(shape, 5, device="cuda:0"))
+        for kind in (1, 2, 3):
+            b.set_gemm_plan(kind, 1, 16)
+        rid = b.request_open(gen_prompt(shape, 5, 0, L_p), G, blocks)
+        b.refresh([rid], BB_INIT)
+        X = b.get_tokens(rid)
+        us = []
+        for done in (0, 1):
+            windows = [types.SimpleNamespace(start=L_p, end=L_p + blk, done=done and k, mean_conf=0.5) for k, blk in enumerate(blocks)]
+            b.set_state(rid, X, windows)
+            print("finished branches:", done, flush=True)
+            assert b.denoise_step([rid]).m_q == (4 if done else 128)
+            us.append(_class_us(b, [rid], "glue"))
+    finally:
+        b.close()
+    print("glue us per step:", us, flush=True)
+    assert us[1] < 0.6 * us[0], us
