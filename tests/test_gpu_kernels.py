@@ -300,35 +300,42 @@ def test_swiglu_in_the_gemm_epilogue_with_the_deferred_norm_scale():
 
 
 @pytest.mark.parametrize("blocks,d_ffn", [
-    ((8,), 64),                     # one m-tile; a single workgroup
-    ((32, 24), 688),                # two, the second with padding rows; padded columns of the fused matrix
+    ((8,), 688),                    # one m-tile, most of its rows padding; an odd number of column tiles per wave and group, padded columns
+    ((32,), 1392),                  # one, full
+    ((32, 24), 688),                # two, the second with padding rows
     ((64, 32), 1376 + 16),          # three
     ((64, 48, 16), 33024 + 16),     # four; more column groups than workgroups (one each of 256): the halves' place is used again
 ])
 def test_swiglu_across_two_waves_is_the_one_within_a_wave(blocks, d_ffn):
     """The gate/up projection with one column tile per wave and k whole finishes SiLU(gate) * up with halves that two waves swap through
-    LDS; with two tiles per wave both factors are in one wave's registers.  Same sums, same expressions: logits and caches equal bit for bit."""
+    LDS; with two tiles per wave both factors are in one wave's registers.  Same sums, same expressions: logits and caches equal bit for bit.
+    (Rows of 512 columns: shorter k ranges than eight chunks are not split.)  Neither has a SwiGLU launch of its own: the step's launches between the GEMMs are three per layer, the final norm, the
+    vocabulary merge and the packing; with the k range in two there is one more per layer."""
     from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
     from workload.gen import gen_weights, gen_prompt
-    shape = ModelShape("swaptest", 2, 256, 4, 4, 64, d_ffn, 1024, qkv_bias=False)
+    shape = ModelShape("swaptest", 2, 512, 4, 4, 64, d_ffn, 1024, qkv_bias=False)
+    assert (d_ffn + 63) // 64 * 4 >= 8          # column tiles: with fewer than eight, two per wave would be taken back to one
     weights = dict(gen_weights(shape, 11))
     prompt = gen_prompt(shape, 11, 0, 40)
-    G, res = 64, {}
-    for nt in (1, 2):
+    G, res, glue = 64, {}, {}
+    for nt, split in ((1, 1), (2, 1), (1, 2)):
         b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 8), Limits(1, len(blocks), 40 + G, G, sum(blocks)), poison_workspace=True)
         try:
             b.load_weights(weights.items())
             b.keep_logits(True)
-            b.set_gemm_plan(2, nt, 1)
+            b.set_gemm_plan(2, nt, split)
             rid = b.request_open(prompt, G, blocks)
             b.refresh([rid], BB_INIT)
             b.merge_commit([rid])
-            print(f"swiglu swap blocks={blocks} d_ffn={d_ffn} nt={nt}", flush=True)
+            print(f"swiglu swap blocks={blocks} d_ffn={d_ffn} nt={nt} split={split}", flush=True)
+            b.profile_enable()
             v = b.denoise_step([rid])
-            res[nt] = [v.logits().copy()] + [x for k in range(len(blocks)) for l in range(2) for x in b.get_kv(rid, k, l)]
+            glue[nt, split] = b.profile_read()["glue"]["launches"]
+            res[nt, split] = [v.logits().copy()] + [x for k in range(len(blocks)) for l in range(2) for x in b.get_kv(rid, k, l)]
         finally:
             b.close()
-    for a, r in zip(res[1], res[2]):
+    assert glue == {(1, 1): 9, (2, 1): 9, (1, 2): 11}, glue
+    for a, r in zip(res[1, 1], res[2, 1]):
         assert np.isfinite(a[..., :-1]).all() and np.array_equal(a, r)
 
 
@@ -448,25 +455,30 @@ def test_plan_overrides_leave_larger_panels_alone():
         b.close()
 
 
-@pytest.mark.parametrize("requests,blocks", [
-    (7, (4, 8, 16)),                # 21 branches: more than the packing kernel has waves
-    (32, (4, 4, 8, 8, 16, 16, 4, 8)),       # 256: the most there can be
-    (1, (16,)),
+@pytest.mark.parametrize("requests,blocks,G", [
+    (1, (16,), 32),                 # one branch, four waves
+    (1, (4, 8, 16, 32, 8), 32),     # five branches, as many waves
+    (3, (80, 16, 100), 224),        # nine; windows of more than 64 positions, over two and three pages
+    (2, (4, 8, 16, 32, 4, 8, 16, 32), 32),      # sixteen: the most waves
+    (6, (4, 8, 16), 32),            # eighteen: some waves have two branches
+    (32, (4, 4, 8, 8, 16, 16, 4, 8), 32),       # 256: the most there can be
 ])
-def test_packed_rows_of_many_branches(requests, blocks):
-    """The block step's row list, for every number of branches per wave of the packing kernel: rows in branch order, every position of
-    every unfinished window, the masked ones listed for the LM head in the same order; from the windows and tokens set before."""
-    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
+def test_packed_rows_of_many_branches(requests, blocks, G):
+    """The block step's row list for one to sixteen branches per wave of the packing kernel: rows in branch order, every position of
+    every unfinished window, the masked ones listed for the LM head in the same order; from the windows and tokens set before.  And its list of pages
+    to copy: after the step the keys and values outside the windows are those before it, bit for bit, in pages that the branches owned and in
+    those they shared, and inside the windows those of a refresh of the same tokens (another GEMM plan: to 1e-3 of the largest value)."""
+    from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT, BB_PERIODIC
     from workload.gen import gen_weights, gen_prompt
     shape = ModelShape("packtest", 1, 128, 2, 2, 64, 128, 512, qkv_bias=False)
-    G, Lp, N = 32, 20, len(blocks)
+    Lp, N = 20, len(blocks)
     rng = np.random.default_rng(requests)
     b = BlockBatch(shape, DecodeParams(0.9, 0.5, 4, 8), Limits(requests, N, Lp + G, G, requests * sum(blocks)), poison_workspace=True)
     try:
         b.load_weights(gen_weights(shape, 3))
         b.keep_logits(True)
         ids = [b.request_open(gen_prompt(shape, 3, i, Lp), G, blocks) for i in range(requests)]
-        rows, lm = [], []
+        rows, lm, live = [], [], []
         for i, rid in enumerate(ids):
             b.refresh([rid], BB_INIT)
             X = rng.integers(0, shape.vocab - 1, (N, Lp + G), dtype=np.int32)
@@ -482,13 +494,27 @@ def test_packed_rows_of_many_branches(requests, blocks):
                 if not done:
                     lm += [len(rows) + j for j in range(blk) if masked[j]]
                     rows += [(rid * N + k, start + j) for j in range(blk)]
+                    live.append((rid, k, slice(start, start + blk)))
             b.set_state(rid, X, windows)
+        before = [b.get_kv(rid, k, 0) for rid in ids for k in range(N)]
         print(f"packed rows requests={requests} branches={N}", flush=True)
         v = b.denoise_step(ids)
         gbr, pos = v.rows()
         assert list(zip(gbr.tolist(), pos.tolist())) == rows
         assert v.lm_rows().tolist() == lm
         assert np.isfinite(v.conf()).all()
+        after = [b.get_kv(rid, k, 0) for rid in ids for k in range(N)]
+        b.refresh(ids, BB_PERIODIC)
+        windows = {(rid, k): w for rid, k, w in live}
+        for i, (rid, k) in enumerate((rid, k) for rid in ids for k in range(N)):
+            outside = np.ones(Lp + G, dtype=bool)
+            w = windows.get((rid, k))
+            if w is not None:
+                outside[w] = False
+                for x, r in zip(after[i], b.get_kv(rid, k, 0)):
+                    assert np.abs(x[w] - r[w]).max() <= 1e-3 * np.abs(r).max()
+            for x, x0 in zip(after[i], before[i]):
+                assert np.isfinite(x).all() and np.array_equal(x[outside], x0[outside])
     finally:
         b.close()
 

@@ -94,6 +94,29 @@ def test_tiny_variants(seed, blocks, prompt_len, gen_len, decode):
     check_report(s)
 
 
+@pytest.mark.parametrize("d_model", [2112, 4096, 4160, 8192])
+def test_rows_of_more_than_2048_columns(d_model):
+    """Full passes and final norms of rows that 512 threads share in the norm kernel: eight columns per thread with only eight of the second
+    half at work, and with all; sixteen (more than 4096 columns) likewise.  Against the oracle in fp64, with a refresh every second step."""
+    shape = ModelShape("widerow", 1, d_model, 2, 2, 64, 64, 512)
+    s = run_case(shape, DecodeParams(0.9, 0.5, 8, 2, 0), 200, 60, (8, 16), seed=31, max_steps=3)
+    assert s.rep.max_logit_err <= 3e-2
+    check_report(s)
+
+
+@pytest.mark.parametrize("blocks", [(32,), (24, 32)])
+def test_gate_and_up_of_two_waves_over_a_long_k(blocks):
+    """Steps of one and two m-tiles whose gate/up projection has one column tile per wave and its 32 chunks of k whole: SwiGLU comes from
+    halves that two waves exchange (padded columns of the fused matrix among them).  Against the oracle in fp64."""
+    from paper_2605_29233_amd.binding import gemm_plan
+    shape = ModelShape("longk", 1, 2048, 2, 2, 64, 10240 + 16, 512)
+    p = gemm_plan(sum(blocks), (shape.d_ffn + 63) // 64 * 128, shape.d_model)
+    assert (p["nt"], p["split_k"], p["chunks_per_split"]) == (1, 1, 32), p
+    s = run_case(shape, DecodeParams(0.9, 0.5, 8, 8, 0), 40, 64, blocks, seed=32, max_steps=2)
+    assert s.rep.max_logit_err <= 3e-2
+    check_report(s)
+
+
 @pytest.mark.parametrize("seed", range(100, 124))
 def test_random_configurations(seed):
     """Seeded draws of model shape (MHA head 64, GQA with bias, head 128), block-size set, decode parameters
