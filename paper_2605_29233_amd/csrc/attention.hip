@@ -391,9 +391,9 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(Dev D, const flo
     const int group = D.hq / D.hkv, nflat = seg_rows * group, wg_base = blockIdx.y * 32, kvh = blockIdx.x;
     if (wg_base >= nflat) return;
     const float* src = part + (((size_t)blockIdx.z * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * n_splits * (64 + 32 * HD);
-    // The loads of four splits are on their way together.  us per launch: 32 tiles in three splits 6.4 -> 4.8, 100 in two 5.6 -> 5.0.  (None before
-    // the segment's size is known: the grid has a place for every tile of every slot of the context, and reading those of 255 empty
-    // segments, 32 tiles in three splits each, took 64 us.)
+    // The loads of four splits are on their way together.  us per launch: 32 tiles in three splits 6.4 -> 4.8, 100 in two
+    // 5.6 -> 5.0.  (None before the segment's size is known: the grid has a place for every tile of every slot of the context, and
+    // reading those of 255 empty segments, 32 tiles in three splits each, took 64 us.)
     for (int item = threadIdx.x; item < 32 * (HD / 8); item += 256) {
         const int q = item / (HD / 8), d8 = item % (HD / 8), f = wg_base + q;
         if (f >= nflat) break;          // (items go through the tile's rows in order)
@@ -444,8 +444,9 @@ AttentionPlan attention_plan(const Dev& D, int max_seg_rows, int n_segs, int max
     // workgroup per CU four waves leave the CU's loads idle (80 pages, 256 tiles: 236 us against 149; 24 pages, 200
     // workgroups: 27.5 against 19.8), with few pages eight have too little each (12 pages, 320 tiles: 44.9 us against 43.3).
     // Where the tiles leave CUs idle the pages of a row are split over several workgroups and a second kernel merges the
-    // partial results: worth it once the share of a CU's own stream that it saves (about 50 KB per us) exceeds that launch
-    // (100 tiles, 24 pages: 31.0 us unsplit, 20.1 + 5.0 in two).
+    // partial results: worth it once the share of a CU's own stream that it saves (about 50 KB per us) exceeds that launch, its
+    // place in the stream and the store of the partial results (100 tiles, 24 pages: 31.0 us unsplit, 20.1 + 5.0 in two; the launch
+    // alone takes 4.8 to 5.0, and 7.0 dates from when it took 5.6 to 6.4: lower values are not measured).
     const int qtiles = (nflat + 31) / 32, tiles = qtiles * D.hkv * n_segs, wgs = std::max(1, seg_tiles * D.hkv), waves = max_pages > 16 ? 8 : 4;
     const double stream_us = max_pages * (D.hd * 512.0) / 50e3, combine_us = 7.0;
     int n_splits = std::min(std::min(256 / wgs, (max_pages + waves - 1) / waves), 16);

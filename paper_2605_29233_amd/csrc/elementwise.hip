@@ -88,8 +88,9 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
         mrow = (size_t)gbr * D.gmax + gi;
     }
     float* hr = h + (size_t)r * d;
-    // The row stays in registers between the two passes.  256 threads: one 8-column group each (d <= 2048).  512: thread t of the first half
-    // owns the groups t (and t + 256 of a row of more than 4096 columns), thread t of the second half the one or two that follow 256 apart.
+    // The row stays in registers between the two passes.  256 threads: one 8-column group each (d <= 2048).  512: thread t of the
+    // first half owns the group t (and t + 256 of a row of more than 4096 columns), thread t of the second half the one or two that
+    // follow 256 apart.
     constexpr int MAXG = THREADS / 256;         // d <= 8192
     const int t = threadIdx.x & 255, half = threadIdx.x >> 8, groups = THREADS == 512 && k8s > 512 ? 2 : 1;
     auto group = [&](int i) { return (half * groups + i) * 256 + t; };
@@ -114,8 +115,8 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_pack_kernel(Dev D, float* __r
             }
         }
     }
-    // The squares are added as by 256 threads that own the groups t, t + 256, ...: the second half goes on from the first's sums.  A row so has
-    // the same scale here and in rmsnorm_pack8_kernel, whichever of them a pass's row count takes.
+    // The squares are added as by 256 threads that own the groups t, t + 256, ...: the second half goes on from the first's sums.
+    // A row so has the same scale here and in rmsnorm_pack8_kernel, whichever of them a pass's row count takes.
     float ss = 0.f;
     auto squares = [&]() {
 #pragma unroll
@@ -242,8 +243,9 @@ void launch_rmsnorm_pack(const Dev& D, float* h, const float* partial, int n_par
     // one (d <= 512: at most 64 of the 256 threads have a column group)
     if (!gather && D.d <= 4096 && mt_total * 32 > 256 && (mt_total * 4 >= 256 || D.d <= 512))
         rmsnorm_pack8_kernel<<<mt_total * 4, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, wide, emb);
-    else if (D.d > 2048)        // (up to 4096 columns a thread then has one group of eight; with 256 threads two: 120 rows and eight
-        // partial tiles 10.4 -> 8.8 us, 252 rows and two to five 11.3 -> 10.1, 768 rows and four 18.3 -> 17.6)
+    else if (D.d > 2048)
+        // (up to 4096 columns a thread then has one group of eight; with 256 threads two: 120 rows and eight partial tiles
+        // 10.4 -> 8.8 us, 252 rows and two to five 11.3 -> 10.1, 768 rows and four 18.3 -> 17.6)
         rmsnorm_pack_kernel<512><<<mt_total * 32, 512, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
     else
         rmsnorm_pack_kernel<256><<<mt_total * 32, 256, 0, s>>>(D, h, partial, n_partial, partial_stride, gain, Apk, mt_total, gather, bcast, wide, emb);
@@ -455,9 +457,9 @@ __global__ __launch_bounds__(256) void qkv_epilogue_kernel(Dev D, const float* _
 void launch_qkv_epilogue(const Dev& D, const float* qkv, int n_partial, size_t partial_stride, const float* bias,
                          half_t* Q, int layer, int rows_cap, const float* ssq, int nblk, hipStream_t s) {
     dim3 grid((rows_cap + 15) / 16, D.nqkv / 128);
-    // The rotation's angles take two dependent loads.  With few workgroups these start before the partial results' (their chain is the longer one),
-    // with many after (what counts there is how soon the many bytes are asked for).  us per launch, angles first / last, by rows x columns:
-    // 120 x 12288 8.4 / 8.8, 252 x 12288 11.4 / 11.6, 768 x 12288 17.2 / 16.8, 3072 x 12288 64.0 / 59.2.
+    // The rotation's angles take two dependent loads.  With few workgroups these start before the partial results' (their chain is
+    // the longer one), with many after (what counts there is how soon the many bytes are asked for).  us per launch, angles first /
+    // last, by rows x columns: 120 x 12288 8.4 / 8.8, 252 x 12288 11.4 / 11.6, 768 x 12288 17.2 / 16.8, 3072 x 12288 64.0 / 59.2.
     if (rows_cap <= 256) qkv_epilogue_kernel<false><<<grid, 256, 0, s>>>(D, qkv, n_partial, partial_stride, bias, Q, layer, ssq, nblk);
     else qkv_epilogue_kernel<true><<<grid, 256, 0, s>>>(D, qkv, n_partial, partial_stride, bias, Q, layer, ssq, nblk);
 }
@@ -505,8 +507,8 @@ void launch_swiglu_epilogue(const Dev& D, const float* gu, int n_partial, size_t
 __global__ __launch_bounds__(256) void vocab_finish_kernel(Dev D, int bcast) {
     const int j = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (j >= D.counts[1]) return;
-    // The row's place in the probability map takes three dependent loads: they are on their way beside the tiles, of which eight per lane are asked
-    // for together (494 tiles, 240 rows: 9.0 -> 7.6 us).
+    // The row's place in the probability map takes three dependent loads: they are on their way beside the tiles, of which eight
+    // per lane are asked for together (494 tiles, 240 rows: 9.0 -> 7.6 us).
     const int r = D.lm_row[j];
     int gbr = D.row_gbr[r], nb = 1;
     const int slot = gbr / D.max_br;

@@ -60,10 +60,10 @@ static __device__ __forceinline__ void fp16x8_to_e4m3x8(const u32x4& w, int& lo,
 
 // WEPI_PARTIAL: P[split][m][n] (fp32, leading dimension ldp) = this workgroup's share of the k range.
 // WEPI_SWIGLU: the weight matrix is the fused gate/up projection (32 gate rows alternate with the 32 up rows of the
-// same features; k not split): writes SiLU(gate) * up as the wide-format panel Opk of the down projection.  With two tiles per wave both factors
-// are in its registers; with one, waves 2 i and 2 i + 1 hold them and swap halves through LDS, so that each finishes 16 of the 32 features.  (Before, these
-// passes stored the projection and a launch of its own read it back: us per layer, 24576 x 4096 at 32 rows 36.0 + 4.6 -> 36.3, 1408 x 256 at 56 rows
-// 5.4 + 3.8 -> 8.1.)
+// same features; k not split): writes SiLU(gate) * up as the wide-format panel Opk of the down projection.  With two tiles per
+// wave both factors are in its registers; with one, waves 2 i and 2 i + 1 hold them and swap halves through LDS, so that each
+// finishes 16 of the 32 features.  (Before, these passes stored the projection and a launch of its own read it back: us per
+// layer, 24576 x 4096 at 32 rows 36.0 + 4.6 -> 36.3, 1408 x 256 at 56 rows 5.4 + 3.8 -> 8.1.)
 //
 // Chunk pipeline (one wave per SIMD, nothing else hides a stall), five phases per 64 k:
 //   fp16 k-step 0: MFMAs | LDS reads of step 1 | LDS writes of chunk c+1's activations (loaded during c-AD), first half
@@ -129,9 +129,11 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gemm_wide_kernel(const u32x4* _
     }
     const u32x4* abase = Apk + (size_t)mt0 * (BB_WFRAGS * 64);
     const size_t a_chunk = (size_t)mt_total * (BB_WFRAGS * 64);
-    // Past the end of the k range the loads are issued for the wait counts only: all lanes then read one address (a mask, not a choice, which
-    // would cut the pipeline's block in two).  Before, they fetched the last chunk again two or three times, which the epilogue then waited for: us per launch
-    // at 32 rows, 12288 x 4096 in two splits 20.7 -> 19.0, 24576 x 4096 37.5 -> 35.7, 4096 x 4096 and 4096 x 12288 in eight 14.9 -> 14.2 on average; at 120 rows within 1 %.
+    // Past the end of the k range the loads are issued for the wait counts only: all lanes then read one address (a mask, not a
+    // choice, which would cut the pipeline's block in two).  Before, they fetched the last chunk again two or three times, which
+    // the epilogue then waited for.  us per launch, with the scalar bases and the prologue's order that came with it: at 32 rows,
+    // 12288 x 4096 in two splits 20.7 -> 19.0, 24576 x 4096 37.5 -> 35.7, 4096 x 4096 and 4096 x 12288 in eight 14.9 -> 14.2 on
+    // average; at 120 rows within 1 %.
     auto inside = [&](int c) { return (unsigned)((c - c1) >> 31); };
     auto load_a = [&](u32x4 (&a)[WA_PER_THREAD], int c, int lo, int hi) {
         const u32x4* p = abase + (size_t)min(c, c1 - 1) * a_chunk;
@@ -382,6 +384,9 @@ static int block_step_body(int mt_total, int nt) {
     return nt == 3 ? 4 : (mt_total + groups - 1) / groups;
 }
 
+// fusable: only bb_debug_gemm_plan and the sizing of the buffers set it here.  A forward of up to 128 rows does not, since its norm
+// is deferred, although it does take SwiGLU from the epilogue of any plan that leaves k whole, with one tile per wave too: neither
+// the SwiGLU launch behind a split plan nor the partial tiles that a fused one does not write are in the price of its plans.
 static GemmPlan plan_one_group(int mt_total, int N, int K, bool fusable) {
     const int n_tiles = N / 32, total_chunks = (K + 63) / 64;
     GemmPlan best;

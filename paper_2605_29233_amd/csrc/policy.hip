@@ -34,8 +34,9 @@ static __device__ __forceinline__ float wg_sum_f(float v, float* sh) {
 // window; rows still masked are additionally listed for the LM head.  Pages under a window
 // that the branch does not own yet are queued for copy-on-write and re-pointed.
 //
-// One workgroup, a wave per branch (round robin).  A chain of dependent loads; what the second walk over a branch needs of the first is kept in LDS.
-// Up to sixteen waves and a parallel prefix sum, before four and a serial one: us per launch with 64 branches 46.2 -> 15.2, with six 8.2 -> 6.1.
+// One workgroup, a wave per branch (round robin).  A chain of dependent loads; what the second walk over a branch needs of the
+// first is kept in LDS.  Up to sixteen waves and a parallel prefix sum, before four and a serial one: us per launch with 64
+// branches 46.2 -> 15.2, with six 8.2 -> 6.1.
 __global__ __launch_bounds__(1024) void pack_step_kernel(Dev D, int n_req) {
     __shared__ int s_rows[256], s_lm[256], s_off[256], s_lmoff[256], s_slot[256], s_start[256], s_tot[8];
     const int nb_all = D.max_req * D.max_br, nb = n_req * D.max_br, t = threadIdx.x, waves = blockDim.x >> 6;

@@ -309,8 +309,8 @@ def test_swiglu_in_the_gemm_epilogue_with_the_deferred_norm_scale():
 def test_swiglu_across_two_waves_is_the_one_within_a_wave(blocks, d_ffn):
     """The gate/up projection with one column tile per wave and k whole finishes SiLU(gate) * up with halves that two waves swap through
     LDS; with two tiles per wave both factors are in one wave's registers.  Same sums, same expressions: logits and caches equal bit for bit.
-    (Rows of 512 columns: shorter k ranges than eight chunks are not split.)  Neither has a SwiGLU launch of its own: the step's launches between the GEMMs are three per layer, the final norm, the
-    vocabulary merge and the packing; with the k range in two there is one more per layer."""
+    Neither has a SwiGLU launch of its own: the step's launches between the GEMMs are three per layer, the final norm, the vocabulary merge
+    and the packing; with the k range in two there is one more per layer.  (Rows of 512 columns: fewer than eight chunks of k are not split.)"""
     from paper_2605_29233_amd import BlockBatch, Limits, BB_INIT
     from workload.gen import gen_weights, gen_prompt
     shape = ModelShape("swaptest", 2, 512, 4, 4, 64, d_ffn, 1024, qkv_bias=False)
