@@ -613,4 +613,4 @@ def test_finished_branches_cost_the_kernels_between_the_gemms_little():
     finally:
         b.close()
     print("glue us per step:", us, flush=True)
-    assert us[1] < 0.6 * us[0], us
+    assert us[1] < 0.7 * us[0], us          # (0.47 to 0.49; 0.89 with every row read)
